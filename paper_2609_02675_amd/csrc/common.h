@@ -77,6 +77,14 @@ struct SceneDev {
   int pad;
 };
 
+// What a wavefront of the flat iteration works on: the bodies [first, first +
+// count) of one scene, lpb lanes each.
+struct FlatWave {
+  int first, count, lpb, contact;  // lpb: CL for a contact wave, else 1
+  int scene, ce0, ccap;            // contact slots: ccap per body from ce0, the first body's
+  int iters;                       // K, or 0 when the scene has no steps left: set every step
+};
+
 // first contact slot of body i of scene S
 __device__ __forceinline__ size_t ce_base(const SceneDev& S, int i) {
   return (size_t)S.ce_off + (size_t)(i - S.body_off) * (size_t)S.ccap;

@@ -57,6 +57,14 @@ __device__ __forceinline__ T rsqrt_(T x) {
     return (T)1 / sqrt(x);
 }
 
+// Values of their own: the compiler fuses no product across this point, so that
+// code inlined in several kernels rounds alike in all of them.
+template <int N, typename T>
+__device__ __forceinline__ void settle(T* x) {
+#pragma unroll
+  for (int k = 0; k < N; ++k) asm("" : "+v"(x[k]));
+}
+
 // ---- 3x3 helpers (row-major) ------------------------------------------------
 
 template <typename T>

@@ -462,7 +462,8 @@ struct Engine {
   static constexpr int BRUTE_MAX = 2048;
   // predict: the prep kernel also runs the step's prediction for the bodies
   // [0, min(cap.n, contact bodies))
-  void launch_contacts(int n_scenes, hipStream_t st, bool predict = false) {
+  void launch_contacts(int n_scenes, hipStream_t st, bool predict = false, FlatWave* waves = nullptr,
+                       const int* n_waves = nullptr) {
     View<T> v = view();
     v.n = std::min(cap.n, ncb);
     ContactBuf cb{tb,    bucket_count, bucket_start, bucket_fill, brec,  reach,   hist,
@@ -471,7 +472,7 @@ struct Engine {
     const bool brute = n_scenes == 1 && n <= BRUTE_MAX;
     const int nbk = brute ? 0 : tb;  // bucket counts cleared by the prep kernel
     hipLaunchKernelGGL(k_contact_prep<T>, grid_for(std::max({n, REACH_BINS * n_scenes, nbk}), 256), dim3(256), 0,
-                       st, v, cb, n_scenes, nbk, predict);
+                       st, v, cb, n_scenes, nbk, predict, waves, n_waves);
     hipLaunchKernelGGL(k_contact_reach<T>, grid_for(n, 256), dim3(256), 0, st, v, cb);
     if (brute) {
       // one scene of few bodies: all pairs directly, no spatial hash
@@ -550,9 +551,9 @@ struct Engine {
   // the K iteration launches of a flat step, CL lanes per contact body; by
   // default one wavefront per workgroup, so that a small scene's waves spread
   // over as many CUs (and L1 caches) as there are waves
-  template <int CL>
-  void launch_iterations(int kmax, bool contacts, bool history, hipStream_t st, const FlatWave* waves,
-                         const int* n_waves, int wave_grid, double* hn, double* hd) {
+  template <int CL, bool EARLY>
+  void launch_iterations_as(int kmax, bool contacts, int ccap, hipStream_t st, const FlatWave* waves,
+                            const int* n_waves, int wave_grid, double* hn, double* hd) {
     View<T> v = view();
     const int gw = group_waves;
     const dim3 wg(64 * gw);
@@ -560,13 +561,29 @@ struct Engine {
     const dim3 g1 = grid_for(cap.n, 64 * gw);
     const dim3 gwv((unsigned)std::max(1, (wave_grid + gw - 1) / gw));
     for (int k = 0; k < kmax; ++k) {
-      if (waves && !history)
-        hipLaunchKernelGGL((k_iterate_waves<T, CL>), gwv, wg, 0, st, v, k, waves, n_waves);
+      if (waves)
+        hipLaunchKernelGGL((k_iterate_waves<T, CL, EARLY>), gwv, wg, 0, st, v, k, waves, n_waves);
       else if (contacts)
-        hipLaunchKernelGGL((k_iterate<T, true, CL>), gc, wg, 0, st, v, k, hn, hd);
+        hipLaunchKernelGGL((k_iterate<T, true, CL, EARLY>), gc, wg, 0, st, v, k, kmax, ccap, hn, hd);
       else
-        hipLaunchKernelGGL((k_iterate<T, false, 1>), g1, wg, 0, st, v, k, hn, hd);
+        hipLaunchKernelGGL((k_iterate<T, false, 1, EARLY>), g1, wg, 0, st, v, k, kmax, 0, hn, hd);
     }
+  }
+  // At most this many waves, one per SIMD, take the iteration's latency variant:
+  // beyond it its registers cost more waves in flight than its early loads save.
+  // Step times, the other variant against this one: piles of 5,000 boxes (312
+  // waves) 0.376 against 0.332 ms, of 16,000 (1,000 waves) 0.536 against 0.502,
+  // of 40,000 (2,500 waves) 0.946 against 0.983; in FP64 5,000 boxes 0.423
+  // against 0.401, 20,000 (1,250 waves) 0.790 against 0.928.
+  static constexpr long long EARLY_WAVES = 1024;
+  template <int CL>
+  void launch_iterations(int kmax, bool contacts, int ccap, hipStream_t st, const FlatWave* waves, const int* n_waves,
+                         int wave_grid, double* hn, double* hd) {
+    const long long nw = waves ? wave_grid : ((long long)cap.n * (contacts ? CL : 1) + 63) / 64;
+    if (nw <= EARLY_WAVES)
+      launch_iterations_as<CL, true>(kmax, contacts, ccap, st, waves, n_waves, wave_grid, hn, hd);
+    else
+      launch_iterations_as<CL, false>(kmax, contacts, ccap, st, waves, n_waves, wave_grid, hn, hd);
   }
 
   // One step of Algorithm 1 with flat per-body kernels (one launch per iteration).
@@ -577,8 +594,10 @@ struct Engine {
   // resident_grid (optional): the scenes of the resident lists take their whole
   // step in the resident kernel, after the contact construction; with
   // flat = false no flat-path kernel is launched (every flat scene is resident).
-  void launch_flat_step(int n_scenes, int kmax, bool contacts, int n_driven, bool history,
-                        bool finish_scenes, hipStream_t st, const FlatWave* waves = nullptr,
+  //
+  // ccap: contact slots per body of a plain scene (a wave table holds its own)
+  void launch_flat_step(int n_scenes, int kmax, bool contacts, int ccap, int n_driven, bool history,
+                        bool finish_scenes, hipStream_t st, FlatWave* waves = nullptr,
                         const int* n_waves = nullptr, int wave_grid = 0,
                         const int* resident_grid = nullptr, bool flat = true) {
     View<T> v = view();
@@ -595,10 +614,10 @@ struct Engine {
     // with contacts, the contact construction's first kernel also predicts
     // (when its body range covers the flat path's)
     const bool predict_in_prep = contacts && flat && ncb >= cap.n;
-    if (contacts) launch_contacts(n_scenes, st, predict_in_prep);
+    if (contacts) launch_contacts(n_scenes, st, predict_in_prep, waves, n_waves);
     if (resident_grid) launch_resident(resident_grid, drive_inside ? n_driven : 0, st);
     if (!flat) return;
-    if (!predict_in_prep) hipLaunchKernelGGL(k_predict<T>, g, b, 0, st, v);
+    if (!predict_in_prep) hipLaunchKernelGGL(k_predict<T>, g, b, 0, st, v, waves, n_waves);
     double* hn = history ? rh_num : nullptr;
     double* hd = history ? rh_den : nullptr;
     if (history) {
@@ -608,11 +627,11 @@ struct Engine {
       hipLaunchKernelGGL(k_zero_double, gz, dim3(256), 0, st, rh_den, nh);
     }
     switch (contact_lanes) {
-      case 1: launch_iterations<1>(kmax, contacts, history, st, waves, n_waves, wave_grid, hn, hd); break;
-      case 2: launch_iterations<2>(kmax, contacts, history, st, waves, n_waves, wave_grid, hn, hd); break;
-      case 8: launch_iterations<8>(kmax, contacts, history, st, waves, n_waves, wave_grid, hn, hd); break;
-      case 16: launch_iterations<16>(kmax, contacts, history, st, waves, n_waves, wave_grid, hn, hd); break;
-      default: launch_iterations<4>(kmax, contacts, history, st, waves, n_waves, wave_grid, hn, hd); break;
+      case 1: launch_iterations<1>(kmax, contacts, ccap, st, waves, n_waves, wave_grid, hn, hd); break;
+      case 2: launch_iterations<2>(kmax, contacts, ccap, st, waves, n_waves, wave_grid, hn, hd); break;
+      case 8: launch_iterations<8>(kmax, contacts, ccap, st, waves, n_waves, wave_grid, hn, hd); break;
+      case 16: launch_iterations<16>(kmax, contacts, ccap, st, waves, n_waves, wave_grid, hn, hd); break;
+      default: launch_iterations<4>(kmax, contacts, ccap, st, waves, n_waves, wave_grid, hn, hd); break;
     }
     // (each body's step ends in its last iteration: velocities, health, q^{n+1})
     if (!finish_scenes) return;

@@ -103,7 +103,8 @@ __device__ __forceinline__ bool contact_body(const View<T>& v, int i, int sc) {
 }
 
 template <typename T>
-__global__ void k_contact_prep(View<T> v, ContactBuf cb, int n_scenes, int n_buckets, bool predict) {
+__global__ void k_contact_prep(View<T> v, ContactBuf cb, int n_scenes, int n_buckets, bool predict, FlatWave* waves,
+                               const int* n_waves) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n_buckets) {  // the spatial hash's counts, when this step builds it
     cb.bucket_count[i] = 0;
@@ -118,7 +119,10 @@ __global__ void k_contact_prep(View<T> v, ContactBuf cb, int n_scenes, int n_buc
   v.r_den[i] = 0.0;
   // the step's prediction, which the contact construction neither reads nor
   // changes (it reads q^n and the velocities)
-  if (predict) predict_body(v, i);
+  if (predict) {
+    predict_body(v, i);
+    arm_wave(v.scenes, waves, n_waves, i);
+  }
 }
 
 __device__ __forceinline__ int reach_bin(double r) {

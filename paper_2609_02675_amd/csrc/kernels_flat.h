@@ -140,45 +140,238 @@ __device__ __forceinline__ void residual_terms(const T* m, const T* qo, const T*
   *den = m_norm2(m, cc, q);
 }
 
-// sum over the LPB consecutive lanes of a body (xor butterfly: every lane gets
-// the same bits, since each partial sum is formed from the same two operands)
+// x of another lane of this lane's row of 16, by a data-parallel primitive of
+// the vector ALU (a shuffle would go through LDS)
+template <int CTRL>
+__device__ __forceinline__ int dpp_of(int x) {
+  return __builtin_amdgcn_update_dpp(x, x, CTRL, 0xf, 0xf, false);
+}
+template <int CTRL, typename U>
+__device__ __forceinline__ U lane_of(U x) {
+  if constexpr (sizeof(U) == 8) {
+    const long long b = __builtin_bit_cast(long long, x);
+    const unsigned lo = (unsigned)dpp_of<CTRL>((int)b), hi = (unsigned)dpp_of<CTRL>((int)(b >> 32));
+    return __builtin_bit_cast(U, (long long)(((unsigned long long)hi << 32) | lo));
+  } else {
+    return __builtin_bit_cast(U, dpp_of<CTRL>(__builtin_bit_cast(int, x)));
+  }
+}
+
+// sum over the LPB consecutive lanes of a body (2, 4, 8 or 16, aligned): pairs,
+// quads, then mirrored halves of eight and sixteen, whose lanes already agree
+// within each half, so a mirrored lane stands for any lane of the other half.
+// Every lane gets the same bits, since each partial sum is formed from the same
+// two operands.
 template <int LPB, typename U>
 __device__ __forceinline__ U lane_sum(U x) {
-#pragma unroll
-  for (int o = 1; o < LPB; o <<= 1) x += __shfl_xor(x, o);
+  if constexpr (LPB >= 2) x += lane_of<0xB1>(x);    // quad_perm 1 0 3 2
+  if constexpr (LPB >= 4) x += lane_of<0x4E>(x);    // quad_perm 2 3 0 1
+  if constexpr (LPB >= 8) x += lane_of<0x141>(x);   // row_half_mirror
+  if constexpr (LPB >= 16) x += lane_of<0x140>(x);  // row_mirror
   return x;
 }
 
-// One Jacobi iteration.  LPB consecutive lanes share a body: they split its
-// static bond ends and contact ends (lane l takes ends l, l + LPB, ...), sum the
-// force terms and the contact change of the FP64 block across the lanes, and the
-// first lane solves, projects and stores.
-//
-// q^k is read from qs and q^{k+1} written to qd, the record of body b at
-// (b - qoff) QR: the double-buffered global arrays with qoff = 0 for the flat
-// kernels, the scene's LDS buffers with qoff = its first body for the resident
-// step.  A body runs in the kernel family that its scene's `resident` flag
-// names, so the two never both advance it.
-// ENDS chooses the loop over the static ends: 0 per wave at run time (below), 1
-// the quadratic loop only (the caller knows the scene has no variable end), 2
-// the general loop only.
-template <typename T, bool CONTACT, int LPB, bool RESIDENT = false, int ENDS = 0>
-__device__ __forceinline__ void iterate_body(const View<T>& v, int k, double* rh_num, double* rh_den,
-                                             int i, int sub, const T* qs, T* qd, int qoff) {
+// The pieces of one Jacobi iteration of a body, shared by the flat kernels and
+// the resident step so that both round alike: its static ends (quadratic only,
+// or of any kind), a contact end, the sum across the lanes that share the body,
+// and the solve with the local step.
+
+// forces of the static ends e, e + LPB, ... below e1, quadratic ends only, two
+// ends per round with both ends' loads (record and partner state) in flight
+// together; each end's terms are added in end order
+template <typename T, int LPB>
+__device__ __forceinline__ void quadratic_ends(const View<T>& v, int e, int e1, const T* q, const T* qs, int qoff,
+                                               T* rb) {
+  constexpr int QR = Rec<T>::Q;
+  for (; e < e1; e += 2 * LPB) {
+    const int eb = e + LPB;
+    const bool hb = eb < e1;
+    const int ja = v.se_partner[e];
+    const int jb = hb ? v.se_partner[eb] : -1;
+    T Ea[EW], Eb[EW], qa[QR], qb[QR];
+    load<T, EW>(v.se + (size_t)EW * e, Ea);
+    if (hb) load<T, EW>(v.se + (size_t)EW * eb, Eb);
+    if (ja >= 0) load<T, QR>(qs + (size_t)QR * (ja - qoff), qa);
+    if (jb >= 0) load<T, QR>(qs + (size_t)QR * (jb - qoff), qb);
+    T d[3], f[3];
+    bond_vec<T>(q, Ea, ja < 0 ? (const T*)nullptr : qa, Ea + 4, d);
+    quad_end_force(Ea, d, f);
+    settle<3>(f);
+    add_JT(rb, Ea, f[0], f[1], f[2]);
+    if (hb) {
+      bond_vec<T>(q, Eb, jb < 0 ? (const T*)nullptr : qb, Eb + 4, d);
+      quad_end_force(Eb, d, f);
+      settle<3>(f);
+      add_JT(rb, Eb, f[0], f[1], f[2]);
+    }
+  }
+}
+
+// the same for ends of any kind (augmented, polynomial and slider ends among
+// others; var: the body owns some), one end at a time: every end's terms are
+// formed with the same operations in the same order as above.  Ends whose
+// weight or point moves add to dB, the change of the block, and set refactor;
+// `last`: the step's last iteration.
+template <typename T, int LPB>
+__device__ __forceinline__ void general_ends(const View<T>& v, const SceneDev& S, int e, int e1, bool var, bool last,
+                                             const T* q, const T* qs, int qoff, T* rb, Block& dB, bool& refactor) {
+  constexpr int QR = Rec<T>::Q;
+  for (; e < e1; e += LPB) {
+    const int j = v.se_partner[e];
+    T E[EW];
+    load<T, EW>(v.se + (size_t)EW * e, E);
+    T* a = var ? v.al + 4 * (size_t)e : nullptr;
+    const T kind = a ? a[3] : (T)0;
+    // a slider end's line anchor sits t0 = E[7] along the axis from the given
+    // one (a slider's rest length is 0, so E[7] holds no phi^-): the same line,
+    // re-anchored near the point every step so that the bond vector, whose
+    // across-axis part is the force, stays short (in FP32 a long one would lose
+    // that part to rounding)
+    T xs[3] = {E[0], E[1], E[2]}, xo[3] = {E[4], E[5], E[6]};
+    if (kind == (T)AL_SLIDER_POINT) {
+#pragma unroll
+      for (int r = 0; r < 3; ++r) xo[r] = fma(E[7], a[r], xo[r]);
+    } else if (kind == (T)AL_SLIDER_LINE) {
+#pragma unroll
+      for (int r = 0; r < 3; ++r) xs[r] = fma(E[7], a[r], xs[r]);
+    }
+    T d[3], f[3];
+    T qj[QR];
+    if (j < 0) {
+      bond_vec<T>(q, xs, nullptr, xo, d);
+    } else {
+      load<T, QR>(qs + (size_t)QR * (j - qoff), qj);
+      bond_vec<T>(q, xs, qj, xo, d);
+    }
+    if (kind == (T)AL_SLIDER_POINT) {
+      // fixed weight at the own point (in the static block), drawn to the foot
+      T dp[3];
+      const T t = slider_end(d, j < 0 ? (const T*)nullptr : qj + 3, a, dp);
+      end_force(E[3], (T)0, dp, f);
+      add_JT(rb, E, f[0], f[1], f[2]);
+      if (last) v.se[(size_t)EW * e + 7] = E[7] - t;  // the foot is -t from the anchor
+    } else if (kind == (T)AL_SLIDER_LINE) {
+      // the own point is the foot xf = x_s + t u, so its weight moves every iteration
+      T dp[3];
+      const T t = slider_end(d, q + 3, a, dp);
+      const T xf[3] = {fma(t, a[0], xs[0]), fma(t, a[1], xs[1]), fma(t, a[2], xs[2])};
+      end_force(E[3], (T)0, dp, f);
+      add_JT(rb, xf, f[0], f[1], f[2]);
+      block_add_end(dB, (double)E[3], (double)xf[0], (double)xf[1], (double)xf[2]);
+      refactor = true;
+      if (last) v.se[(size_t)EW * e + 7] = E[7] + t;
+    } else if (kind != (T)0) {
+      const T w = kind > (T)0 ? augmented_end(a, d, (T)(S.h * S.h), (T)S.al_beta, f)
+                              : polynomial_end(a, d, (T)(S.h * S.h), f);
+      block_add_end(dB, (double)w, (double)E[0], (double)E[1], (double)E[2]);
+      refactor = true;
+      add_JT(rb, E, f[0], f[1], f[2]);
+    } else {
+      quad_end_force(E, d, f);
+      settle<3>(f);
+      add_JT(rb, E, f[0], f[1], f[2]);
+    }
+  }
+}
+
+// one contact end: record C, partner j (-1: a plane) at qj
+template <typename T>
+__device__ __forceinline__ void contact_end(const T* C, int j, const T* q, const T* qj, T mu, T* rb, Block& dB,
+                                            bool& refactor) {
+  T d[3], f[3], n[3], kap;
+  bond_vec<T>(q, C, j < 0 ? nullptr : qj, C + 4, d);
+  if constexpr (sizeof(T) == 4) {
+    // h^2 kappa from the two q records, the normal from its octahedral form
+    kap = fmax(q[Q_KAPPA], j < 0 ? (T)0 : qj[Q_KAPPA]);
+    oct_decode(C[3], C[7], n);
+  } else {
+    kap = C[3];
+    n[0] = C[8];
+    n[1] = C[9];
+    n[2] = C[10];
+  }
+  if (!contact_end_force(kap, mu, n, d, f)) return;
+  add_JT(rb, C, f[0], f[1], f[2]);
+  block_add_end(dB, (double)kap, (double)C[0], (double)C[1], (double)C[2]);
+  refactor = true;
+}
+
+// the force terms and the block change summed over the lanes of a body
+template <typename T, int LPB>
+__device__ __forceinline__ void sum_lanes(T* rb, Block& dB, bool& refactor) {
+  if constexpr (LPB > 1) {
+#pragma unroll
+    for (int c = 0; c < QW; ++c) rb[c] = lane_sum<LPB>(rb[c]);
+    refactor = lane_sum<LPB>(refactor ? 1 : 0) > 0;
+    if (refactor) {  // uniform across the body's lanes
+      dB.a = lane_sum<LPB>(dB.a);
+      dB.b0 = lane_sum<LPB>(dB.b0);
+      dB.b1 = lane_sum<LPB>(dB.b1);
+      dB.b2 = lane_sum<LPB>(dB.b2);
+      dB.d00 = lane_sum<LPB>(dB.d00);
+      dB.d01 = lane_sum<LPB>(dB.d01);
+      dB.d02 = lane_sum<LPB>(dB.d02);
+      dB.d11 = lane_sum<LPB>(dB.d11);
+      dB.d12 = lane_sum<LPB>(dB.d12);
+      dB.d22 = lane_sum<LPB>(dB.d22);
+    }
+  }
+}
+
+// the factor of H^k = H + dB from the static block bb (10 doubles)
+template <typename T>
+__device__ __forceinline__ void refactored(const double* bb, const Block& dB, T* fac) {
+  const Block B{bb[0] + dB.a,   bb[1] + dB.b0,  bb[2] + dB.b1,  bb[3] + dB.b2,  bb[4] + dB.d00,
+                bb[5] + dB.d01, bb[6] + dB.d02, bb[7] + dB.d11, bb[8] + dB.d12, bb[9] + dB.d22};
+  double f64[10];
+  block_inverse(B, f64);
+#pragma unroll
+  for (int c = 0; c < 10; ++c) fac[c] = (T)f64[c];
+}
+
+// global and local step of one body: qo = q^{k+1} from q = q^k, its summed force
+// terms rb (scaled by h^2), s, masses and factor
+template <typename T>
+__device__ __forceinline__ void solve_body(const T* fac, const T* s, const T* m, const T* rb, const T* q,
+                                           bool skip_local, unsigned* polar, int i, T* qo) {
+  constexpr int QR = Rec<T>::Q;
+  T r[QW];  // M (s - q^k) + h^2 sum (...)
+#pragma unroll
+  for (int c = 0; c < QW; ++c) r[c] = rb[c];
+  settle<QW>(r);
+  add_inertia(r, m, s, q);
+  T dq[QW];
+  block_apply(fac, r, dq);
+#pragma unroll
+  for (int c = 0; c < QR; ++c) qo[c] = q[c];
+  pos_add_lo(qo, dq[0], dq[1], dq[2]);
+  T Ah[9];
+#pragma unroll
+  for (int c = 0; c < 9; ++c) Ah[c] = q[3 + c] + dq[3 + c];
+  if (skip_local) {
+#pragma unroll
+    for (int c = 0; c < 9; ++c) qo[3 + c] = Ah[c];
+  } else {
+    polar_rotation(Ah, qo + 3, polar, i);
+  }
+}
+
+// One Jacobi iteration of body i in the resident step.  LPB consecutive lanes
+// share a body: they split its static bond ends and contact ends (lane l takes
+// ends l, l + LPB, ...), sum the force terms and the contact change of the FP64
+// block across the lanes, and the first lane solves, projects and stores.  q^k
+// is read from qs and q^{k+1} written to qd, the record of body b at
+// (b - qoff) QR of the scene's LDS buffers.  ENDS chooses the loop over the
+// static ends: 1 the quadratic loop (the caller knows the scene has no variable
+// end), 2 the general one.
+template <typename T, bool CONTACT, int LPB, int ENDS>
+__device__ __forceinline__ void iterate_resident(const View<T>& v, int k, int i, int sub, const T* qs, T* qd,
+                                                 int qoff) {
   constexpr int QR = Rec<T>::Q;
   const int sc = v.bscene[i];
   if (sc < 0) return;
-  if (v.flags[i] & F_PINNED) {
-    // a pinned body's residual shares stay zero (it never moves); written in
-    // the first iteration, before the step's residual reduction reads them
-    if (!RESIDENT && k == 0 && sub == 0) {
-      v.r_num[i] = 0.0;
-      v.r_den[i] = 0.0;
-    }
-    return;
-  }
+  if (v.flags[i] & F_PINNED) return;
   const SceneDev& S = v.scenes[sc];
-  if ((S.resident != 0) != RESIDENT) return;
   const int K = S.iters;
   if (k >= K || S.step >= S.steps_total) return;
   T q[QR];
@@ -186,226 +379,190 @@ __device__ __forceinline__ void iterate_body(const View<T>& v, int k, double* rh
   T rb[QW];
 #pragma unroll
   for (int c = 0; c < QW; ++c) rb[c] = (T)0;
-  T fac[FW];
   bool refactor = false;
   Block dB{};  // contact and augmented part of H^k - H (this lane's ends)
-  const bool var = (v.flags[i] & F_VARIABLE) != 0;
-  const int e1 = v.srow_end[i];
-  // a wave with a body that has variable ends takes the general loop, any
-  // other wave the quadratic loop below (a divergent wave would run both loops
-  // one after the other).  Both form every end's terms with the same
-  // operations in the same order, so the choice does not change the bits.
-  bool general;
   if constexpr (ENDS == 1)
-    general = false;
-  else if constexpr (ENDS == 2)
-    general = true;
+    quadratic_ends<T, LPB>(v, v.srow[i] + sub, v.srow_end[i], q, qs, qoff, rb);
   else
-    general = wave_any(var);
-  if (general) {
-    // the general loop (augmented, polynomial and slider ends among others),
-    // one end at a time
-    for (int e = v.srow[i] + sub; e < e1; e += LPB) {
-      const int j = v.se_partner[e];
-      T E[EW];
-      load<T, EW>(v.se + (size_t)EW * e, E);
-      T* a = var ? v.al + 4 * (size_t)e : nullptr;
-      const T kind = a ? a[3] : (T)0;
-      // a slider end's line anchor sits t0 = E[7] along the axis from the given
-      // one (a slider's rest length is 0, so E[7] holds no phi^-): the same line,
-      // re-anchored near the point every step so that the bond vector, whose
-      // across-axis part is the force, stays short (in FP32 a long one would lose
-      // that part to rounding)
-      T xs[3] = {E[0], E[1], E[2]}, xo[3] = {E[4], E[5], E[6]};
-      if (kind == (T)AL_SLIDER_POINT) {
-#pragma unroll
-        for (int r = 0; r < 3; ++r) xo[r] = fma(E[7], a[r], xo[r]);
-      } else if (kind == (T)AL_SLIDER_LINE) {
-#pragma unroll
-        for (int r = 0; r < 3; ++r) xs[r] = fma(E[7], a[r], xs[r]);
-      }
-      T d[3], f[3];
-      T qj[QR];
-      if (j < 0) {
-        bond_vec<T>(q, xs, nullptr, xo, d);
-      } else {
-        load<T, QR>(qs + (size_t)QR * (j - qoff), qj);
-        bond_vec<T>(q, xs, qj, xo, d);
-      }
-      if (kind == (T)AL_SLIDER_POINT) {
-        // fixed weight at the own point (in the static block), drawn to the foot
-        T dp[3];
-        const T t = slider_end(d, j < 0 ? (const T*)nullptr : qj + 3, a, dp);
-        end_force(E[3], (T)0, dp, f);
-        add_JT(rb, E, f[0], f[1], f[2]);
-        if (k == K - 1) v.se[(size_t)EW * e + 7] = E[7] - t;  // the foot is -t from the anchor
-      } else if (kind == (T)AL_SLIDER_LINE) {
-        // the own point is the foot xf = x_s + t u, so its weight moves every iteration
-        T dp[3];
-        const T t = slider_end(d, q + 3, a, dp);
-        const T xf[3] = {fma(t, a[0], xs[0]), fma(t, a[1], xs[1]), fma(t, a[2], xs[2])};
-        end_force(E[3], (T)0, dp, f);
-        add_JT(rb, xf, f[0], f[1], f[2]);
-        block_add_end(dB, (double)E[3], (double)xf[0], (double)xf[1], (double)xf[2]);
-        refactor = true;
-        if (k == K - 1) v.se[(size_t)EW * e + 7] = E[7] + t;
-      } else if (kind != (T)0) {
-        const T w = kind > (T)0 ? augmented_end(a, d, (T)(S.h * S.h), (T)S.al_beta, f)
-                                : polynomial_end(a, d, (T)(S.h * S.h), f);
-        block_add_end(dB, (double)w, (double)E[0], (double)E[1], (double)E[2]);
-        refactor = true;
-        add_JT(rb, E, f[0], f[1], f[2]);
-      } else {
-        quad_end_force(E, d, f);
-        add_JT(rb, E, f[0], f[1], f[2]);
-      }
-    }
-  } else {
-    // quadratic ends only: the lanes of a body take its ends in turn, two ends
-    // per round with both ends' loads (record and partner state) in flight
-    // together; each end's terms are still added in end order
-    for (int e = v.srow[i] + sub; e < e1; e += 2 * LPB) {
-      const int eb = e + LPB;
-      const bool hb = eb < e1;
-      const int ja = v.se_partner[e];
-      const int jb = hb ? v.se_partner[eb] : -1;
-      T Ea[EW], Eb[EW], qa[QR], qb[QR];
-      load<T, EW>(v.se + (size_t)EW * e, Ea);
-      if (hb) load<T, EW>(v.se + (size_t)EW * eb, Eb);
-      if (ja >= 0) load<T, QR>(qs + (size_t)QR * (ja - qoff), qa);
-      if (jb >= 0) load<T, QR>(qs + (size_t)QR * (jb - qoff), qb);
-      T d[3], f[3];
-      bond_vec<T>(q, Ea, ja < 0 ? (const T*)nullptr : qa, Ea + 4, d);
-      quad_end_force(Ea, d, f);
-      add_JT(rb, Ea, f[0], f[1], f[2]);
-      if (hb) {
-        bond_vec<T>(q, Eb, jb < 0 ? (const T*)nullptr : qb, Eb + 4, d);
-        quad_end_force(Eb, d, f);
-        add_JT(rb, Eb, f[0], f[1], f[2]);
-      }
-    }
-  }
+    general_ends<T, LPB>(v, S, v.srow[i] + sub, v.srow_end[i], (v.flags[i] & F_VARIABLE) != 0, k == K - 1, q, qs,
+                         qoff, rb, dB, refactor);
   if constexpr (CONTACT) {
     int cnt = v.ccount[i];
     if (cnt > S.ccap) cnt = S.ccap;
     const size_t base = ce_base(S, i);
     // the lanes of a body take its ends in turn (neighbouring lanes read
-    // neighbouring records), two ends per round with both ends' loads (record
-    // and partner state) in flight together
+    // neighbouring records), two ends per round
     constexpr int W = ContactRec<T>::W;
     const T mu = (T)S.mu;
-    auto contact_end = [&](const T* C, int j, const T* qj) {
-      T d[3], f[3], n[3], kap;
-      bond_vec<T>(q, C, j < 0 ? nullptr : qj, C + 4, d);
-      if constexpr (sizeof(T) == 4) {
-        // h^2 kappa from the two q records, the normal from its octahedral form
-        kap = fmax(q[Q_KAPPA], j < 0 ? (T)0 : qj[Q_KAPPA]);
-        oct_decode(C[3], C[7], n);
-      } else {
-        kap = C[3];
-        n[0] = C[8];
-        n[1] = C[9];
-        n[2] = C[10];
-      }
-      if (!contact_end_force(kap, mu, n, d, f)) return;
-      add_JT(rb, C, f[0], f[1], f[2]);
-      block_add_end(dB, (double)kap, (double)C[0], (double)C[1], (double)C[2]);
-      refactor = true;
-    };
-    // In the flat kernels the next round's partner ids are loaded during this
-    // round, so that a round's records and partner states all go out at once
-    // instead of the states waiting for the ids.  The resident kernel, whose
-    // partner states come from LDS, loads each round's ids at its start (it has
-    // no registers to spare for the ids ahead).
-    int ja = -1, jb = -1;
-    if constexpr (!RESIDENT) {
-      if (sub < cnt) {
-        ja = v.ce_partner[base + sub];
-        jb = sub + LPB < cnt ? v.ce_partner[base + sub + LPB] : -1;
-      }
-    }
     for (int c = sub; c < cnt; c += 2 * LPB) {
       const int cb = c + LPB;
       const bool hb = cb < cnt;
-      if constexpr (RESIDENT) {
-        ja = v.ce_partner[base + c];
-        jb = hb ? v.ce_partner[base + cb] : -1;
-      }
+      const int ja = v.ce_partner[base + c];
+      const int jb = hb ? v.ce_partner[base + cb] : -1;
       T Ca[W], Cb[W], qa[QR], qb[QR];
       load<T, W>(v.ce + (size_t)W * (base + c), Ca);
       if (hb) load<T, W>(v.ce + (size_t)W * (base + cb), Cb);
       if (ja >= 0) load<T, QR>(qs + (size_t)QR * (ja - qoff), qa);
       if (jb >= 0) load<T, QR>(qs + (size_t)QR * (jb - qoff), qb);
-      int jan = -1, jbn = -1;
-      if constexpr (!RESIDENT) {
-        const int cn = c + 2 * LPB;
-        jan = cn < cnt ? v.ce_partner[base + cn] : -1;
-        jbn = cn + LPB < cnt ? v.ce_partner[base + cn + LPB] : -1;
-      }
-      contact_end(Ca, ja, qa);
-      if (hb) contact_end(Cb, jb, qb);
-      if constexpr (!RESIDENT) {
-        ja = jan;
-        jb = jbn;
-      }
+      contact_end(Ca, ja, q, qa, mu, rb, dB, refactor);
+      if (hb) contact_end(Cb, jb, q, qb, mu, rb, dB, refactor);
     }
   }
-  if constexpr (LPB > 1) {
-#pragma unroll
-    for (int c = 0; c < QW; ++c) rb[c] = lane_sum<LPB>(rb[c]);
-    {
-      refactor = lane_sum<LPB>(refactor ? 1 : 0) > 0;
-      if (refactor) {  // uniform across the body's lanes
-        dB.a = lane_sum<LPB>(dB.a);
-        dB.b0 = lane_sum<LPB>(dB.b0);
-        dB.b1 = lane_sum<LPB>(dB.b1);
-        dB.b2 = lane_sum<LPB>(dB.b2);
-        dB.d00 = lane_sum<LPB>(dB.d00);
-        dB.d01 = lane_sum<LPB>(dB.d01);
-        dB.d02 = lane_sum<LPB>(dB.d02);
-        dB.d11 = lane_sum<LPB>(dB.d11);
-        dB.d12 = lane_sum<LPB>(dB.d12);
-        dB.d22 = lane_sum<LPB>(dB.d22);
-      }
-    }
-    if (sub != 0) return;
-  }
-  if (refactor) {  // H^k changed: a contact penetrates, or a variable end's weight or point moved
-    const double* bb = v.blk + 10 * (size_t)i;
-    const Block B{bb[0] + dB.a,   bb[1] + dB.b0,  bb[2] + dB.b1,  bb[3] + dB.b2,  bb[4] + dB.d00,
-                  bb[5] + dB.d01, bb[6] + dB.d02, bb[7] + dB.d11, bb[8] + dB.d12, bb[9] + dB.d22};
-    double f64[10];
-    block_inverse(B, f64);
-#pragma unroll
-    for (int c = 0; c < 10; ++c) fac[c] = (T)f64[c];
-  } else {
+  sum_lanes<T, LPB>(rb, dB, refactor);
+  if (sub != 0) return;
+  T fac[FW];
+  if (refactor)  // H^k changed: a contact penetrates, or a variable end's weight or point moved
+    refactored(v.blk + 10 * (size_t)i, dB, fac);
+  else
     load<T, FW>(v.fac + (size_t)FW * i, fac);
-  }
-  T s[QR], m[MW];
+  T s[QR], m[MW], qo[QR];
   load<T, QR>(v.s + (size_t)QR * i, s);
   load<T, MW>(v.mass + (size_t)MW * i, m);
-  T r[QW];  // M (s - q^k) + h^2 sum (...): the forces are already scaled by h^2
-#pragma unroll
-  for (int c = 0; c < QW; ++c) r[c] = rb[c];
-  add_inertia(r, m, s, q);
-  T dq[QW];
-  block_apply(fac, r, dq);
-  T qo[QR];
-#pragma unroll
-  for (int c = 0; c < QR; ++c) qo[c] = q[c];
-  pos_add_lo(qo, dq[0], dq[1], dq[2]);
-  T Ah[9];
-#pragma unroll
-  for (int c = 0; c < 9; ++c) Ah[c] = q[3 + c] + dq[3 + c];
-  if (S.debug & 1) {
-#pragma unroll
-    for (int c = 0; c < 9; ++c) qo[3 + c] = Ah[c];
-  } else {
-    polar_rotation(Ah, qo + 3, v.polar, i);
+  solve_body(fac, s, m, rb, q, (S.debug & 1) != 0, v.polar, i, qo);
+  store<T, QR>(qd + (size_t)QR * (i - qoff), qo);
+  if (k == K - 1) {
+    double num, den;
+    residual_terms(m, qo, q, &num, &den);
+    v.r_num[i] = num;
+    v.r_den[i] = den;
   }
-  // q^{k+1} for the partners' next iteration; after the flat path's last
-  // iteration nothing reads it (the body's step ends below)
-  if (RESIDENT || k < K - 1) store<T, QR>(qd + (size_t)QR * (i - qoff), qo);
+}
+
+// One Jacobi iteration of the flat path for body i (Algorithm 1's global and
+// local step; reads q^k of every body, writes q^{k+1} to the other buffer), LPB
+// lanes per body.  A launch covers one iteration, and a kernel boundary leaves
+// nothing in the caches nearest the compute units, so what a small scene waits
+// for is the chain of loads that need one another's results.  The chain has two
+// links: everything whose address follows from the body's index (its state,
+// count of contact ends, factor, block, masses, the partner ids and records of
+// its first ends -- slots beyond the count hold no end, but lie in the body's
+// own range), then the partners' states.  `base` is the body's first contact
+// slot.
+//
+// EARLY also loads what only the solve needs at the start, and the first U ends
+// of every lane before the count is known: for launches with so few waves that
+// latency decides.  Otherwise the solve's operands are loaded before the sum
+// across the lanes and records only for ends that exist, in fewer registers, so
+// that more waves hide one another's waits.
+//
+// Measured (FP32, per step): a 1,000-box pile 0.251 -> 0.209 ms against the chain
+// of six links it had (scene id, scene, ranges, partner ids, records and states,
+// solve operands), a chain of 2,000 bodies 0.119 -> 0.103; the 125,000-block
+// pile, bound by the bytes of its records (4.5 TB/s), unchanged at 64 us an
+// iteration.
+template <typename T, bool CONTACT, int LPB, int U, bool EARLY>
+__device__ __forceinline__ void iterate_flat(const View<T>& v, const SceneDev& S, int k, int K, double* rh_num,
+                                             double* rh_den, int i, int sub, size_t base, int ccap, int sc) {
+  constexpr int QR = Rec<T>::Q, W = ContactRec<T>::W;
+  const T* qs = v.q[k & 1];
+  T* qd = v.q[(k + 1) & 1];
+  T q[QR], s[QR], m[MW], fac[FW];
+  double bb[10];
+  const uint8_t flags = v.flags[i];
+  const int e0 = v.srow[i], e1 = v.srow_end[i];
+  load<T, QR>(qs + (size_t)QR * i, q);
+  int cnt = 0;
+  int id[U];
+  T C[U][W];
+  if constexpr (CONTACT) {
+    cnt = v.ccount[i];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int c = sub + u * LPB;
+      const size_t slot = base + (c < ccap ? c : 0);
+      id[u] = v.ce_partner[slot];
+      if constexpr (EARLY) load<T, W>(v.ce + (size_t)W * slot, C[u]);
+    }
+  }
+  auto solve_operands = [&]() {
+    load<T, QR>(v.s + (size_t)QR * i, s);
+    load<T, MW>(v.mass + (size_t)MW * i, m);
+    load<T, FW>(v.fac + (size_t)FW * i, fac);
+    if constexpr (CONTACT) {
+#pragma unroll
+      for (int c = 0; c < 5; ++c) {
+        const double2 b2 = reinterpret_cast<const double2*>(v.blk + 10 * (size_t)i)[c];
+        bb[2 * c] = b2.x;
+        bb[2 * c + 1] = b2.y;
+      }
+    }
+  };
+  if constexpr (EARLY) solve_operands();
+  const bool pinned = (flags & F_PINNED) != 0;
+  T rb[QW];
+#pragma unroll
+  for (int c = 0; c < QW; ++c) rb[c] = (T)0;
+  bool refactor = false;
+  Block dB{};  // contact and augmented part of H^k - H (this lane's ends)
+  const bool var = (flags & F_VARIABLE) != 0;
+  const int eb = e0 + sub, ee = pinned ? eb : e1;
+  // a wave with a body that has variable ends takes the general loop, any
+  // other wave the quadratic loop (a divergent wave would run both loops one
+  // after the other)
+  if (wave_any(var && !pinned))
+    general_ends<T, LPB>(v, S, eb, ee, var, k == K - 1, q, qs, 0, rb, dB, refactor);
+  else
+    quadratic_ends<T, LPB>(v, eb, ee, q, qs, 0, rb);
+  if constexpr (CONTACT) {
+    const T mu = (T)S.mu;
+    cnt = pinned ? 0 : (cnt < ccap ? cnt : ccap);
+    // U ends per lane and round (neighbouring lanes take neighbouring records):
+    // a round's partner states go out at once
+    for (int c0 = sub; c0 < cnt; c0 += U * LPB) {
+      if (c0 != sub) {
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (EARLY && c0 + u * LPB < cnt) id[u] = v.ce_partner[base + c0 + u * LPB];
+      }
+      T qj[U][QR];
+      int idn[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int c = c0 + u * LPB;
+        if (c < cnt) {
+          if (!EARLY || c0 != sub) load<T, W>(v.ce + (size_t)W * (base + c), C[u]);
+          if (id[u] >= 0) load<T, QR>(qs + (size_t)QR * id[u], qj[u]);
+        }
+        if constexpr (!EARLY) {
+          // the next round's partner ids during this one
+          const int cn = c + U * LPB;
+          idn[u] = cn < cnt ? v.ce_partner[base + cn] : -1;
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (c0 + u * LPB < cnt) contact_end(C[u], id[u], q, qj[u], mu, rb, dB, refactor);
+      if constexpr (!EARLY) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) id[u] = idn[u];
+      }
+    }
+  }
+  if constexpr (!EARLY) solve_operands();
+  sum_lanes<T, LPB>(rb, dB, refactor);
+  // H^k changed: a contact penetrates, or a variable end's weight or point moved
+  if (refactor) {
+    if constexpr (!CONTACT) {
+#pragma unroll
+      for (int c = 0; c < 10; ++c) bb[c] = v.blk[10 * (size_t)i + c];
+    }
+    refactored(bb, dB, fac);
+  }
+  if (pinned) {
+    // a pinned body's residual shares stay zero (it never moves); written in
+    // the first iteration, before the step's residual reduction reads them
+    if (k == 0 && sub == 0) {
+      v.r_num[i] = 0.0;
+      v.r_den[i] = 0.0;
+    }
+    return;
+  }
+  if (sub != 0) return;
+  T qo[QR];
+  solve_body(fac, s, m, rb, q, (S.debug & 1) != 0, v.polar, i, qo);
+  // q^{k+1} for the partners' next iteration; after the last iteration nothing
+  // reads it (the body's step ends below)
+  if (k < K - 1) store<T, QR>(qd + (size_t)QR * i, qo);
   if (k == K - 1 || rh_num) {
     double num, den;
     residual_terms(m, qo, q, &num, &den);
@@ -418,65 +575,76 @@ __device__ __forceinline__ void iterate_body(const View<T>& v, int k, double* rh
       rh_den[(size_t)k * v.n + i] = den;
     }
   }
-  if constexpr (!RESIDENT) {
-    if (k == K - 1) {
-      // the end of the body's step on the flat path: velocity recovery (Sec. 4.4)
-      // from q^K and q^n, the health bit, and q^{n+1} = q^K with its position
-      // folded back to (hi, lo) (the resident kernel ends its scenes' steps itself)
-      T q0[QR], vw[VW];
-      load<T, QR>(v.qn + (size_t)QR * i, q0);
-      // q^K as a value of its own, as if read back from memory: the recovery's
-      // subtractions must not fuse with the local step's last products, so
-      // that the flat path rounds as the resident kernel does
+  if (k == K - 1) {
+    // the end of the body's step: velocity recovery (Sec. 4.4) from q^K and
+    // q^n, the health bit, and q^{n+1} = q^K with its position folded back to
+    // (hi, lo) (the resident kernel ends its scenes' steps itself)
+    T q0[QR], vw[VW];
+    load<T, QR>(v.qn + (size_t)QR * i, q0);
+    // q^K as if read back from memory: the recovery's subtractions must not
+    // fuse with the local step's last products, so that the flat path rounds
+    // as the resident kernel does
+    settle<QR>(qo);
+    recover_velocity(qo, q0, (T)(1.0 / S.h), vw);
+    bool finite = true;
 #pragma unroll
-      for (int c = 0; c < QR; ++c) asm volatile("" : "+v"(qo[c]));
-      recover_velocity(qo, q0, (T)(1.0 / S.h), vw);
-      bool finite = true;
+    for (int c = 0; c < QR; ++c) finite = finite && isfinite(qo[c]);
 #pragma unroll
-      for (int c = 0; c < QR; ++c) finite = finite && isfinite(qo[c]);
-#pragma unroll
-      for (int c = 0; c < 6; ++c) finite = finite && isfinite(vw[c]);
-      if (!finite) atomicOr(v.health + sc, 1);
-      pos_renorm(qo);
-      store<T, QR>(v.qn + (size_t)QR * i, qo);
-      store<T, VW>(v.vel + (size_t)VW * i, vw);
-    }
+    for (int c = 0; c < 6; ++c) finite = finite && isfinite(vw[c]);
+    if (!finite) atomicOr(v.health + sc, 1);
+    pos_renorm(qo);
+    store<T, QR>(v.qn + (size_t)QR * i, qo);
+    store<T, VW>(v.vel + (size_t)VW * i, vw);
   }
 }
 
-// occupancy: at least four waves per SIMD in FP32 (at most 128 registers), two
-// in FP64; the iteration waits on loads of its partners and contact records,
-// so resident waves matter more than the few registers of its rare paths
-template <typename T, bool CONTACT, int LPB>
-__global__ void __launch_bounds__(256, sizeof(T) == 4 ? 4 : 2) k_iterate(View<T> v, int k, double* rh_num, double* rh_den) {
-  const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  const int i = (int)(t / LPB), sub = (int)(t % LPB);
-  if (i >= v.n) return;
-  iterate_body<T, CONTACT, LPB>(v, k, rh_num, rh_den, i, sub, v.q[k & 1], v.q[(k + 1) & 1], 0);
-}
-
-// The same iteration over a table of wavefronts (first body, bodies, lanes per
-// body): a wave covers 64 / CL bodies of a contact scene with CL lanes each (16
-// with the default four), or 64 bodies of a contact-free scene with one lane
-// each, and never spans two scenes.  Waves past the table's count leave at
-// once, so the grid can stay fixed while scenes come and go.
-struct FlatWave {
-  int first, count, lpb, contact;  // lpb: lanes per body (CL for a contact wave, else 1)
+// Registers: the latency variant may take as many as one wave per SIMD leaves;
+// the other at most what four waves per SIMD leave in FP32 (128), two in FP64.
+template <typename T, bool EARLY>
+struct FlatBounds {
+  static constexpr int WAVES = EARLY ? 1 : (sizeof(T) == 4 ? 4 : 2);
+};
+// ends per lane and round: the latency variant sixteen per body and round (at
+// most four per lane), the other two per lane
+template <int LPB, bool EARLY>
+struct FlatRound {
+  static constexpr int U = EARLY ? (LPB >= 8 ? 2 : 4) : 2;
 };
 
-template <typename T, int CL>
-__global__ void __launch_bounds__(256, sizeof(T) == 4 ? 4 : 2) k_iterate_waves(View<T> v, int k, const FlatWave* waves,
-                                                       const int* n_waves) {
-  const int w = (int)((blockIdx.x * (long long)blockDim.x + threadIdx.x) / 64);
+// the single scene of a plain handle, n bodies, ccap contact slots per body
+template <typename T, bool CONTACT, int LPB, bool EARLY>
+__global__ void __launch_bounds__(256, (FlatBounds<T, EARLY>::WAVES)) k_iterate(View<T> v, int k, int K, int ccap,
+                                                                            double* rh_num, double* rh_den) {
+  const int t = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+  const int i = t / LPB, sub = t % LPB;
+  if (i >= v.n) return;
+  iterate_flat<T, CONTACT, LPB, FlatRound<LPB, EARLY>::U, EARLY>(v, v.scenes[0], k, K, rh_num, rh_den, i, sub,
+                                                               (size_t)i * ccap, ccap, 0);
+}
+
+// The same iteration over a batch's table of wavefronts: a wave covers 64 / CL
+// bodies of a contact scene with CL lanes each (16 with the default four), or
+// 64 bodies of a contact-free scene with one lane each, and never spans two
+// scenes.  Waves past the table's count leave at once, so the grid can stay
+// fixed while scenes come and go.
+template <typename T, int CL, bool EARLY>
+__global__ void __launch_bounds__(256, (FlatBounds<T, EARLY>::WAVES)) k_iterate_waves(View<T> v, int k,
+                                                                                  const FlatWave* waves,
+                                                                                  const int* n_waves) {
+  const int w = (int)(blockIdx.x * (blockDim.x / 64) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x / 64)));
   const int l = (int)(threadIdx.x & 63);
   if (w >= *n_waves) return;
   const FlatWave fw = waves[w];
+  if (k >= fw.iters) return;
+  const SceneDev& S = v.scenes[fw.scene];
   if (fw.contact) {
-    if (l / CL >= fw.count) return;
-    iterate_body<T, true, CL>(v, k, nullptr, nullptr, fw.first + l / CL, l % CL, v.q[k & 1], v.q[(k + 1) & 1], 0);
+    const int b = l / CL;
+    if (b >= fw.count) return;
+    iterate_flat<T, true, CL, FlatRound<CL, EARLY>::U, EARLY>(v, S, k, fw.iters, nullptr, nullptr, fw.first + b, l % CL,
+                                                            (size_t)fw.ce0 + (size_t)b * fw.ccap, fw.ccap, fw.scene);
   } else {
     if (l >= fw.count) return;
-    iterate_body<T, false, 1>(v, k, nullptr, nullptr, fw.first + l, 0, v.q[k & 1], v.q[(k + 1) & 1], 0);
+    iterate_flat<T, false, 1, 1, EARLY>(v, S, k, fw.iters, nullptr, nullptr, fw.first + l, 0, 0, 0, fw.scene);
   }
 }
 

@@ -5,7 +5,7 @@
 // exchange q^k through two LDS buffers behind one barrier per iteration, so an
 // iteration waits on no global load of a partner's state and a step is one
 // launch after its contact construction instead of one launch per iteration.
-// Each body's iteration is the flat path's own code (iterate_body) with LDS as
+// Each body's iteration is the flat path's own code (the pieces in kernels_flat.h) with LDS as
 // the source of q^k: a scene gives the same bits here whichever other scenes
 // share its batch, and its residual and step counter are kept here.
 #pragma once
@@ -46,7 +46,7 @@ struct DrivenTable {
 // the contact scenes.  LPB lanes per body as in the flat iteration: four for
 // contact scenes (their ends split among them), one otherwise; a scene larger
 // than NT / LPB bodies takes several passes per iteration.
-// ENDS as for iterate_body: 1 when no listed scene has variable ends, 2 otherwise,
+// ENDS as for iterate_resident: 1 when no listed scene has variable ends, 2 otherwise,
 // so that each variant carries one loop over the static ends; DRIVEN when the
 // scenes have driven bonds (the variants without carry no refactor code)
 template <typename T, int LPB, bool CONTACT, int ENDS, bool DRIVEN>
@@ -115,7 +115,7 @@ __global__ void __launch_bounds__(Resident<T>::NT) k_resident_step(View<T> v, co
     T* dst = lq[(k + 1) & 1];
     for (int b0 = 0; b0 < n; b0 += BPP) {
       const int b = b0 + t / LPB;  // the same for the LPB lanes of a body
-      if (b < n) iterate_body<T, CONTACT, LPB, true, ENDS>(v, k, nullptr, nullptr, off + b, t % LPB, src, dst, off);
+      if (b < n) iterate_resident<T, CONTACT, LPB, ENDS>(v, k, off + b, t % LPB, src, dst, off);
     }
     __syncthreads();
   }

@@ -54,10 +54,21 @@ __device__ __forceinline__ void predict_body(const View<T>& v, int i) {
   }
 }
 
+// the iterations of wave w of a batch's table in this step: a scene that has
+// taken its steps iterates no more
+__device__ __forceinline__ void arm_wave(const SceneDev* scenes, FlatWave* waves, const int* n_waves, int w) {
+  if (!waves || w >= *n_waves) return;
+  const SceneDev& S = scenes[waves[w].scene];
+  waves[w].iters = S.step < S.steps_total ? S.iters : 0;
+}
+
+// the step's prediction and, for a batch, its wave table (a table has at most
+// one wave per body, so the grid over the bodies covers it)
 template <typename T>
-__global__ void __launch_bounds__(256) k_predict(View<T> v) {
+__global__ void __launch_bounds__(256) k_predict(View<T> v, FlatWave* waves, const int* n_waves) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < v.n) predict_body(v, i);
+  arm_wave(v.scenes, waves, n_waves, i);
 }
 
 // mass64: 8 doubles per body (m, Pi sym 6, -)

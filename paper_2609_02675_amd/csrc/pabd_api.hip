@@ -47,9 +47,9 @@ struct EngineBase {
                              hipStream_t st) = 0;
   virtual pabd_status clear_bodies(int boff, int n, hipStream_t st, int doff, int nd) = 0;
   virtual void factor(hipStream_t st, int first = 0, int count = -1) = 0;
-  virtual void flat_step(int first, int n, int n_scenes, int kmax, bool contacts, int n_driven,
+  virtual void flat_step(int first, int n, int n_scenes, int kmax, bool contacts, int ccap, int n_driven,
                          bool history, bool finish_scenes, hipStream_t st,
-                         const FlatWave* waves = nullptr, const int* n_waves = nullptr,
+                         FlatWave* waves = nullptr, const int* n_waves = nullptr,
                          int wave_grid = 0, const int* resident_grid = nullptr, bool flat = true) = 0;
   virtual pabd_status set_resident(const std::vector<int>& contact, const std::vector<int>& other,
                                    bool variable, hipStream_t st) = 0;
@@ -106,13 +106,13 @@ struct EngineT final : EngineBase {
     return e.clear_bodies(boff, n, st, doff, nd);
   }
   void factor(hipStream_t st, int first, int count) override { e.launch_factor(st, first, count); }
-  void flat_step(int first, int n, int n_scenes, int kmax, bool contacts, int n_driven, bool history,
-                 bool fin, hipStream_t st, const FlatWave* waves, const int* n_waves,
+  void flat_step(int first, int n, int n_scenes, int kmax, bool contacts, int ccap, int n_driven, bool history,
+                 bool fin, hipStream_t st, FlatWave* waves, const int* n_waves,
                  int wave_grid, const int* resident_grid, bool flat) override {
     (void)first;
     const int saved = e.cap.n;
     e.cap.n = n;  // flat kernels cover bodies [0, n)
-    e.launch_flat_step(n_scenes, kmax, contacts, n_driven, history, fin, st, waves, n_waves, wave_grid,
+    e.launch_flat_step(n_scenes, kmax, contacts, ccap, n_driven, history, fin, st, waves, n_waves, wave_grid,
                        resident_grid, flat);
     e.cap.n = saved;
   }
@@ -441,11 +441,11 @@ static void scene_enqueue_step(pabd_scene* s, hipStream_t st) {
   const HostScene& hs = s->hs;
   if (s->resident && !s->history) {
     const int grid[2] = {hs.contact ? 1 : 0, hs.contact ? 0 : 1};
-    s->eng->flat_step(0, std::max(1, hs.n), 1, hs.params.iters, hs.contact, (int)hs.drv_end_i.size(), false,
-                      true, st, nullptr, nullptr, 0, grid, false);
+    s->eng->flat_step(0, std::max(1, hs.n), 1, hs.params.iters, hs.contact, hs.ccap, (int)hs.drv_end_i.size(),
+                      false, true, st, nullptr, nullptr, 0, grid, false);
     return;
   }
-  s->eng->flat_step(0, std::max(1, hs.n), 1, hs.params.iters, hs.contact,
+  s->eng->flat_step(0, std::max(1, hs.n), 1, hs.params.iters, hs.contact, hs.ccap,
                     (int)hs.drv_end_i.size(), s->history, true, st);
 }
 
@@ -708,7 +708,7 @@ struct pabd_batch {
   // device tile table
   int *d_first = nullptr, *d_count = nullptr, *d_kmax = nullptr, *d_ntiles = nullptr;
   int tile_table_cap = 0;
-  // wave table of the flat-path iterations when contact scenes are on it
+  // wave table of the flat-path iterations
   FlatWave* d_waves = nullptr;
   int* d_nwaves = nullptr;
   int wave_table_cap = 0;
@@ -826,25 +826,26 @@ pabd_status batch_tables(pabd_batch* b) {
     if (st != PABD_OK) return fail(st, b->eng->error());
   }
   auto round_up = [](int x, int q, int cap) { return std::min(cap, (x + q - 1) / q * q); };
-  // flat-path waves, when contact scenes share the flat path with others: a
-  // contact scene's bodies take contact_lanes lanes each (64 / contact_lanes
-  // per wave), any other scene's one lane each (64 per wave); a wave stays
-  // within one scene
+  // flat-path waves: a contact scene's bodies take contact_lanes lanes each (64 /
+  // contact_lanes per wave), any other scene's one lane each (64 per wave); a wave
+  // stays within one scene
   b->eng->set_schedule(b->contact_lanes, b->group_waves);
   std::vector<FlatWave> waves;
-  if (b->any_contact) {
+  if (any_flat) {
     std::vector<const Slot*> flat;
     for (const Slot& s : b->slots)
       if (s.used && !s.tiled && !s.resident && s.n > 0) flat.push_back(&s);
     std::sort(flat.begin(), flat.end(), [](const Slot* x, const Slot* y) { return x->boff < y->boff; });
     for (const Slot* s : flat) {
-      const int lpb = s->contact ? b->contact_lanes : 1, per = 64 / lpb;
+      const int lpb = s->contact ? b->contact_lanes : 1, per = 64 / lpb, cc = s->contact ? s->hs->ccap : 0;
+      const int scene = (int)(s - b->slots.data());
       for (int f = 0; f < s->n; f += per)
-        waves.push_back(FlatWave{s->boff + f, std::min(per, s->n - f), lpb, s->contact ? 1 : 0});
+        waves.push_back(FlatWave{s->boff + f, std::min(per, s->n - f), lpb, s->contact ? 1 : 0, scene,
+                                 s->coff + f * cc, cc, 0});
     }
   }
   const int nw = (int)waves.size();
-  if (b->any_contact) {
+  if (any_flat) {
     if (nw > b->wave_table_cap || !b->d_waves) {
       const int cap = std::max(nw, 2 * b->wave_table_cap + 256);
       API_HIP(hipStreamSynchronize(b->stream));
@@ -874,8 +875,8 @@ pabd_status batch_tables(pabd_batch* b) {
   L.table = b->d_first;
   // the wave grid is rounded like the other extents, so most admissions and
   // releases reuse the captured graph
-  L.wave_grid = b->any_contact ? round_up(std::max(1, nw), 256, INT_MAX) : 0;
-  L.waves = b->any_contact ? b->d_waves : nullptr;
+  L.wave_grid = any_flat ? round_up(std::max(1, nw), 256, INT_MAX) : 0;
+  L.waves = any_flat ? b->d_waves : nullptr;
   L.contact_lanes = b->contact_lanes;
   L.group_waves = b->group_waves;
   if (!(L == b->launch)) {
@@ -895,7 +896,7 @@ void batch_enqueue(pabd_batch* b, int nsteps, hipStream_t st) {
   }
   if (L.stream) {
     for (int k = 0; k < nsteps; ++k) {
-      b->eng->flat_step(0, L.stream_n, b->max_slots, L.kmax, L.contact, L.driven_n, false, false, st,
+      b->eng->flat_step(0, L.stream_n, b->max_slots, L.kmax, L.contact, 0, L.driven_n, false, false, st,
                         L.wave_grid > 0 ? b->d_waves : nullptr, b->d_nwaves, L.wave_grid, L.res_grid, L.flat);
       // scenes on the flat path: residual reduction and step counters (tiled
       // and resident scenes do both inside their kernels)
@@ -2060,8 +2061,8 @@ pabd_status pabd_scene_run_noalloc(const pabd_scene_desc* desc, int32_t nsteps, 
   eng->factor(stream);
   const int grid[2] = {hs.contact ? 1 : 0, hs.contact ? 0 : 1};
   for (int k = 0; k < nsteps && hs.n > 0; ++k)
-    eng->flat_step(0, std::max(1, hs.n), 1, hs.params.iters, hs.contact, (int)hs.drv_end_i.size(), false,
-                   true, stream, nullptr, nullptr, 0, resident ? grid : nullptr, !resident);
+    eng->flat_step(0, std::max(1, hs.n), 1, hs.params.iters, hs.contact, hs.ccap, (int)hs.drv_end_i.size(),
+                   false, true, stream, nullptr, nullptr, 0, resident ? grid : nullptr, !resident);
   API_HIP(hipGetLastError());
   st = eng->read_bodies(0, hs.n, c, A, v, w, stream);
   if (st != PABD_OK) return st;
