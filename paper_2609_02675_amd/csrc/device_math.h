@@ -19,7 +19,8 @@ struct Eps;
 // polar iteration ends (the error left is below polar_tol2 / 2); polar_e_one /
 // polar_e_two: det X_1 - 1 after the first step up to which one / two further
 // steps leave that same error (sqrt(tol) and (4 tol)^(1/4), rounded down for the
-// rounding of the determinant)
+// rounding of the determinant); polar_e_three, in FP64 alone: up to which three do
+// ((64 tol)^(1/8))
 template <>
 struct Eps<float> {
   static constexpr float polar_tol2 = 1e-7f;
@@ -33,6 +34,7 @@ struct Eps<double> {
   static constexpr double det_floor = 1e-12;
   static constexpr double polar_e_one = 0.99e-8;
   static constexpr double polar_e_two = 1.4e-4;
+  static constexpr double polar_e_three = 1.6e-2;
 };
 
 template <typename T>
@@ -246,7 +248,9 @@ __device__ __forceinline__ bool wave_all(bool p) { return __builtin_amdgcn_ballo
 // step is not measured; the second takes det X_1 from the cofactors it needs
 // anyway, and with the error target tau / 2 (tau = polar_tol2) it ends the
 // iteration when e <= polar_e_one (e^2 / 2 < tau / 2), adds a third step when
-// e <= polar_e_two (e^4 / 8 < tau / 2), and otherwise hands the lane to the
+// e <= polar_e_two (e^4 / 8 < tau / 2), in FP64, whose small target many
+// iterations of a scene in motion miss with that, a fourth when e <=
+// polar_e_three (e^8 / 128 < tau / 2), and otherwise hands the lane to the
 // measured continuation.  Every Newton iterate has the input's orthogonal
 // factor, so if det X is not safely positive or Newton stalls, the nearest
 // proper rotation from the SVD of the current iterate is the answer.
@@ -270,12 +274,17 @@ __device__ __forceinline__ bool polar_fast(T* X, bool* ok_out) {
   const T det1 = cofactor(X, C1);
   const T e = fma(sigma * sigma * sigma, det1, (T)-1);
   const bool one = ok && unscaled && e <= Eps<T>::polar_e_one;
-  const bool two = ok && unscaled && !one && e <= Eps<T>::polar_e_two;
+  bool three = false;
+  if constexpr (sizeof(T) == 8) three = ok && unscaled && e > Eps<T>::polar_e_two && e <= Eps<T>::polar_e_three;
+  const bool two = three || (ok && unscaled && !one && e <= Eps<T>::polar_e_two);
   const T g1 = one || two ? rcp(sigma * sigma * det1) : (T)0;
   sigma = one || two ? (T)0.5 * sigma : sigma;
 #pragma unroll
   for (int k = 0; k < 9; ++k) X[k] = fma(g1, C1[k], X[k]);
   if (wave_any(two)) polar_newton_plain<T>(X, &sigma, two);
+  if constexpr (sizeof(T) == 8) {
+    if (wave_any(three)) polar_newton_plain<T>(X, &sigma, three);
+  }
 #pragma unroll
   for (int k = 0; k < 9; ++k) X[k] *= sigma;
   *ok_out = ok;
