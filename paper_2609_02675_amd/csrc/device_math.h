@@ -382,26 +382,29 @@ __device__ __forceinline__ void polar_rotation(const T* A, T* R, unsigned* count
 // ---- prediction (Algorithm 1, prediction loop) ---------------------------------
 
 // A* = R(dQ) A with dQ = normalise(h w / 2, 1) (scalar last): the normalised
-// quaternion update Q* = Q + h/2 [w, 0] Q expressed on the rotation matrix.
+// quaternion update Q* = Q + h/2 [w, 0] Q expressed on the rotation matrix.  Every
+// product is fused by name: a sum of products leaves the compiler the choice,
+// which differs from kernel to kernel, and a scene gives the same bits in all.
 template <typename T>
 __device__ __forceinline__ void predict_rotation(const T* A, const T* w, T h, T* As) {
   T x = (T)0.5 * h * w[0], y = (T)0.5 * h * w[1], z = (T)0.5 * h * w[2];
-  T inv = rcp((T)1 + x * x + y * y + z * z);
+  T inv = rcp(fma(z, z, fma(y, y, fma(x, x, (T)1))));
   T R[9];
-  R[0] = (T)1 - (T)2 * (y * y + z * z) * inv;
-  R[1] = (T)2 * (x * y - z) * inv;
-  R[2] = (T)2 * (x * z + y) * inv;
-  R[3] = (T)2 * (x * y + z) * inv;
-  R[4] = (T)1 - (T)2 * (x * x + z * z) * inv;
-  R[5] = (T)2 * (y * z - x) * inv;
-  R[6] = (T)2 * (x * z - y) * inv;
-  R[7] = (T)2 * (y * z + x) * inv;
-  R[8] = (T)1 - (T)2 * (x * x + y * y) * inv;
+  R[0] = fma(-(T)2 * fma(y, y, z * z), inv, (T)1);
+  R[1] = (T)2 * fma(x, y, -z) * inv;
+  R[2] = (T)2 * fma(x, z, y) * inv;
+  R[3] = (T)2 * fma(x, y, z) * inv;
+  R[4] = fma(-(T)2 * fma(x, x, z * z), inv, (T)1);
+  R[5] = (T)2 * fma(y, z, -x) * inv;
+  R[6] = (T)2 * fma(x, z, -y) * inv;
+  R[7] = (T)2 * fma(y, z, x) * inv;
+  R[8] = fma(-(T)2 * fma(x, x, y * y), inv, (T)1);
 #pragma unroll
-  for (int r = 0; r < 3; ++r)
-#pragma unroll
-    for (int c = 0; c < 3; ++c)
-      As[3 * r + c] = R[3 * r] * A[c] + R[3 * r + 1] * A[3 + c] + R[3 * r + 2] * A[6 + c];
+  for (int c = 0; c < 3; ++c) {
+    As[c] = fma(R[2], A[6 + c], fma(R[1], A[3 + c], R[0] * A[c]));
+    As[3 + c] = fma(R[5], A[6 + c], fma(R[3], A[c], R[4] * A[3 + c]));
+    As[6 + c] = fma(R[8], A[6 + c], fma(R[6], A[c], R[7] * A[3 + c]));
+  }
 }
 
 // ---- the 12x12 block (Sec. 4.3) ------------------------------------------------
@@ -423,6 +426,19 @@ __device__ __forceinline__ void block_add_end(Block& B, double w, double x0, dou
   B.d11 += w * x1 * x1;
   B.d12 += w * x1 * x2;
   B.d22 += w * x2 * x2;
+}
+
+__device__ __forceinline__ void settle_block(Block& B) {
+  settle<1>(&B.a);
+  settle<1>(&B.b0);
+  settle<1>(&B.b1);
+  settle<1>(&B.b2);
+  settle<1>(&B.d00);
+  settle<1>(&B.d01);
+  settle<1>(&B.d02);
+  settle<1>(&B.d11);
+  settle<1>(&B.d12);
+  settle<1>(&B.d22);
 }
 
 // Schur complement inverse in FP64: out = (alpha, g0..2, G00 G01 G02 G11 G12 G22)

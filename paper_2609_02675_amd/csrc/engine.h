@@ -125,11 +125,6 @@ struct Engine {
   // residual history (optional)
   double *rh_num = nullptr, *rh_den = nullptr, *rh_rho = nullptr;
   int rh_k = 0;
-  // scenes run by the resident step kernel: [0] contact scenes (four lanes per
-  // body), [1] the others; capacity one entry per scene slot, counts on the device
-  int* res_list[2] = {nullptr, nullptr};
-  int* res_count = nullptr;
-  bool res_variable = true;  // some resident scene has variable ends
   // flat-path schedule: lanes that share a contact body's ends (1, 2, 4, 8 or
   // 16) and wavefronts per workgroup of the iteration launches (1, 2 or 4)
   int contact_lanes = 4, group_waves = 1;
@@ -264,9 +259,6 @@ struct Engine {
     PABD_TRY(alloc(drv_end_i, (size_t)c.dr));
     PABD_TRY(alloc(drv_end_j, (size_t)c.dr));
     PABD_TRY(alloc(drv_param, 13 * (size_t)c.dr));
-    PABD_TRY(alloc(res_list[0], (size_t)c.s));
-    PABD_TRY(alloc(res_list[1], (size_t)c.s));
-    PABD_TRY(alloc(res_count, 2));
     if (c.contacts) {
       ncb = c.nc < 0 ? c.n : std::min(c.nc, c.n);
       const size_t nb = (size_t)ncb, nc = (size_t)std::max(1LL, c.cslots);
@@ -304,8 +296,6 @@ struct Engine {
     PABD_HIP(hipMemcpy(srow_end, zero.data(), n * sizeof(int), hipMemcpyHostToDevice));
     PABD_HIP(hipMemcpy(ccount, zero.data(), n * sizeof(int), hipMemcpyHostToDevice));
     PABD_HIP(hipMemcpy(health, zero.data(), (size_t)c.s * sizeof(int), hipMemcpyHostToDevice));
-    const int zero_counts[2] = {0, 0};
-    PABD_HIP(hipMemcpy(res_count, zero_counts, sizeof zero_counts, hipMemcpyHostToDevice));
     std::vector<double> rz((size_t)c.s, 0.0);
     PABD_HIP(hipMemcpy(rho, rz.data(), rz.size() * sizeof(double), hipMemcpyHostToDevice));
     std::vector<unsigned> zero2n(2 * n, 0u);
@@ -500,44 +490,37 @@ struct Engine {
     hipLaunchKernelGGL(k_sort_contacts<T>, dim3((unsigned)std::max(1, n)), dim3(64), 0, st, v);
   }
 
-  // the scene slots the resident step kernel runs: [0] contact scenes, [1] others
-  // variable: some listed scene has variable ends (augmented, polynomial, slider)
-  pabd_status set_resident(const std::vector<int>& contact, const std::vector<int>& other, bool variable,
-                           hipStream_t st) {
-    res_variable = variable;
-    const int counts[2] = {(int)contact.size(), (int)other.size()};
-    if (counts[0]) PABD_HIP(hipMemcpyAsync(res_list[0], contact.data(), counts[0] * sizeof(int), hipMemcpyHostToDevice, st));
-    if (counts[1]) PABD_HIP(hipMemcpyAsync(res_list[1], other.data(), counts[1] * sizeof(int), hipMemcpyHostToDevice, st));
-    PABD_HIP(hipMemcpyAsync(res_count, counts, sizeof counts, hipMemcpyHostToDevice, st));
-    PABD_HIP(hipStreamSynchronize(st));
-    return PABD_OK;
-  }
-
-  // one step of the resident scenes: grid[0] workgroups over the contact list,
-  // grid[1] over the other (extents rounded by the caller; extra workgroups leave)
-  // n_driven > 0: the resident scenes' driven anchors and refactor run inside
-  // the resident kernel (no flat-path scene shares the step)
-  void launch_resident(const int* grid, int n_driven, hipStream_t st) {
-    View<T> v = view();
-    const DrivenTable dt{n_driven, drv_scene, drv_end_i, drv_end_j, drv_param, mass64};
-    const bool driven = n_driven > 0;
-    if (res_variable && driven)
-      launch_resident_as<2, true>(v, grid, dt, st);
-    else if (res_variable)
-      launch_resident_as<2, false>(v, grid, dt, st);
-    else if (driven)
-      launch_resident_as<1, true>(v, grid, dt, st);
+  // nsteps steps of the plain scene in the resident kernels, after a contact scene's
+  // contact construction (then nsteps is 1); general: it has variable bonds
+  void launch_resident(bool contact, bool general, int n_driven, int ccap, int nsteps, hipStream_t st) {
+    const int lanes = cap.n * (contact ? 4 : 1);
+    if (lanes <= 64)
+      launch_resident_as<64>(contact, general, n_driven, ccap, nsteps, st);
+    else if (lanes <= 256)
+      launch_resident_as<256>(contact, general, n_driven, ccap, nsteps, st);
+    else if (lanes <= 512)
+      launch_resident_as<512>(contact, general, n_driven, ccap, nsteps, st);
     else
-      launch_resident_as<1, false>(v, grid, dt, st);
+      launch_resident_as<Resident<T>::NT>(contact, general, n_driven, ccap, nsteps, st);
   }
-  template <int ENDS, bool DRIVEN>
-  void launch_resident_as(const View<T>& v, const int* grid, const DrivenTable& dt, hipStream_t st) {
-    if (grid[0] > 0)
-      hipLaunchKernelGGL((k_resident_step<T, 4, true, ENDS, DRIVEN>), dim3(grid[0]), dim3(Resident<T>::NT), 0,
-                         st, v, (const int*)res_list[0], (const int*)res_count, dt);
-    if (grid[1] > 0)
-      hipLaunchKernelGGL((k_resident_step<T, 1, false, ENDS, DRIVEN>), dim3(grid[1]), dim3(Resident<T>::NT), 0,
-                         st, v, (const int*)res_list[1], (const int*)(res_count + 1), dt);
+  template <int NT>
+  void launch_resident_as(bool contact, bool general, int n_driven, int ccap, int nsteps, hipStream_t st) {
+    const View<T> v = view();
+    const DrivenTable dt{n_driven, drv_scene, drv_end_i, drv_end_j, drv_param, mass64};
+    const bool g = general || n_driven > 0;
+    if constexpr (NT <= 256) {
+      if (contact) {
+        if (g)
+          hipLaunchKernelGGL((k_resident_contact<T, NT, true>), dim3(1), dim3(NT), 0, st, v, cap.n, ccap, dt);
+        else
+          hipLaunchKernelGGL((k_resident_contact<T, NT, false>), dim3(1), dim3(NT), 0, st, v, cap.n, ccap, dt);
+        return;
+      }
+    }
+    if (g)
+      hipLaunchKernelGGL((k_resident_joints<T, NT, true>), dim3(1), dim3(NT), 0, st, v, cap.n, nsteps, dt);
+    else
+      hipLaunchKernelGGL((k_resident_joints<T, NT, false>), dim3(1), dim3(NT), 0, st, v, cap.n, nsteps, dt);
   }
 
   // FP64 block factorisation of bodies [first, first + count)
@@ -591,21 +574,13 @@ struct Engine {
   // contact_lanes lanes per body of a contact scene, one per body of any other
   // scene.
   //
-  // resident_grid (optional): the scenes of the resident lists take their whole
-  // step in the resident kernel, after the contact construction; with
-  // flat = false no flat-path kernel is launched (every flat scene is resident).
-  //
   // ccap: contact slots per body of a plain scene (a wave table holds its own)
   void launch_flat_step(int n_scenes, int kmax, bool contacts, int ccap, int n_driven, bool history,
                         bool finish_scenes, hipStream_t st, FlatWave* waves = nullptr,
-                        const int* n_waves = nullptr, int wave_grid = 0,
-                        const int* resident_grid = nullptr, bool flat = true) {
+                        const int* n_waves = nullptr, int wave_grid = 0) {
     View<T> v = view();
     const dim3 g = grid_for(cap.n, 256), b(256);
-    // with every scene resident the driven update and refactor run in the
-    // resident kernel, after the contact construction, which reads neither
-    const bool drive_inside = resident_grid && !flat;
-    if (n_driven > 0 && !drive_inside) {
+    if (n_driven > 0) {
       hipLaunchKernelGGL(k_update_driven<T>, grid_for(n_driven, 64), dim3(64), 0, st, v, n_driven,
                          (const int*)drv_scene, (const int*)drv_end_i, (const int*)drv_end_j,
                          (const double*)drv_param);
@@ -613,10 +588,8 @@ struct Engine {
     }
     // with contacts, the contact construction's first kernel also predicts
     // (when its body range covers the flat path's)
-    const bool predict_in_prep = contacts && flat && ncb >= cap.n;
+    const bool predict_in_prep = contacts && ncb >= cap.n;
     if (contacts) launch_contacts(n_scenes, st, predict_in_prep, waves, n_waves);
-    if (resident_grid) launch_resident(resident_grid, drive_inside ? n_driven : 0, st);
-    if (!flat) return;
     if (!predict_in_prep) hipLaunchKernelGGL(k_predict<T>, g, b, 0, st, v, waves, n_waves);
     double* hn = history ? rh_num : nullptr;
     double* hd = history ? rh_den : nullptr;

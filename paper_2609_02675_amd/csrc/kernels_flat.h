@@ -8,7 +8,8 @@
 //   k_iterate_waves  the same over a batch's table of wavefronts (CL lanes per
 //               body of a contact scene, one per body of any other scene)
 // with the force terms of the variable ends (augmented, polynomial, slider) and
-// of the contact ends.  The resident step kernel runs the same body iteration.
+// of the contact ends.  The resident step kernel forms its iteration from the
+// same pieces.
 #pragma once
 
 #include "common.h"
@@ -18,6 +19,12 @@
 
 namespace pabd {
 
+// a . b, fused in one order in every kernel
+template <typename T>
+__device__ __forceinline__ T dot_fused(const T* a, const T* b) {
+  return fma(a[2], b[2], fma(a[0], b[0], a[1] * b[1]));
+}
+
 // one augmented end (Sec. 5.2.2) with bond vector d = y_o - y_s at iterate k:
 // h^2-scaled force and implicit weight of Psi = 1/2 kappa C^2 + lambda C, C = d - l
 // (the multiplier's tension beyond kappa l joins the weight), then the
@@ -25,7 +32,7 @@ namespace pabd {
 template <typename T>
 __device__ __forceinline__ T augmented_end(T* a, const T* d, T h2, T beta, T* f) {
   const T kap = a[0], lam = a[1], l = a[2];
-  const T dn = sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
+  const T dn = sqrt(dot_fused(d, d));
   T w = kap, phim = lam - kap * l;
   if (phim > (T)0 && dn > (T)1e-12) {
     w += phim / dn;
@@ -45,31 +52,43 @@ __device__ __forceinline__ T augmented_end(T* a, const T* d, T h2, T beta, T* f)
 // kappa (d - l)^{p-1} = kappa sum_k C(p-1, k) d^k (-l)^{p-1-k}; the terms with
 // p-1-k even are >= 0 and form phi^+ (implicit weight phi^+ / d), the others
 // phi^- (explicit) -- the split of Sec. 4.2.1; a = (kappa, 0, l, -p)
+//
+// The sums for one order, every coefficient known at compile time (all are
+// whole numbers below 2^9, so forming them ahead changes no bit).
+template <int P, typename T>
+__device__ __forceinline__ void polynomial_sums(T l, T dn, T* w_out, T* phim_out) {
+  T lp[P];  // l^j
+  lp[0] = (T)1;
+#pragma unroll
+  for (int j = 1; j < P; ++j) lp[j] = lp[j - 1] * l;
+  int binom = 1;
+  T dk1 = (T)1, w = (T)0, phim = (T)0;  // dk1 = d^{k-1}
+#pragma unroll
+  for (int k = 0; k < P; ++k) {
+    if (k > 0) binom = binom * (P - k) / k;
+    const int j = P - 1 - k;
+    if (j % 2 == 0) {
+      if (k >= 1) w += (T)binom * dk1 * lp[j];
+    } else {
+      phim -= (T)binom * (k >= 1 ? dk1 * dn : (T)1) * lp[j];
+    }
+    if (k >= 1) dk1 *= dn;
+  }
+  *w_out = w;
+  *phim_out = phim;
+}
 template <typename T>
 __device__ __forceinline__ T polynomial_end(const T* a, const T* d, T h2, T* f) {
   const T kap = a[0], l = a[2];
-  const int p = (int)(-a[3]);
-  const T dn = sqrt(d[0] * d[0] + d[1] * d[1] + d[2] * d[2]);
-  T lp[12];  // l^j
-  lp[0] = (T)1;
-#pragma unroll
-  for (int j = 1; j < 12; ++j) lp[j] = lp[j - 1] * l;
-  T binom = (T)1, dk1 = (T)1, w = (T)0, phim = (T)0;  // dk1 = d^{k-1}
-#pragma unroll
-  for (int k = 0; k < 12; ++k) {
-    if (k >= p) break;
-    if (k > 0) binom = binom * (T)(p - k) / (T)k;
-    const int j = p - 1 - k;
-    T lj = (T)0;
-#pragma unroll
-    for (int u = 0; u < 12; ++u)
-      if (u == j) lj = lp[u];
-    if (j % 2 == 0) {
-      if (k >= 1) w += binom * dk1 * lj;
-    } else {
-      phim -= binom * (k >= 1 ? dk1 * dn : (T)1) * lj;
-    }
-    if (k >= 1) dk1 *= dn;
+  const T dn = sqrt(dot_fused(d, d));
+  T w = (T)0, phim = (T)0;
+  switch ((int)(-a[3])) {
+    case 2: polynomial_sums<2>(l, dn, &w, &phim); break;
+    case 4: polynomial_sums<4>(l, dn, &w, &phim); break;
+    case 6: polynomial_sums<6>(l, dn, &w, &phim); break;
+    case 8: polynomial_sums<8>(l, dn, &w, &phim); break;
+    case 10: polynomial_sums<10>(l, dn, &w, &phim); break;
+    default: polynomial_sums<12>(l, dn, &w, &phim); break;
   }
   w *= kap;
   phim *= kap;
@@ -93,8 +112,9 @@ template <typename T>
 __device__ __forceinline__ T slider_end(const T* d0, const T* A, const T* u, T* d) {
   T g[3];
 #pragma unroll
-  for (int r = 0; r < 3; ++r) g[r] = A ? A[3 * r] * u[0] + A[3 * r + 1] * u[1] + A[3 * r + 2] * u[2] : u[r];
-  const T t = (d0[0] * g[0] + d0[1] * g[1] + d0[2] * g[2]) / (g[0] * g[0] + g[1] * g[1] + g[2] * g[2]);
+  for (int r = 0; r < 3; ++r) g[r] = A ? dot_fused(A + 3 * r, u) : u[r];
+  T t = dot_fused(d0, g) / dot_fused(g, g);
+  settle<1>(&t);
 #pragma unroll
   for (int r = 0; r < 3; ++r) d[r] = d0[r] - t * g[r];
   return t;
@@ -109,11 +129,11 @@ template <typename T>
 __device__ __forceinline__ bool contact_end_force(T kap, T mu, const T* n, const T* d, T* f) {
   const T d0 = d[0], d1 = d[1], d2 = d[2];
   const T n0 = n[0], n1 = n[1], n2 = n[2];
-  T dn = n0 * d0 + n1 * d1 + n2 * d2;  // = -gap
+  T dn = dot_fused(n, d);  // = -gap
   if (!(dn > (T)0)) return false;
   T fn = kap * dn;
-  T t0 = kap * (d0 - dn * n0), t1 = kap * (d1 - dn * n1), t2 = kap * (d2 - dn * n2);
-  T tn2 = t0 * t0 + t1 * t1 + t2 * t2;
+  T t0 = kap * fma(-dn, n0, d0), t1 = kap * fma(-dn, n1, d1), t2 = kap * fma(-dn, n2, d2);
+  T tn2 = fma(t2, t2, fma(t0, t0, t1 * t1));
   T lim = mu * fn;
   if (tn2 > lim * lim) {
     T sc = lim * rsqrt_(tn2);
@@ -121,9 +141,9 @@ __device__ __forceinline__ bool contact_end_force(T kap, T mu, const T* n, const
     t1 *= sc;
     t2 *= sc;
   }
-  f[0] = fn * n0 + t0;
-  f[1] = fn * n1 + t1;
-  f[2] = fn * n2 + t2;
+  f[0] = fma(fn, n0, t0);
+  f[1] = fma(fn, n1, t1);
+  f[2] = fma(fn, n2, t2);
   return true;
 }
 
@@ -172,16 +192,27 @@ __device__ __forceinline__ U lane_sum(U x) {
 }
 
 // The pieces of one Jacobi iteration of a body, shared by the flat kernels and
-// the resident step so that both round alike: its static ends (quadratic only,
-// or of any kind), a contact end, the sum across the lanes that share the body,
-// and the solve with the local step.
+// the resident step so that both round alike: a static end (quadratic, or of any
+// kind), a contact end, the sum across the lanes that share the body, and the
+// solve with the local step.
+
+// one quadratic static end
+template <typename T>
+__device__ __forceinline__ void quadratic_end(const T* E, int j, const T* q, const T* qj, T* rb) {
+  T d[3], f[3];
+  bond_vec<T>(q, E, j < 0 ? (const T*)nullptr : qj, E + 4, d);
+  quad_end_force(E, d, f);
+  settle<3>(f);
+  add_JT(rb, E, f[0], f[1], f[2]);
+  settle<QW>(rb);
+}
 
 // forces of the static ends e, e + LPB, ... below e1, quadratic ends only, two
 // ends per round with both ends' loads (record and partner state) in flight
-// together; each end's terms are added in end order
-template <typename T, int LPB>
-__device__ __forceinline__ void quadratic_ends(const View<T>& v, int e, int e1, const T* q, const T* qs, int qoff,
-                                               T* rb) {
+// together; each end's terms are added in end order.  state(j, qj) loads a
+// partner's q^k.
+template <typename T, int LPB, typename State>
+__device__ __forceinline__ void quadratic_ends(const View<T>& v, int e, int e1, const T* q, State state, T* rb) {
   constexpr int QR = Rec<T>::Q;
   for (; e < e1; e += 2 * LPB) {
     const int eb = e + LPB;
@@ -191,85 +222,92 @@ __device__ __forceinline__ void quadratic_ends(const View<T>& v, int e, int e1, 
     T Ea[EW], Eb[EW], qa[QR], qb[QR];
     load<T, EW>(v.se + (size_t)EW * e, Ea);
     if (hb) load<T, EW>(v.se + (size_t)EW * eb, Eb);
-    if (ja >= 0) load<T, QR>(qs + (size_t)QR * (ja - qoff), qa);
-    if (jb >= 0) load<T, QR>(qs + (size_t)QR * (jb - qoff), qb);
-    T d[3], f[3];
-    bond_vec<T>(q, Ea, ja < 0 ? (const T*)nullptr : qa, Ea + 4, d);
-    quad_end_force(Ea, d, f);
-    settle<3>(f);
-    add_JT(rb, Ea, f[0], f[1], f[2]);
-    if (hb) {
-      bond_vec<T>(q, Eb, jb < 0 ? (const T*)nullptr : qb, Eb + 4, d);
-      quad_end_force(Eb, d, f);
-      settle<3>(f);
-      add_JT(rb, Eb, f[0], f[1], f[2]);
-    }
+    if (ja >= 0) state(ja, qa);
+    if (jb >= 0) state(jb, qb);
+    quadratic_end(Ea, ja, q, qa, rb);
+    if (hb) quadratic_end(Eb, jb, q, qb, rb);
   }
 }
 
-// the same for ends of any kind (augmented, polynomial and slider ends among
-// others; var: the body owns some), one end at a time: every end's terms are
-// formed with the same operations in the same order as above.  Ends whose
-// weight or point moves add to dB, the change of the block, and set refactor;
-// `last`: the step's last iteration.
-template <typename T, int LPB>
+// one static end of any kind, record E and, for a body with variable ends, its
+// state a (else zeros), partner j (-1: the world) at qj.  Ends whose weight or
+// point moves add to dB, the change of the block, and set refactor; an augmented
+// end's multiplier and stiffness move on in a, a slider's anchor, in the step's
+// last iteration, in E[7].
+template <typename T>
+__device__ __forceinline__ void general_end(T* E, T* a, int j, const T* q, const T* qj, const SceneDev& S, bool last,
+                                            T* rb, Block& dB, bool& refactor) {
+  const T kind = a[3];
+  // a slider end's line anchor sits t0 = E[7] along the axis from the given
+  // one (a slider's rest length is 0, so E[7] holds no phi^-): the same line,
+  // re-anchored near the point every step so that the bond vector, whose
+  // across-axis part is the force, stays short (in FP32 a long one would lose
+  // that part to rounding)
+  T xs[3] = {E[0], E[1], E[2]}, xo[3] = {E[4], E[5], E[6]};
+  if (kind == (T)AL_SLIDER_POINT) {
+#pragma unroll
+    for (int r = 0; r < 3; ++r) xo[r] = fma(E[7], a[r], xo[r]);
+  } else if (kind == (T)AL_SLIDER_LINE) {
+#pragma unroll
+    for (int r = 0; r < 3; ++r) xs[r] = fma(E[7], a[r], xs[r]);
+  }
+  T d[3], f[3];
+  bond_vec<T>(q, xs, j < 0 ? (const T*)nullptr : qj, xo, d);
+  settle<3>(d);
+  if (kind == (T)AL_SLIDER_POINT) {
+    // fixed weight at the own point (in the static block), drawn to the foot
+    T dp[3];
+    const T t = slider_end(d, j < 0 ? (const T*)nullptr : qj + 3, a, dp);
+    end_force(E[3], (T)0, dp, f);
+    settle<3>(f);
+    add_JT(rb, E, f[0], f[1], f[2]);
+    if (last) E[7] = E[7] - t;  // the foot is -t from the anchor
+  } else if (kind == (T)AL_SLIDER_LINE) {
+    // the own point is the foot xf = x_s + t u, so its weight moves every iteration
+    T dp[3];
+    const T t = slider_end(d, q + 3, a, dp);
+    const T xf[3] = {fma(t, a[0], xs[0]), fma(t, a[1], xs[1]), fma(t, a[2], xs[2])};
+    end_force(E[3], (T)0, dp, f);
+    settle<3>(f);
+    add_JT(rb, xf, f[0], f[1], f[2]);
+    block_add_end(dB, (double)E[3], (double)xf[0], (double)xf[1], (double)xf[2]);
+    refactor = true;
+    if (last) E[7] = E[7] + t;
+  } else if (kind != (T)0) {
+    const T w = kind > (T)0 ? augmented_end(a, d, (T)(S.h * S.h), (T)S.al_beta, f)
+                            : polynomial_end(a, d, (T)(S.h * S.h), f);
+    settle<3>(f);
+    block_add_end(dB, (double)w, (double)E[0], (double)E[1], (double)E[2]);
+    refactor = true;
+    add_JT(rb, E, f[0], f[1], f[2]);
+  } else {
+    quad_end_force(E, d, f);
+    settle<3>(f);
+    add_JT(rb, E, f[0], f[1], f[2]);
+  }
+  settle<QW>(rb);
+  settle_block(dB);
+}
+
+// forces of the static ends e, e + LPB, ... below e1 of any kind, from global
+// memory, one at a time: every end's terms are formed with the same operations
+// in the same order as above.  var: the body owns variable ends; state(j, qj)
+// loads the partner's q^k; `last`: the step's last iteration.
+template <typename T, int LPB, typename State>
 __device__ __forceinline__ void general_ends(const View<T>& v, const SceneDev& S, int e, int e1, bool var, bool last,
-                                             const T* q, const T* qs, int qoff, T* rb, Block& dB, bool& refactor) {
-  constexpr int QR = Rec<T>::Q;
+                                             const T* q, State state, T* rb, Block& dB, bool& refactor) {
   for (; e < e1; e += LPB) {
     const int j = v.se_partner[e];
-    T E[EW];
+    T E[EW], a[4] = {(T)0, (T)0, (T)0, (T)0}, qj[Rec<T>::Q];
     load<T, EW>(v.se + (size_t)EW * e, E);
-    T* a = var ? v.al + 4 * (size_t)e : nullptr;
-    const T kind = a ? a[3] : (T)0;
-    // a slider end's line anchor sits t0 = E[7] along the axis from the given
-    // one (a slider's rest length is 0, so E[7] holds no phi^-): the same line,
-    // re-anchored near the point every step so that the bond vector, whose
-    // across-axis part is the force, stays short (in FP32 a long one would lose
-    // that part to rounding)
-    T xs[3] = {E[0], E[1], E[2]}, xo[3] = {E[4], E[5], E[6]};
-    if (kind == (T)AL_SLIDER_POINT) {
-#pragma unroll
-      for (int r = 0; r < 3; ++r) xo[r] = fma(E[7], a[r], xo[r]);
-    } else if (kind == (T)AL_SLIDER_LINE) {
-#pragma unroll
-      for (int r = 0; r < 3; ++r) xs[r] = fma(E[7], a[r], xs[r]);
-    }
-    T d[3], f[3];
-    T qj[QR];
-    if (j < 0) {
-      bond_vec<T>(q, xs, nullptr, xo, d);
-    } else {
-      load<T, QR>(qs + (size_t)QR * (j - qoff), qj);
-      bond_vec<T>(q, xs, qj, xo, d);
-    }
-    if (kind == (T)AL_SLIDER_POINT) {
-      // fixed weight at the own point (in the static block), drawn to the foot
-      T dp[3];
-      const T t = slider_end(d, j < 0 ? (const T*)nullptr : qj + 3, a, dp);
-      end_force(E[3], (T)0, dp, f);
-      add_JT(rb, E, f[0], f[1], f[2]);
-      if (last) v.se[(size_t)EW * e + 7] = E[7] - t;  // the foot is -t from the anchor
-    } else if (kind == (T)AL_SLIDER_LINE) {
-      // the own point is the foot xf = x_s + t u, so its weight moves every iteration
-      T dp[3];
-      const T t = slider_end(d, q + 3, a, dp);
-      const T xf[3] = {fma(t, a[0], xs[0]), fma(t, a[1], xs[1]), fma(t, a[2], xs[2])};
-      end_force(E[3], (T)0, dp, f);
-      add_JT(rb, xf, f[0], f[1], f[2]);
-      block_add_end(dB, (double)E[3], (double)xf[0], (double)xf[1], (double)xf[2]);
-      refactor = true;
-      if (last) v.se[(size_t)EW * e + 7] = E[7] + t;
-    } else if (kind != (T)0) {
-      const T w = kind > (T)0 ? augmented_end(a, d, (T)(S.h * S.h), (T)S.al_beta, f)
-                              : polynomial_end(a, d, (T)(S.h * S.h), f);
-      block_add_end(dB, (double)w, (double)E[0], (double)E[1], (double)E[2]);
-      refactor = true;
-      add_JT(rb, E, f[0], f[1], f[2]);
-    } else {
-      quad_end_force(E, d, f);
-      settle<3>(f);
-      add_JT(rb, E, f[0], f[1], f[2]);
+    if (var) load<T, 4>(v.al + 4 * (size_t)e, a);
+    if (j >= 0) state(j, qj);
+    general_end(E, a, j, q, qj, S, last, rb, dB, refactor);
+    if (a[3] > (T)0) {
+      v.al[4 * (size_t)e] = a[0];
+      v.al[4 * (size_t)e + 1] = a[1];
+    } else if (last && (a[3] == (T)AL_SLIDER_POINT || a[3] == (T)AL_SLIDER_LINE)) {
+      v.se[(size_t)EW * e + 7] = E[7];
     }
   }
 }
@@ -286,6 +324,7 @@ __device__ __forceinline__ void contact_end(const T* C, int j, const T* q, const
     oct_decode(C[3], C[7], n);
   } else {
     kap = C[3];
+    settle<1>(&kap);  // no product of the record's own values taken ahead of a caller's loop
     n[0] = C[8];
     n[1] = C[9];
     n[2] = C[10];
@@ -293,6 +332,8 @@ __device__ __forceinline__ void contact_end(const T* C, int j, const T* q, const
   if (!contact_end_force(kap, mu, n, d, f)) return;
   add_JT(rb, C, f[0], f[1], f[2]);
   block_add_end(dB, (double)kap, (double)C[0], (double)C[1], (double)C[2]);
+  settle<QW>(rb);
+  settle_block(dB);
   refactor = true;
 }
 
@@ -353,78 +394,6 @@ __device__ __forceinline__ void solve_body(const T* fac, const T* s, const T* m,
     for (int c = 0; c < 9; ++c) qo[3 + c] = Ah[c];
   } else {
     polar_rotation(Ah, qo + 3, polar, i);
-  }
-}
-
-// One Jacobi iteration of body i in the resident step.  LPB consecutive lanes
-// share a body: they split its static bond ends and contact ends (lane l takes
-// ends l, l + LPB, ...), sum the force terms and the contact change of the FP64
-// block across the lanes, and the first lane solves, projects and stores.  q^k
-// is read from qs and q^{k+1} written to qd, the record of body b at
-// (b - qoff) QR of the scene's LDS buffers.  ENDS chooses the loop over the
-// static ends: 1 the quadratic loop (the caller knows the scene has no variable
-// end), 2 the general one.
-template <typename T, bool CONTACT, int LPB, int ENDS>
-__device__ __forceinline__ void iterate_resident(const View<T>& v, int k, int i, int sub, const T* qs, T* qd,
-                                                 int qoff) {
-  constexpr int QR = Rec<T>::Q;
-  const int sc = v.bscene[i];
-  if (sc < 0) return;
-  if (v.flags[i] & F_PINNED) return;
-  const SceneDev& S = v.scenes[sc];
-  const int K = S.iters;
-  if (k >= K || S.step >= S.steps_total) return;
-  T q[QR];
-  load<T, QR>(qs + (size_t)QR * (i - qoff), q);
-  T rb[QW];
-#pragma unroll
-  for (int c = 0; c < QW; ++c) rb[c] = (T)0;
-  bool refactor = false;
-  Block dB{};  // contact and augmented part of H^k - H (this lane's ends)
-  if constexpr (ENDS == 1)
-    quadratic_ends<T, LPB>(v, v.srow[i] + sub, v.srow_end[i], q, qs, qoff, rb);
-  else
-    general_ends<T, LPB>(v, S, v.srow[i] + sub, v.srow_end[i], (v.flags[i] & F_VARIABLE) != 0, k == K - 1, q, qs,
-                         qoff, rb, dB, refactor);
-  if constexpr (CONTACT) {
-    int cnt = v.ccount[i];
-    if (cnt > S.ccap) cnt = S.ccap;
-    const size_t base = ce_base(S, i);
-    // the lanes of a body take its ends in turn (neighbouring lanes read
-    // neighbouring records), two ends per round
-    constexpr int W = ContactRec<T>::W;
-    const T mu = (T)S.mu;
-    for (int c = sub; c < cnt; c += 2 * LPB) {
-      const int cb = c + LPB;
-      const bool hb = cb < cnt;
-      const int ja = v.ce_partner[base + c];
-      const int jb = hb ? v.ce_partner[base + cb] : -1;
-      T Ca[W], Cb[W], qa[QR], qb[QR];
-      load<T, W>(v.ce + (size_t)W * (base + c), Ca);
-      if (hb) load<T, W>(v.ce + (size_t)W * (base + cb), Cb);
-      if (ja >= 0) load<T, QR>(qs + (size_t)QR * (ja - qoff), qa);
-      if (jb >= 0) load<T, QR>(qs + (size_t)QR * (jb - qoff), qb);
-      contact_end(Ca, ja, q, qa, mu, rb, dB, refactor);
-      if (hb) contact_end(Cb, jb, q, qb, mu, rb, dB, refactor);
-    }
-  }
-  sum_lanes<T, LPB>(rb, dB, refactor);
-  if (sub != 0) return;
-  T fac[FW];
-  if (refactor)  // H^k changed: a contact penetrates, or a variable end's weight or point moved
-    refactored(v.blk + 10 * (size_t)i, dB, fac);
-  else
-    load<T, FW>(v.fac + (size_t)FW * i, fac);
-  T s[QR], m[MW], qo[QR];
-  load<T, QR>(v.s + (size_t)QR * i, s);
-  load<T, MW>(v.mass + (size_t)MW * i, m);
-  solve_body(fac, s, m, rb, q, (S.debug & 1) != 0, v.polar, i, qo);
-  store<T, QR>(qd + (size_t)QR * (i - qoff), qo);
-  if (k == K - 1) {
-    double num, den;
-    residual_terms(m, qo, q, &num, &den);
-    v.r_num[i] = num;
-    v.r_den[i] = den;
   }
 }
 
@@ -499,10 +468,11 @@ __device__ __forceinline__ void iterate_flat(const View<T>& v, const SceneDev& S
   // a wave with a body that has variable ends takes the general loop, any
   // other wave the quadratic loop (a divergent wave would run both loops one
   // after the other)
+  auto state = [&](int j, T* qj) { load<T, QR>(qs + (size_t)QR * j, qj); };
   if (wave_any(var && !pinned))
-    general_ends<T, LPB>(v, S, eb, ee, var, k == K - 1, q, qs, 0, rb, dB, refactor);
+    general_ends<T, LPB>(v, S, eb, ee, var, k == K - 1, q, state, rb, dB, refactor);
   else
-    quadratic_ends<T, LPB>(v, eb, ee, q, qs, 0, rb);
+    quadratic_ends<T, LPB>(v, eb, ee, q, state, rb);
   if constexpr (CONTACT) {
     const T mu = (T)S.mu;
     cnt = pinned ? 0 : (cnt < ccap ? cnt : ccap);

@@ -14,8 +14,8 @@
 namespace pabd {
 
 // the prediction of body i (Algorithm 1): s = q^0 from q^n and the velocities,
-// and the augmented ends' warm start; scenes of the resident kernel, finished
-// scenes and unused slots are left alone
+// and the augmented ends' warm start; finished scenes and unused slots are left
+// alone
 template <typename T>
 __device__ __forceinline__ void predict_body(const View<T>& v, int i) {
   constexpr int QR = Rec<T>::Q;
@@ -23,7 +23,7 @@ __device__ __forceinline__ void predict_body(const View<T>& v, int i) {
   if (sc < 0) return;
   T q[QR];
   load<T, QR>(v.qn + (size_t)QR * i, q);
-  if (v.scenes[sc].step >= v.scenes[sc].steps_total || v.scenes[sc].resident) return;
+  if (v.scenes[sc].step >= v.scenes[sc].steps_total) return;
   if (v.flags[i] & F_PINNED) {
     store<T, QR>(v.q[0] + (size_t)QR * i, q);
     store<T, QR>(v.q[1] + (size_t)QR * i, q);
@@ -142,8 +142,8 @@ __device__ __forceinline__ void recover_velocity(const T* qf, const T* q0, T ih,
   for (int r = 0; r < 3; ++r)
 #pragma unroll
     for (int c = 0; c < 3; ++c)
-      W[3 * r + c] = dA[3 * r] * q0[3 + 3 * c] + dA[3 * r + 1] * q0[4 + 3 * c] +
-                     dA[3 * r + 2] * q0[5 + 3 * c];
+      W[3 * r + c] = fma(dA[3 * r + 2], q0[5 + 3 * c],
+                         fma(dA[3 * r], q0[3 + 3 * c], dA[3 * r + 1] * q0[4 + 3 * c]));
   // average of [w]_x and -[w]_x^T
   vw[3] = (T)0.5 * (W[7] - W[5]) * ih;
   vw[4] = (T)0.5 * (W[2] - W[6]) * ih;
@@ -163,7 +163,7 @@ __global__ void __launch_bounds__(RED_THREADS) k_reduce_residual(SceneDev* scene
   __shared__ double sn[RED_THREADS], sd[RED_THREADS];
   const int sc = blockIdx.x;
   if (sc >= n_scenes) return;
-  if (scenes[sc].tiled || scenes[sc].resident) return;  // those kernels reduce their own scenes
+  if (scenes[sc].tiled) return;  // the tile kernel reduces its own scenes
   const int off = scenes[sc].body_off, nb = scenes[sc].n_bodies;
   // each thread sums a fixed stride of the scene's bodies in order; the unrolled
   // loop keeps several loads in flight
@@ -226,11 +226,9 @@ __global__ void __launch_bounds__(256) k_reduce_history(int n, int K, const doub
 // the step being taken.  Updates the i-side end's partner anchor and the j-side
 // end's own anchor (T and FP64 copies).
 template <typename T>
-__device__ __forceinline__ void update_driven_entry(const View<T>& v, int b, int sc, const int* d_end_i,
-                                                    const int* d_end_j, const double* d_param) {
-  const SceneDev& S = v.scenes[sc];
-  if (S.step >= S.steps_total) return;
-  const double t = S.t0 + (double)(S.step + 1) * S.h;
+__device__ __forceinline__ void update_driven_entry(const View<T>& v, int b, int step, const SceneDev& S,
+                                                    const int* d_end_i, const int* d_end_j, const double* d_param) {
+  const double t = S.t0 + (double)(step + 1) * S.h;
   const double* p = d_param + 13 * (size_t)b;
   const double th = p[9] + p[10] * sin(2.0 * 3.14159265358979323846 * p[11] * t + p[12]);
   const double u0 = p[0], u1 = p[1], u2 = p[2];
@@ -264,7 +262,8 @@ __global__ void k_update_driven(View<T> v, int n_driven, const int* d_scene, con
   if (b >= n_driven) return;
   const int sc = d_scene[b];
   if (sc < 0) return;  // unused table entry
-  update_driven_entry(v, b, sc, d_end_i, d_end_j, d_param);
+  const SceneDev& S = v.scenes[sc];
+  if (S.step < S.steps_total) update_driven_entry(v, b, S.step, S, d_end_i, d_end_j, d_param);
 }
 
 }  // namespace pabd

@@ -50,13 +50,12 @@ struct EngineBase {
   virtual void flat_step(int first, int n, int n_scenes, int kmax, bool contacts, int ccap, int n_driven,
                          bool history, bool finish_scenes, hipStream_t st,
                          FlatWave* waves = nullptr, const int* n_waves = nullptr,
-                         int wave_grid = 0, const int* resident_grid = nullptr, bool flat = true) = 0;
-  virtual pabd_status set_resident(const std::vector<int>& contact, const std::vector<int>& other,
-                                   bool variable, hipStream_t st) = 0;
-  // the most bodies a scene run by the resident step kernel may have: those
-  // that one pass of the workgroup covers (a contact scene's bodies take four
-  // lanes each); larger scenes wait on their partners' loads pass after pass
-  // there, and run faster on the flat path, spread over many compute units
+                         int wave_grid = 0) = 0;
+  // nsteps steps of a plain scene that the resident kernels take (contact
+  // construction included)
+  virtual void resident_steps(const HostScene& hs, int nsteps, hipStream_t st) = 0;
+  // the most bodies of a scene that one workgroup takes (a contact scene's bodies
+  // take four lanes each)
   virtual int resident_max(bool contact) const = 0;
   virtual void tile_step(int tile_bodies, const TileTable& tt, int grid, int nsteps,
                          hipStream_t st) = 0;
@@ -108,19 +107,31 @@ struct EngineT final : EngineBase {
   void factor(hipStream_t st, int first, int count) override { e.launch_factor(st, first, count); }
   void flat_step(int first, int n, int n_scenes, int kmax, bool contacts, int ccap, int n_driven, bool history,
                  bool fin, hipStream_t st, FlatWave* waves, const int* n_waves,
-                 int wave_grid, const int* resident_grid, bool flat) override {
+                 int wave_grid) override {
     (void)first;
     const int saved = e.cap.n;
     e.cap.n = n;  // flat kernels cover bodies [0, n)
-    e.launch_flat_step(n_scenes, kmax, contacts, ccap, n_driven, history, fin, st, waves, n_waves, wave_grid,
-                       resident_grid, flat);
+    e.launch_flat_step(n_scenes, kmax, contacts, ccap, n_driven, history, fin, st, waves, n_waves, wave_grid);
     e.cap.n = saved;
   }
-  pabd_status set_resident(const std::vector<int>& contact, const std::vector<int>& other, bool variable,
-                           hipStream_t st) override {
-    return e.set_resident(contact, other, variable, st);
+  void resident_steps(const HostScene& hs, int nsteps, hipStream_t st) override {
+    const int nd = (int)hs.drv_end_i.size();
+    if (!hs.contact) {
+      e.launch_resident(false, hs.variable, nd, 0, nsteps, st);
+      return;
+    }
+    for (int k = 0; k < nsteps; ++k) {
+      e.launch_contacts(1, st);
+      e.launch_resident(true, hs.variable, nd, hs.ccap, 1, st);
+    }
   }
-  int resident_max(bool contact) const override { return contact ? Resident<T>::NT / 4 : Resident<T>::NT; }
+  // A contact scene's limit is four waves, one per SIMD of the workgroup's compute
+  // unit: with more, their instructions queue there, while the flat kernels spread
+  // them over the chip (steps of piles, resident against flat: 120 boxes 0.181
+  // against 0.167 ms, 200 boxes 0.222 against 0.180).  Joint scenes gain from one
+  // workgroup at every size it holds (chain of 500 0.043 against 0.093 ms, of
+  // 1,000 0.088 against 0.097).
+  int resident_max(bool contact) const override { return contact ? 64 : Resident<T>::NT; }
   void tile_step(int tb, const TileTable& tt, int grid, int nsteps, hipStream_t st) override {
     View<T> v = e.view();
     switch (tb) {
@@ -403,14 +414,8 @@ pabd_status pabd_scene_create(const pabd_scene_desc* desc, pabd_scene** out) {
   if (st != PABD_OK) return fail(st, s->eng->error());
   s->hs.params.steps_total = INT_MAX;
   s->resident = s->hs.n > 0 && s->hs.n <= s->eng->resident_max(s->hs.contact);
-  s->hs.params.resident = s->resident ? 1 : 0;
   st = s->eng->upload(s->hs, 0, 0, 0, 0, 0, s->stream);
   if (st != PABD_OK) return fail(st, s->eng->error());
-  if (s->resident) {
-    st = s->hs.contact ? s->eng->set_resident({0}, {}, s->hs.variable, s->stream)
-                       : s->eng->set_resident({}, {0}, s->hs.variable, s->stream);
-    if (st != PABD_OK) return fail(st, s->eng->error());
-  }
   s->eng->factor(s->stream);
   API_HIP(hipGetLastError());
   API_HIP(hipStreamSynchronize(s->stream));
@@ -440,9 +445,7 @@ pabd_status pabd_set_allocator(void* (*alloc)(size_t bytes, void* ctx), void (*r
 static void scene_enqueue_step(pabd_scene* s, hipStream_t st) {
   const HostScene& hs = s->hs;
   if (s->resident && !s->history) {
-    const int grid[2] = {hs.contact ? 1 : 0, hs.contact ? 0 : 1};
-    s->eng->flat_step(0, std::max(1, hs.n), 1, hs.params.iters, hs.contact, hs.ccap, (int)hs.drv_end_i.size(),
-                      false, true, st, nullptr, nullptr, 0, grid, false);
+    s->eng->resident_steps(hs, 1, st);
     return;
   }
   s->eng->flat_step(0, std::max(1, hs.n), 1, hs.params.iters, hs.contact, hs.ccap,
@@ -454,6 +457,13 @@ pabd_status pabd_scene_step(pabd_scene* s, int32_t nsteps, void* hip_stream) {
   if (nsteps < 0) return fail(PABD_E_INVALID, "negative step count");
   if (nsteps == 0 || s->hs.n == 0) return PABD_OK;
   hipStream_t st = hip_stream ? (hipStream_t)hip_stream : s->stream;
+  if (s->resident && !s->hs.contact && !s->history) {
+    // a launch takes several steps, so there is nothing to record
+    for (int k = 0; k < nsteps; k += PABD_MAX_STEPS_PER_LAUNCH)
+      s->eng->resident_steps(s->hs, std::min(nsteps - k, PABD_MAX_STEPS_PER_LAUNCH), st);
+    API_HIP(hipGetLastError());
+    return PABD_OK;
+  }
   if (!use_graphs() || s->history) {
     for (int k = 0; k < nsteps; ++k) scene_enqueue_step(s, st);
     API_HIP(hipGetLastError());
@@ -537,11 +547,7 @@ pabd_status pabd_scene_set_debug(pabd_scene* s, int32_t flags) {
   int dbg = flags & 1;
   API_HIP(hipMemcpy((char*)s->eng->scene_table() + offsetof(SceneDev, debug), &dbg, sizeof(int),
                     hipMemcpyHostToDevice));
-  // recording every iteration's residual is the flat kernels' work
-  const int res = s->resident && !s->history ? 1 : 0;
-  API_HIP(hipMemcpy((char*)s->eng->scene_table() + offsetof(SceneDev, resident), &res, sizeof(int),
-                    hipMemcpyHostToDevice));
-  s->graph.reset();
+  s->graph.reset();  // recording every iteration's residual is the flat kernels' work
   return PABD_OK;
 }
 
@@ -670,7 +676,6 @@ struct RangeAlloc {
 struct Slot {
   bool used = false;
   bool tiled = false;
-  bool resident = false;  // not tiled, and its whole step runs in the resident kernel
   int boff = 0, n = 0, eoff = 0, ne = 0, poff = 0, np = 0, doff = 0, nd = 0;
   int coff = 0, nslot = 0;  // contact slots [coff, coff + nslot): n bodies x the scene's capacity
   int tile = -1;
@@ -724,16 +729,14 @@ struct pabd_batch {
   // (and so the captured step graph) unchanged; kernels skip unused slots
   struct Launch {
     int stream_n = 0, driven_n = 0, grid = 0, kmax = 0, tile = 0, wave_grid = 0;
-    int res_grid[2] = {0, 0};  // workgroups over the resident lists (contact, other)
     int contact_lanes = 0, group_waves = 0;
-    bool stream = false, contact = false, flat = false;
+    bool stream = false, contact = false;
     const int* table = nullptr;
     const FlatWave* waves = nullptr;
     bool operator==(const Launch& o) const {
       return stream_n == o.stream_n && driven_n == o.driven_n && grid == o.grid && kmax == o.kmax &&
              tile == o.tile && stream == o.stream && contact == o.contact && table == o.table &&
-             wave_grid == o.wave_grid && waves == o.waves && res_grid[0] == o.res_grid[0] &&
-             res_grid[1] == o.res_grid[1] && flat == o.flat && contact_lanes == o.contact_lanes &&
+             wave_grid == o.wave_grid && waves == o.waves && contact_lanes == o.contact_lanes &&
              group_waves == o.group_waves;
     }
   } launch;
@@ -805,8 +808,6 @@ pabd_status batch_tables(pabd_batch* b) {
   b->stream_kmax = 0;
   b->n_driven_hi = 0;
   b->stream_hi = 0;
-  bool any_flat = false;  // some scene on the flat path iterates in the flat kernels
-  std::vector<int> res_contact, res_other;
   for (int k = 0; k < b->max_slots; ++k) {
     const Slot& s = b->slots[k];
     if (!s.used || s.tiled) continue;
@@ -814,16 +815,7 @@ pabd_status batch_tables(pabd_batch* b) {
     b->any_contact = b->any_contact || s.contact;
     if (s.nd > 0) b->n_driven_hi = std::max(b->n_driven_hi, s.doff + s.nd);
     b->stream_hi = std::max(b->stream_hi, s.boff + std::max(1, s.n));
-    if (s.resident) {
-      (s.contact ? res_contact : res_other).push_back(k);
-    } else {
-      any_flat = true;
-      b->stream_kmax = std::max(b->stream_kmax, s.iters);
-    }
-  }
-  {
-    pabd_status st = b->eng->set_resident(res_contact, res_other, true, b->stream);
-    if (st != PABD_OK) return fail(st, b->eng->error());
+    b->stream_kmax = std::max(b->stream_kmax, s.iters);
   }
   auto round_up = [](int x, int q, int cap) { return std::min(cap, (x + q - 1) / q * q); };
   // flat-path waves: a contact scene's bodies take contact_lanes lanes each (64 /
@@ -831,10 +823,10 @@ pabd_status batch_tables(pabd_batch* b) {
   // stays within one scene
   b->eng->set_schedule(b->contact_lanes, b->group_waves);
   std::vector<FlatWave> waves;
-  if (any_flat) {
+  if (b->any_stream) {
     std::vector<const Slot*> flat;
     for (const Slot& s : b->slots)
-      if (s.used && !s.tiled && !s.resident && s.n > 0) flat.push_back(&s);
+      if (s.used && !s.tiled && s.n > 0) flat.push_back(&s);
     std::sort(flat.begin(), flat.end(), [](const Slot* x, const Slot* y) { return x->boff < y->boff; });
     for (const Slot* s : flat) {
       const int lpb = s->contact ? b->contact_lanes : 1, per = 64 / lpb, cc = s->contact ? s->hs->ccap : 0;
@@ -845,7 +837,7 @@ pabd_status batch_tables(pabd_batch* b) {
     }
   }
   const int nw = (int)waves.size();
-  if (any_flat) {
+  if (b->any_stream) {
     if (nw > b->wave_table_cap || !b->d_waves) {
       const int cap = std::max(nw, 2 * b->wave_table_cap + 256);
       API_HIP(hipStreamSynchronize(b->stream));
@@ -863,11 +855,8 @@ pabd_status batch_tables(pabd_batch* b) {
   pabd_batch::Launch L;
   L.stream = b->any_stream;
   L.contact = b->any_contact;
-  L.flat = any_flat;
   L.kmax = b->stream_kmax;
   // rounded like the other extents, so that most admissions reuse the graph
-  L.res_grid[0] = res_contact.empty() ? 0 : round_up((int)res_contact.size(), 64, b->max_slots);
-  L.res_grid[1] = res_other.empty() ? 0 : round_up((int)res_other.size(), 64, b->max_slots);
   L.stream_n = b->any_stream ? round_up(b->stream_hi, 16384, b->n_stream) : 0;
   L.driven_n = b->n_driven_hi > 0 ? round_up(b->n_driven_hi, 256, b->caps.dr) : 0;
   L.grid = b->grid_tiles > 0 ? round_up(b->grid_tiles, 256, INT_MAX) : 0;
@@ -875,8 +864,8 @@ pabd_status batch_tables(pabd_batch* b) {
   L.table = b->d_first;
   // the wave grid is rounded like the other extents, so most admissions and
   // releases reuse the captured graph
-  L.wave_grid = any_flat ? round_up(std::max(1, nw), 256, INT_MAX) : 0;
-  L.waves = any_flat ? b->d_waves : nullptr;
+  L.wave_grid = b->any_stream ? round_up(std::max(1, nw), 256, INT_MAX) : 0;
+  L.waves = b->any_stream ? b->d_waves : nullptr;
   L.contact_lanes = b->contact_lanes;
   L.group_waves = b->group_waves;
   if (!(L == b->launch)) {
@@ -897,10 +886,10 @@ void batch_enqueue(pabd_batch* b, int nsteps, hipStream_t st) {
   if (L.stream) {
     for (int k = 0; k < nsteps; ++k) {
       b->eng->flat_step(0, L.stream_n, b->max_slots, L.kmax, L.contact, 0, L.driven_n, false, false, st,
-                        L.wave_grid > 0 ? b->d_waves : nullptr, b->d_nwaves, L.wave_grid, L.res_grid, L.flat);
-      // scenes on the flat path: residual reduction and step counters (tiled
-      // and resident scenes do both inside their kernels)
-      if (L.flat) b->eng->finish_scenes(b->max_slots, st);
+                        b->d_waves, b->d_nwaves, L.wave_grid);
+      // scenes on the flat path: residual reduction and step counters (the tile
+      // kernel does both itself)
+      b->eng->finish_scenes(b->max_slots, st);
     }
   }
 }
@@ -959,12 +948,6 @@ pabd_status batch_place_and_upload(pabd_batch* b, int slot) {
   const HostScene& hs = *s.hs;
   const bool tiled = !hs.contact && !hs.driven && !hs.variable && hs.n > 0 && hs.n <= b->tile_bodies;
   s.tiled = tiled;
-  // In a batch the flat path's scenes stay in the flat kernels: a resident
-  // workgroup holds a whole compute unit for one scene's step, which beside
-  // the flat kernels' other scenes costs more than it saves (served mix, all
-  // requests queued: 2.96e9 body-iterations/s with resident scenes against
-  // 3.22e9 without); a single scene alone gains from it (pabd_scene_step).
-  s.resident = false;
   if (tiled) {
     pabd_status st = place_tiled(b, slot, hs.n);
     if (st != PABD_OK) return st;
@@ -998,7 +981,6 @@ pabd_status batch_place_and_upload(pabd_batch* b, int slot) {
   copy.params.ccap = hs.ccap;
   copy.params.ce_off = s.coff;
   copy.params.tiled = tiled ? 1 : 0;
-  copy.params.resident = s.resident ? 1 : 0;
   pabd_status st = b->eng->upload(copy, s.boff, s.eoff, s.poff, s.doff, slot, b->stream);
   if (st != PABD_OK) {
     undo();
@@ -1794,7 +1776,7 @@ pabd_status pabd_batch_tune(pabd_batch* b, int32_t flags, pabd_schedule* out) {
   }
   long long flat_contact = 0, flat_other = 0;
   for (const Slot& s : b->slots)
-    if (s.used && !s.tiled && !s.resident) (s.contact ? flat_contact : flat_other) += s.n;
+    if (s.used && !s.tiled) (s.contact ? flat_contact : flat_other) += s.n;
   if (flat_contact + flat_other > 0) {
     API_HIP(hipDeviceSynchronize());
     if ((st = save()) != PABD_OK) return st;
@@ -2050,19 +2032,17 @@ pabd_status pabd_scene_run_noalloc(const pabd_scene_desc* desc, int32_t nsteps, 
   hs.params.steps_total = INT_MAX;
   // the same path as the plain scene's (pabd_scene_step)
   const bool resident = hs.n > 0 && hs.n <= eng->resident_max(hs.contact);
-  hs.params.resident = resident ? 1 : 0;
   st = eng->upload(hs, 0, 0, 0, 0, 0, stream);
   if (st != PABD_OK) return fail(st, eng->error());
-  if (resident) {
-    st = hs.contact ? eng->set_resident({0}, {}, hs.variable, stream)
-                    : eng->set_resident({}, {0}, hs.variable, stream);
-    if (st != PABD_OK) return fail(st, eng->error());
-  }
   eng->factor(stream);
-  const int grid[2] = {hs.contact ? 1 : 0, hs.contact ? 0 : 1};
-  for (int k = 0; k < nsteps && hs.n > 0; ++k)
-    eng->flat_step(0, std::max(1, hs.n), 1, hs.params.iters, hs.contact, hs.ccap, (int)hs.drv_end_i.size(),
-                   false, true, stream, nullptr, nullptr, 0, resident ? grid : nullptr, !resident);
+  if (resident) {
+    for (int k = 0; k < nsteps; k += PABD_MAX_STEPS_PER_LAUNCH)
+      eng->resident_steps(hs, std::min(nsteps - k, PABD_MAX_STEPS_PER_LAUNCH), stream);
+  } else {
+    for (int k = 0; k < nsteps && hs.n > 0; ++k)
+      eng->flat_step(0, std::max(1, hs.n), 1, hs.params.iters, hs.contact, hs.ccap, (int)hs.drv_end_i.size(),
+                     false, true, stream);
+  }
   API_HIP(hipGetLastError());
   st = eng->read_bodies(0, hs.n, c, A, v, w, stream);
   if (st != PABD_OK) return st;

@@ -1,7 +1,8 @@
-"""The flat iteration has two variants, picked by the number of waves in a launch
-(few waves: everything loaded at the start; many: fewer registers).  They form
-the same sums in the same order, so a scene keeps its bits whether it runs alone
-or beside a scene large enough to change the variant."""
+"""The variants of the body iteration form the same sums in the same order, so a
+scene's bits do not depend on which of them runs it: the flat kernels' two
+variants, picked by the number of waves in a launch (few waves: everything loaded
+at the start; many: fewer registers), and the resident kernels' workgroup sizes,
+picked by the scene's size."""
 import numpy as np
 import pytest
 
@@ -51,3 +52,48 @@ def test_launch_size_does_not_change_a_scenes_bits(P, prec, lanes):
     for sc, x, y in zip(scenes, *got):
         for p, q in zip(x, y):
             assert np.array_equal(p, q), sc.name
+
+
+def _moving(sc, seed):
+    """The scene with every body turned, moving and spinning in all directions."""
+    rng = np.random.Generator(np.random.PCG64(seed))
+    n = sc.n_bodies
+    R = S.rot_axis(rng.normal(size=3), 1.0)
+    return sc.copy(c0=sc.c0 @ R.T, A0=R @ sc.A0, v0=rng.uniform(-0.5, 0.5, (n, 3)), w0=rng.uniform(-2, 2, (n, 3)))
+
+
+@pytest.mark.parametrize("prec", [S.PREC_FP32, S.PREC_FP64], ids=["fp32", "fp64"])
+def test_resident_workgroup_size_does_not_change_a_scenes_bits(P, prec):
+    """A plain scene (resident kernels, several steps per launch) against the same
+    scene in a batch that tiles nothing this large (flat kernels, a step at a
+    time): sizes at and beside each workgroup's edge, ends within and beyond what
+    it holds, contact piles at theirs."""
+    chains = [S.chain(n, tilt_deg=20.0, precision=prec) for n in (65, 255, 256, 257, 512, 513, 1024)]
+    nets = [S.spring_net(n, order=p, precision=prec) for n, p in ((2, 12), (8, 4), (16, 6), (17, 2), (23, 4))]
+    star = S.merge([S.spring_net(3, order=4, precision=prec)])  # one hub with more ends than LDS holds
+    hub = np.zeros(12, np.int32)
+    star = star.copy(bond_i=np.concatenate([star.bond_i, hub]), bond_j=np.concatenate([star.bond_j, 1 + np.arange(12, dtype=np.int32) % 8]),
+                     **{k: np.concatenate([getattr(star, k), np.repeat(getattr(star, k)[:1], 12, axis=0)])
+                        for k in ("bond_type", "x_i", "x_j", "kappa", "rest_len", "drive", "order")})
+    other = [S.mass_ratio_chain(precision=prec), S.slider_pair(precision=prec), S.slider_rod(precision=prec),
+             S.linkage("slider", drive_amp_deg=60.0, precision=prec), star]
+    scenes = [_moving(s, k) for k, s in enumerate(chains + nets[:-1])] + other + [nets[-1]]
+    scenes += [_touching(n, prec) for n in (2, 16, 17, 64)]
+    for sc in scenes:
+        if sc.n_bodies > (1024 if prec == S.PREC_FP32 else 512):
+            continue
+        g = P.Scene(sc)
+        g.step(3)
+        g.step(4)
+        b = P.Batch(2, 1 << 28, prec)
+        b.set_schedule(tile_bodies=32)
+        slot = b.admit(sc, 7)
+        for _ in range(7):
+            b.step()
+        if not sc.contact_enable and sc.n_bodies <= 32 and (sc.bond_type == S.BOND_QUADRATIC).all():
+            b.close()
+            continue  # the tile kernel's own arithmetic
+        for p, q in zip(g.state(), b.state(slot)):
+            assert np.array_equal(p, q), sc.name
+        assert g.residual() == pytest.approx(b.residual(slot), rel=1e-12), sc.name
+        b.close()
