@@ -112,7 +112,7 @@ def lib():
     L.pabd_scene_create.argtypes = [_P(_Desc), _P(vp)]
     L.pabd_scene_destroy.argtypes = [vp]
     L.pabd_scene_step.argtypes = [vp, C.c_int32, vp]
-    L.pabd_scene_read_state.argtypes = [vp, _d, _d, _d, _d]
+    L.pabd_scene_read_state.argtypes = [vp, vp, vp, vp, vp]
     L.pabd_scene_residuals.argtypes = [vp, _d, C.c_int32, _i]
     L.pabd_scene_contacts.argtypes = [vp, C.c_int32, _i, _i, _i, _d, _d, _d, _d, _i]
     L.pabd_scene_bond_state.argtypes = [vp, _d, _d]
@@ -129,7 +129,7 @@ def lib():
     L.pabd_batch_step.argtypes = [vp, vp]
     L.pabd_batch_steps.argtypes = [vp, C.c_int32, vp]
     L.pabd_batch_poll.argtypes = [vp, _i, C.c_int32, _i]
-    L.pabd_batch_read_state.argtypes = [vp, C.c_int32, _d, _d, _d, _d]
+    L.pabd_batch_read_state.argtypes = [vp, C.c_int32, vp, vp, vp, vp]
     L.pabd_batch_residual.argtypes = [vp, C.c_int32, _d]
     L.pabd_batch_release.argtypes = [vp, C.c_int32]
     L.pabd_batch_steps_done.argtypes = [vp, C.c_int32, _i]
@@ -279,6 +279,12 @@ def _state_arrays(n):
     return np.zeros((n, 3)), np.zeros((n, 3, 3)), np.zeros((n, 3)), np.zeros((n, 3))
 
 
+def _addresses(arrays):
+    """Addresses of the arrays' data (a tenth of the time of typed ctypes pointers,
+    which counts in a loop that reads thousands of scenes)."""
+    return [a.__array_interface__["data"][0] for a in arrays]
+
+
 def run_noalloc(scene: SceneDesc, nsteps: int, stream: Optional[int] = None):
     """pabd_scene_run_noalloc: create, nsteps steps and read-back in one call,
     with no device allocation (the library's static scratch); returns (c, A, v, w)."""
@@ -317,12 +323,11 @@ class Scene:
         _check(lib().pabd_scene_step(self._h, int(nsteps), C.c_void_p(stream) if stream else None))
 
     def state(self, check: bool = True):
-        c, A, v, w = _state_arrays(self.n)
-        st = lib().pabd_scene_read_state(self._h, _ptr(c, C.c_double), _ptr(A, C.c_double),
-                                         _ptr(v, C.c_double), _ptr(w, C.c_double))
+        out = _state_arrays(self.n)
+        st = lib().pabd_scene_read_state(self._h, *_addresses(out))
         if check:
             _check(st)
-        return c, A, v, w
+        return out
 
     def residuals(self) -> np.ndarray:
         out = np.zeros(self.iters)
@@ -438,12 +443,11 @@ class Batch:
         return out[: min(n.value, cap)].tolist()
 
     def state(self, slot: int, check: bool = True):
-        c, A, v, w = _state_arrays(self._n[slot])
-        st = lib().pabd_batch_read_state(self._h, int(slot), _ptr(c, C.c_double), _ptr(A, C.c_double),
-                                         _ptr(v, C.c_double), _ptr(w, C.c_double))
+        out = _state_arrays(self._n[slot])
+        st = lib().pabd_batch_read_state(self._h, int(slot), *_addresses(out))
         if check:
             _check(st)
-        return c, A, v, w
+        return out
 
     def residual(self, slot: int) -> float:
         r = np.zeros(1)

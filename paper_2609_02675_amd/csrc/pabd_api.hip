@@ -60,7 +60,9 @@ struct EngineBase {
   virtual void tile_step(int tile_bodies, const TileTable& tt, int grid, int nsteps,
                          hipStream_t st) = 0;
   virtual void finish_scenes(int n_scenes, hipStream_t st) = 0;
-  virtual pabd_status read_bodies(int boff, int n, double* c, double* A, double* v, double* w,
+  // state of bodies [boff, boff + n) and the health word of scene `slot`, after
+  // everything enqueued on st, then the whole device, is done
+  virtual pabd_status read_bodies(int boff, int n, int slot, double* c, double* A, double* v, double* w, int* health,
                                   hipStream_t st) = 0;
   virtual pabd_status write_body_field(int body, int field, double value, hipStream_t st) = 0;
   virtual std::string& error() = 0;
@@ -153,10 +155,26 @@ struct EngineT final : EngineBase {
     hipLaunchKernelGGL(k_reduce_residual, dim3(std::max(1, n_scenes)), dim3(RED_THREADS), 0, st, e.scenes,
                        n_scenes, (const double*)e.r_num, (const double*)e.r_den, e.rho);
   }
-  pabd_status read_bodies(int boff, int n, double* c, double* A, double* v, double* w,
+  pabd_status read_bodies(int boff, int n, int slot, double* c, double* A, double* v, double* w, int* health,
                           hipStream_t st) override {
+    const size_t N = (size_t)n, need = (18 * N + 1) * sizeof(double);
+    if (n > 0 && e.h_stage && need <= e.stage_cap) {
+      double* o = reinterpret_cast<double*>(e.h_stage);
+      hipLaunchKernelGGL(k_read_state<T>, dim3((unsigned)((18 * N + 255) / 256)), dim3(256), 0, st, (const T*)e.qn,
+                         (const T*)e.vel, (const int*)(e.health + slot), boff, n, o);
+      if (hipGetLastError() != hipSuccess || hipDeviceSynchronize() != hipSuccess)
+        return fail(PABD_E_DEVICE, "state read failed");
+      if (c) std::memcpy(c, o, 3 * N * sizeof(double));
+      if (A) std::memcpy(A, o + 3 * N, 9 * N * sizeof(double));
+      if (v) std::memcpy(v, o + 12 * N, 3 * N * sizeof(double));
+      if (w) std::memcpy(w, o + 15 * N, 3 * N * sizeof(double));
+      *health = *reinterpret_cast<int*>(o + 18 * N);
+      return PABD_OK;
+    }
+    // no staging buffer, or a smaller one: plain copies
     constexpr int QR = Rec<T>::Q;
     std::vector<T> q((size_t)QR * n), vl((size_t)VW * n);
+    if (hipDeviceSynchronize() != hipSuccess) return fail(PABD_E_DEVICE, "device sync failed");
     if (n > 0) {
       if (hipMemcpyAsync(q.data(), e.qn + (size_t)QR * boff, q.size() * sizeof(T),
                          hipMemcpyDeviceToHost, st) != hipSuccess ||
@@ -164,7 +182,9 @@ struct EngineT final : EngineBase {
                          hipMemcpyDeviceToHost, st) != hipSuccess)
         return fail(PABD_E_DEVICE, "state copy failed");
     }
-    if (hipStreamSynchronize(st) != hipSuccess) return fail(PABD_E_DEVICE, "stream sync failed");
+    if (hipStreamSynchronize(st) != hipSuccess ||
+        hipMemcpy(health, e.health + slot, sizeof(int), hipMemcpyDeviceToHost) != hipSuccess)
+      return fail(PABD_E_DEVICE, "state copy failed");
     for (int b = 0; b < n; ++b) {
       for (int k = 0; k < 3; ++k) {
         if (c) c[3 * b + k] = (double)q[QR * b + k] + (QR > QW ? (double)q[QR * b + 12 + k] : 0.0);
@@ -362,6 +382,7 @@ struct pabd_scene {
   // the whole step in the resident kernel (bodies fit its LDS; not while the
   // residual of every iteration is recorded, which the flat kernels do)
   bool resident = false;
+  bool foreign = false;  // steps were enqueued on a caller's stream since the last read
   Graph graph;
   // releases what the handle holds, also after a create that failed part-way
   // (its own stream is drained first; work on callers' streams is the caller's)
@@ -457,6 +478,7 @@ pabd_status pabd_scene_step(pabd_scene* s, int32_t nsteps, void* hip_stream) {
   if (nsteps < 0) return fail(PABD_E_INVALID, "negative step count");
   if (nsteps == 0 || s->hs.n == 0) return PABD_OK;
   hipStream_t st = hip_stream ? (hipStream_t)hip_stream : s->stream;
+  s->foreign = s->foreign || st != s->stream;
   if (s->resident && !s->hs.contact && !s->history) {
     // a launch takes several steps, so there is nothing to record
     for (int k = 0; k < nsteps; k += PABD_MAX_STEPS_PER_LAUNCH)
@@ -483,11 +505,12 @@ pabd_status pabd_scene_step(pabd_scene* s, int32_t nsteps, void* hip_stream) {
 
 pabd_status pabd_scene_read_state(pabd_scene* s, double* c, double* A, double* v, double* w) {
   if (!s) return fail(PABD_E_INVALID, "null scene");
-  API_HIP(hipDeviceSynchronize());
-  pabd_status st = s->eng->read_bodies(0, s->hs.n, c, A, v, w, s->stream);
-  if (st != PABD_OK) return st;
+  // steps on the handle's own stream precede the read there; others are waited for
+  if (s->foreign) API_HIP(hipDeviceSynchronize());
+  s->foreign = false;
   int health = 0;
-  API_HIP(hipMemcpy(&health, s->eng->health_ptr(), sizeof(int), hipMemcpyDeviceToHost));
+  pabd_status st = s->eng->read_bodies(0, s->hs.n, 0, c, A, v, w, &health, s->stream);
+  if (st != PABD_OK) return st;
   if (health & 1) return fail(PABD_E_DIVERGED, "non-finite state");
   if (health & 2) return fail(PABD_E_DIVERGED, "contact capacity exceeded");
   return PABD_OK;
@@ -721,6 +744,7 @@ struct pabd_batch {
   Graph graph;
   int graph_steps = 0;  // steps one replay of the captured graph advances
   bool dirty = true;
+  bool foreign = false;  // steps were enqueued on a caller's stream since the last read
   int grid_tiles = 0;
   bool any_stream = false, any_contact = false;
   int stream_kmax = 0, n_driven_hi = 0;
@@ -1173,6 +1197,7 @@ pabd_status pabd_batch_steps(pabd_batch* b, int32_t nsteps, void* hip_stream) {
   if (!b) return fail(PABD_E_INVALID, "null batch");
   if (nsteps < 1 || nsteps > PABD_MAX_STEPS_PER_LAUNCH) return fail(PABD_E_INVALID, "nsteps out of range");
   hipStream_t st = hip_stream ? (hipStream_t)hip_stream : b->stream;
+  b->foreign = b->foreign || st != b->stream;
   if (b->dirty) {  // new tables; the graph is rebuilt only if the launch extents changed
     pabd_status s2 = batch_tables(b);
     if (s2 != PABD_OK) return s2;
@@ -1227,12 +1252,12 @@ pabd_status pabd_batch_read_state(pabd_batch* b, int32_t slot, double* c, double
                                   double* w) {
   if (!b) return fail(PABD_E_INVALID, "null batch");
   if (slot < 0 || slot >= b->max_slots || !b->slots[slot].used) return fail(PABD_E_NOTFOUND, "slot not in use");
-  API_HIP(hipDeviceSynchronize());
+  if (b->foreign) API_HIP(hipDeviceSynchronize());
+  b->foreign = false;
   const Slot& s = b->slots[slot];
-  pabd_status st = b->eng->read_bodies(s.boff, s.n, c, A, v, w, b->stream);
-  if (st != PABD_OK) return st;
   int health = 0;
-  API_HIP(hipMemcpy(&health, b->eng->health_ptr() + slot, sizeof(int), hipMemcpyDeviceToHost));
+  pabd_status st = b->eng->read_bodies(s.boff, s.n, slot, c, A, v, w, &health, b->stream);
+  if (st != PABD_OK) return st;
   if (health & 1) return fail(PABD_E_DIVERGED, "non-finite state");
   if (health & 2) return fail(PABD_E_DIVERGED, "contact capacity exceeded");
   return PABD_OK;
@@ -1332,7 +1357,8 @@ static pabd_status batch_repack(pabd_batch* b, int tile_bodies) {
     Slot& s = b->slots[k];
     HostScene& hs = *s.hs;
     std::vector<double> c(3 * s.n), A(9 * s.n), v(3 * s.n), w(3 * s.n);
-    pabd_status st = b->eng->read_bodies(s.boff, s.n, c.data(), A.data(), v.data(), w.data(), b->stream);
+    int health = 0;  // stays where it is
+    pabd_status st = b->eng->read_bodies(s.boff, s.n, k, c.data(), A.data(), v.data(), w.data(), &health, b->stream);
     if (st != PABD_OK) return st;
     auto fresh = std::make_shared<HostScene>(hs);
     for (int i = 0; i < s.n; ++i) {
@@ -2044,10 +2070,9 @@ pabd_status pabd_scene_run_noalloc(const pabd_scene_desc* desc, int32_t nsteps, 
                      false, true, stream);
   }
   API_HIP(hipGetLastError());
-  st = eng->read_bodies(0, hs.n, c, A, v, w, stream);
-  if (st != PABD_OK) return st;
   int health = 0;
-  API_HIP(hipMemcpy(&health, eng->health_ptr(), sizeof(int), hipMemcpyDeviceToHost));
+  st = eng->read_bodies(0, hs.n, 0, c, A, v, w, &health, stream);
+  if (st != PABD_OK) return st;
   if (health & 1) return fail(PABD_E_DIVERGED, "non-finite state");
   if (health & 2) return fail(PABD_E_DIVERGED, "contact capacity exceeded");
   return PABD_OK;
