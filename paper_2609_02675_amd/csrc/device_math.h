@@ -83,19 +83,52 @@ __device__ __forceinline__ void mat_tvec(const T* M, const T* x, T* y) {
   y[2] = M[2] * x[0] + M[5] * x[1] + M[8] * x[2];
 }
 
-// C = cofactor matrix of X (X^{-T} = C / det X); returns det X
+// x of another lane of this lane's row of 16, by a data-parallel primitive of
+// the vector ALU (a shuffle would go through LDS)
+template <int CTRL>
+__device__ __forceinline__ int dpp_of(int x) {
+  return __builtin_amdgcn_mov_dpp(x, CTRL, 0xf, 0xf, true);
+}
+template <int CTRL, typename U>
+__device__ __forceinline__ U lane_of(U x) {
+  if constexpr (sizeof(U) == 8) {
+    const long long b = __builtin_bit_cast(long long, x);
+    const unsigned lo = (unsigned)dpp_of<CTRL>((int)b), hi = (unsigned)dpp_of<CTRL>((int)(b >> 32));
+    return __builtin_bit_cast(U, (long long)(((unsigned long long)hi << 32) | lo));
+  } else {
+    return __builtin_bit_cast(U, dpp_of<CTRL>(__builtin_bit_cast(int, x)));
+  }
+}
+
+// a . b, fused in one order in every kernel
+template <typename T>
+__device__ __forceinline__ T dot_fused(const T* a, const T* b) {
+  return fma(a[2], b[2], fma(a[0], b[0], a[1] * b[1]));
+}
+
+// c = p x s, and x . c, fused by name: kernels that hold a matrix whole and
+// kernels that hold a row per lane round alike
+template <typename T>
+__device__ __forceinline__ void cross_rows(const T* p, const T* s, T* c) {
+  c[0] = fma(p[1], s[2], -(p[2] * s[1]));
+  c[1] = fma(p[2], s[0], -(p[0] * s[2]));
+  c[2] = fma(p[0], s[1], -(p[1] * s[0]));
+}
+template <typename T>
+__device__ __forceinline__ T dot_row(const T* x, const T* c) {
+  return fma(x[2], c[2], fma(x[1], c[1], x[0] * c[0]));
+}
+
+// C = cofactor matrix of X (X^{-T} = C / det X), row r the cross product of the
+// rows after it; returns det X
 template <typename T>
 __device__ __forceinline__ T cofactor(const T* X, T* C) {
-  C[0] = X[4] * X[8] - X[5] * X[7];
-  C[1] = X[5] * X[6] - X[3] * X[8];
-  C[2] = X[3] * X[7] - X[4] * X[6];
-  C[3] = X[2] * X[7] - X[1] * X[8];
-  C[4] = X[0] * X[8] - X[2] * X[6];
-  C[5] = X[1] * X[6] - X[0] * X[7];
-  C[6] = X[1] * X[5] - X[2] * X[4];
-  C[7] = X[2] * X[3] - X[0] * X[5];
-  C[8] = X[0] * X[4] - X[1] * X[3];
-  return X[0] * C[0] + X[1] * C[1] + X[2] * C[2];
+  cross_rows(X + 3, X + 6, C);
+  C[3] = fma(X[2], X[7], -(X[1] * X[8]));
+  C[4] = fma(X[0], X[8], -(X[2] * X[6]));
+  C[5] = fma(X[1], X[6], -(X[0] * X[7]));
+  cross_rows(X, X + 3, C + 6);
+  return dot_row(X, C);
 }
 
 // ---- nearest rotation ---------------------------------------------------------
@@ -476,10 +509,11 @@ __device__ __forceinline__ void block_apply(const F* f, const T* r, T* dq) {
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
     const T* ra = r + 3 + 3 * k;
-    dq[k] = al * r[k] - (g0 * ra[0] + g1 * ra[1] + g2 * ra[2]);
-    dq[3 + 3 * k + 0] = -g0 * r[k] + G00 * ra[0] + G01 * ra[1] + G02 * ra[2];
-    dq[3 + 3 * k + 1] = -g1 * r[k] + G01 * ra[0] + G11 * ra[1] + G12 * ra[2];
-    dq[3 + 3 * k + 2] = -g2 * r[k] + G02 * ra[0] + G12 * ra[1] + G22 * ra[2];
+    // fused by name, as in the kernels that hold a row per lane
+    dq[k] = fma(al, r[k], -fma(g2, ra[2], fma(g0, ra[0], g1 * ra[1])));
+    dq[3 + 3 * k + 0] = fma(G02, ra[2], fma(G01, ra[1], fma(G00, ra[0], -(g0 * r[k]))));
+    dq[3 + 3 * k + 1] = fma(G12, ra[2], fma(G11, ra[1], fma(G01, ra[0], -(g1 * r[k]))));
+    dq[3 + 3 * k + 2] = fma(G22, ra[2], fma(G12, ra[1], fma(G02, ra[0], -(g2 * r[k]))));
   }
 }
 
@@ -615,16 +649,16 @@ __device__ __forceinline__ void add_inertia(T* r, const T* mass, const T* s, con
           p12 = mass[5], p22 = mass[6];
   T dsq[3];
   pos_diff(s, q, dsq);
-  r[0] += m * dsq[0];
-  r[1] += m * dsq[1];
-  r[2] += m * dsq[2];
+  r[0] = fma(m, dsq[0], r[0]);
+  r[1] = fma(m, dsq[1], r[1]);
+  r[2] = fma(m, dsq[2], r[2]);
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
     T d0 = s[3 + 3 * k] - q[3 + 3 * k], d1 = s[4 + 3 * k] - q[4 + 3 * k],
       d2 = s[5 + 3 * k] - q[5 + 3 * k];
-    r[3 + 3 * k] += p00 * d0 + p01 * d1 + p02 * d2;
-    r[4 + 3 * k] += p01 * d0 + p11 * d1 + p12 * d2;
-    r[5 + 3 * k] += p02 * d0 + p12 * d1 + p22 * d2;
+    r[3 + 3 * k] += fma(p02, d2, fma(p00, d0, p01 * d1));
+    r[4 + 3 * k] += fma(p12, d2, fma(p01, d0, p11 * d1));
+    r[5 + 3 * k] += fma(p22, d2, fma(p02, d0, p12 * d1));
   }
 }
 

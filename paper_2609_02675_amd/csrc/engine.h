@@ -16,6 +16,7 @@
 #include "kernels_contact.h"
 #include "kernels_flat.h"
 #include "kernels_resident.h"
+#include "kernels_rows.h"
 #include "kernels_step.h"
 #include "kernels_tile.h"
 
@@ -518,9 +519,26 @@ struct Engine {
     hipLaunchKernelGGL(k_sort_contacts<T>, dim3((unsigned)std::max(1, n)), dim3(64), 0, st, v);
   }
 
+  // Plain scenes of quadratic bonds up to this size take a quad of lanes per body
+  // (kernels_rows.h): as many as a workgroup of 1,024 threads holds, 512 in FP64,
+  // whose rows need more than the 128 registers that 1,024 leave (chain of 200, us
+  // per step: FP32 27 with one lane per body, 20 with quads).
+  static constexpr int ROWS_MAX = sizeof(T) == 4 ? 256 : 128;
   // nsteps steps of the plain scene in the resident kernels, after a contact scene's
   // contact construction (then nsteps is 1); general: it has variable bonds
   void launch_resident(bool contact, bool general, int n_driven, int ccap, int nsteps, hipStream_t st) {
+    if (!contact && !general && n_driven == 0 && cap.n <= ROWS_MAX) {
+      const View<T> v = view();
+      if (cap.n <= 16)
+        hipLaunchKernelGGL((k_resident_rows<T, 64>), dim3(1), dim3(64), 0, st, v, cap.n, nsteps);
+      else if (cap.n <= 64)
+        hipLaunchKernelGGL((k_resident_rows<T, 256>), dim3(1), dim3(256), 0, st, v, cap.n, nsteps);
+      else if (cap.n <= 128)
+        hipLaunchKernelGGL((k_resident_rows<T, 512>), dim3(1), dim3(512), 0, st, v, cap.n, nsteps);
+      else if constexpr (sizeof(T) == 4)
+        hipLaunchKernelGGL((k_resident_rows<T, 1024>), dim3(1), dim3(1024), 0, st, v, cap.n, nsteps);
+      return;
+    }
     const int lanes = cap.n * (contact ? 4 : 1);
     if (lanes <= 64)
       launch_resident_as<64>(contact, general, n_driven, ccap, nsteps, st);

@@ -19,12 +19,6 @@
 
 namespace pabd {
 
-// a . b, fused in one order in every kernel
-template <typename T>
-__device__ __forceinline__ T dot_fused(const T* a, const T* b) {
-  return fma(a[2], b[2], fma(a[0], b[0], a[1] * b[1]));
-}
-
 // one augmented end (Sec. 5.2.2) with bond vector d = y_o - y_s at iterate k:
 // h^2-scaled force and implicit weight of Psi = 1/2 kappa C^2 + lambda C, C = d - l
 // (the multiplier's tension beyond kappa l joins the weight), then the
@@ -158,23 +152,6 @@ __device__ __forceinline__ void residual_terms(const T* m, const T* qo, const T*
   const T cc[3] = {(T)pos_value(q, 0), (T)pos_value(q, 1), (T)pos_value(q, 2)};
   *num = m_norm2(m, dd, dd);
   *den = m_norm2(m, cc, q);
-}
-
-// x of another lane of this lane's row of 16, by a data-parallel primitive of
-// the vector ALU (a shuffle would go through LDS)
-template <int CTRL>
-__device__ __forceinline__ int dpp_of(int x) {
-  return __builtin_amdgcn_update_dpp(x, x, CTRL, 0xf, 0xf, false);
-}
-template <int CTRL, typename U>
-__device__ __forceinline__ U lane_of(U x) {
-  if constexpr (sizeof(U) == 8) {
-    const long long b = __builtin_bit_cast(long long, x);
-    const unsigned lo = (unsigned)dpp_of<CTRL>((int)b), hi = (unsigned)dpp_of<CTRL>((int)(b >> 32));
-    return __builtin_bit_cast(U, (long long)(((unsigned long long)hi << 32) | lo));
-  } else {
-    return __builtin_bit_cast(U, dpp_of<CTRL>(__builtin_bit_cast(int, x)));
-  }
 }
 
 // sum over the LPB consecutive lanes of a body (2, 4, 8 or 16, aligned): pairs,

@@ -73,16 +73,12 @@ struct Plane {
   }
 };
 
-// the scene's FP64 residual in a fixed order (a pairwise tree over the threads,
-// one body each) and its step counter
-template <int NT>
-__device__ __forceinline__ void resident_finish(double num, double den, double* rn, double* rd, double* rho,
-                                                int* step, int steps) {
+// the scene's FP64 residual in a fixed order (a pairwise tree over the partials of
+// NB bodies) and its step counter
+template <int NB>
+__device__ __forceinline__ void resident_finish(double* rn, double* rd, double* rho, int* step, int steps) {
   const int t = threadIdx.x;
-  rn[t] = num;
-  rd[t] = den;
-  __syncthreads();
-  for (int w = NT / 2; w > 0; w >>= 1) {
+  for (int w = NB / 2; w > 0; w >>= 1) {
     if (t < w) {
       rn[t] += rn[t + w];
       rd[t] += rd[t + w];
@@ -346,7 +342,10 @@ __global__ void __launch_bounds__(NT) k_resident_joints(View<T> v, int n, int ns
     }
   }
   double* red = reinterpret_cast<double*>(&lq[0][0]);  // the buffers are done with
-  resident_finish<NT>(num, den, red, red + NT, v.rho, &v.scenes[0].step, step0 + nsteps);
+  red[t] = num;
+  red[NT + t] = den;
+  __syncthreads();
+  resident_finish<NT>(red, red + NT, v.rho, &v.scenes[0].step, step0 + nsteps);
 }
 
 // One step of a contact scene of at most NT / 4 bodies.  Thread t forms the terms
@@ -506,7 +505,10 @@ __global__ void __launch_bounds__(NT) k_resident_contact(View<T> v, int n, int c
     store<T, QR>(v.qn + (size_t)QR * t, q);
     store<T, VW>(v.vel + (size_t)VW * t, vw);
   }
-  resident_finish<NT>(num, den, red, red + NT, v.rho, &v.scenes[0].step, step0 + 1);
+  red[t] = num;
+  red[NT + t] = den;
+  __syncthreads();
+  resident_finish<NT>(red, red + NT, v.rho, &v.scenes[0].step, step0 + 1);
 }
 
 }  // namespace pabd

@@ -112,12 +112,12 @@ __device__ __forceinline__ void end_force(T kap, T phim, const T* d, T* f) {
   f[1] = kap * d[1];
   f[2] = kap * d[2];
   if (phim != (T)0) {
-    T dn2 = d[0] * d[0] + d[1] * d[1] + d[2] * d[2];
+    T dn2 = dot_fused(d, d);
     if (dn2 > (T)1e-24) {
       T sc = phim * rsqrt_(dn2);
-      f[0] += sc * d[0];
-      f[1] += sc * d[1];
-      f[2] += sc * d[2];
+      f[0] = fma(sc, d[0], f[0]);
+      f[1] = fma(sc, d[1], f[1]);
+      f[2] = fma(sc, d[2], f[2]);
     }
   }
 }

@@ -134,8 +134,25 @@ struct EngineT final : EngineBase {
   // workgroup at every size it holds (chain of 500 0.043 against 0.093 ms, of
   // 1,000 0.088 against 0.097).
   int resident_max(bool contact) const override { return contact ? 64 : Resident<T>::NT; }
+  // At most this many tiles (three workgroups per compute unit in FP32, two in FP64,
+  // by registers) take the kernel with a quad of lanes per body; beyond it the
+  // quads' idle lanes cost more issue slots than the shorter chains save.  Us per
+  // step of 64-body tiles (K = 20), one lane per body against quads: FP32 20.1
+  // against 14.4 at 9 tiles, 23.1 against 16.7 at 290, 23.7 against 19.6 at 735,
+  // 23.6 against 30.2 at 1,000; FP64 26.4 against 21.5 at 9, 29.4 against 24.3 at
+  // 151, 31.1 against 31.2 at 506, 32.3 against 47.1 at 735.
+  static constexpr int ROWS_TILES = sizeof(T) == 4 ? 768 : 512;
   void tile_step(int tb, const TileTable& tt, int grid, int nsteps, hipStream_t st) override {
     View<T> v = e.view();
+    if (tb <= 128 && grid <= ROWS_TILES) {
+      if (tb == 32)
+        hipLaunchKernelGGL((k_tile_rows<T, 32>), dim3(grid), dim3(128), 0, st, v, tt, nsteps);
+      else if (tb == 64)
+        hipLaunchKernelGGL((k_tile_rows<T, 64>), dim3(grid), dim3(256), 0, st, v, tt, nsteps);
+      else
+        hipLaunchKernelGGL((k_tile_rows<T, 128>), dim3(grid), dim3(512), 0, st, v, tt, nsteps);
+      return;
+    }
     switch (tb) {
       case 32:
         hipLaunchKernelGGL((k_tile_step<T, 32, 2>), dim3(grid), dim3(32), 0, st, v, tt, nsteps);
