@@ -476,8 +476,8 @@ struct Engine {
 
   // contact-bond construction for every contact scene among the bodies
   // [0, min(cap.n, contact bodies))
-  // a single contact scene of at most this many bodies takes the all-pairs broad
-  // phase (at most 2.1M pair threads)
+  // a single contact scene of at most this many bodies takes the all-pairs search
+  // (at most 2,080 pairs of tiles)
   static constexpr int BRUTE_MAX = 2048;
   // predict: the prep kernel also runs the step's prediction for the bodies
   // [0, min(cap.n, contact bodies))
@@ -492,13 +492,12 @@ struct Engine {
     const int nbk = brute ? 0 : tb;  // bucket counts cleared by the prep kernel
     hipLaunchKernelGGL(k_contact_prep<T>, grid_for(std::max({n, REACH_BINS * n_scenes, nbk}), 256), dim3(256), 0,
                        st, v, cb, n_scenes, nbk, predict, waves, n_waves);
-    hipLaunchKernelGGL(k_contact_reach<T>, grid_for(n, 256), dim3(256), 0, st, v, cb);
     if (brute) {
-      // one scene of few bodies: all pairs directly, no spatial hash
-      const long long threads = (long long)n + (long long)n * (n - 1) / 2;
-      hipLaunchKernelGGL(k_broad_brute<T>, dim3((unsigned)std::max(1LL, (threads + 255) / 256)), dim3(256), 0, st,
-                         v, cb, 0, n);
+      const int tiles = (n + BRUTE_TILE - 1) / BRUTE_TILE, tile_pairs = tiles * (tiles + 1) / 2;
+      hipLaunchKernelGGL(k_contacts_brute<T>, dim3((unsigned)std::max(1, tile_pairs + (n + 31) / 32)), dim3(256), 0, st, v, cb,
+                         0, n, tile_pairs);
     } else {
+      hipLaunchKernelGGL(k_contact_reach<T>, grid_for(n, 256), dim3(256), 0, st, v, cb);
       hipLaunchKernelGGL(k_contact_cells, grid_for(n_scenes, 64), dim3(64), 0, st, scenes, n_scenes,
                          (const unsigned long long*)reach, (const int*)hist);
       hipLaunchKernelGGL(k_hash_count<T>, grid_for(n, 256), dim3(256), 0, st, v, cb);
@@ -513,9 +512,9 @@ struct Engine {
                          dim3(256), 0, st, v, cb);
       hipLaunchKernelGGL(k_large_tasks<T>, dim3(1), dim3(1024), 0, st, v, cb);
       hipLaunchKernelGGL(k_broad_large<T>, dim3(1024), dim3(BL_CHUNK), 0, st, v, cb);
+      const int ng = std::min(8192, std::max(1, (pcap + 255) / 256));
+      hipLaunchKernelGGL(k_narrow_pairs<T>, dim3((unsigned)(ng + (n + 31) / 32)), dim3(256), 0, st, v, cb, ng);
     }
-    const int ng = std::min(8192, std::max(1, (pcap + 255) / 256));
-    hipLaunchKernelGGL(k_narrow_pairs<T>, dim3(ng), dim3(256), 0, st, v, cb);
     hipLaunchKernelGGL(k_sort_contacts<T>, dim3((unsigned)std::max(1, n)), dim3(64), 0, st, v);
   }
 

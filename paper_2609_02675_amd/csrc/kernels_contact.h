@@ -23,17 +23,18 @@
 //                    bodies (scene id in the hash), each bucket a run of 64-byte
 //                    records holding the body's centre, reach, cell and filters;
 //                    large bodies go to a list instead
-//   k_broad_small    14 lanes per body: planes; then own cell and the 13 cells
-//                    of the forward half-neighbourhood of a small body, one per
-//                    lane, pairs with small bodies
+//   k_broad_small    14 lanes per small body: its own cell and the 13 cells of
+//                    the forward half-neighbourhood, one per lane, pairs with
+//                    small bodies
 //   k_large_tasks / k_broad_large   the large bodies' work in tasks of 256
 //                    threads spread over the grid: small partners over the
 //                    cells a body's reach spans (or over the scene's bodies when
 //                    that is fewer), large partners of higher index
-//   k_broad_brute    instead of the hash and both broad kernels, for a single
-//                    scene of few bodies: one thread per pair
-//   k_narrow_pairs   one thread per candidate pair: narrow phase, bond ends into
-//                    the owners' staging slots
+//   k_narrow_pairs   the candidate pairs (eight lanes per pair of boxes that pass
+//                    the exact bounding test): narrow phase, bond ends into the
+//                    owners' staging slots; contacts with planes
+//   k_contacts_brute instead of all of these between prep and sort, for a single
+//                    scene of few bodies
 //   k_sort_contacts  one wave per body, ends copied in canonical key order to
 //                    their final slots, so the iteration sums in a fixed order
 //                    whatever order the atomics produced
@@ -325,14 +326,13 @@ __device__ __forceinline__ double free_mass(const View<T>& v, const ContactBuf& 
   return cb.mass64[8 * (size_t)b];
 }
 
-// write one bond end into the owner's slot list (stiffness as h^2 kappa_c)
+// write one bond end into slot `slot` of the owner's list (stiffness as h^2 kappa_c)
 template <typename T>
-__device__ __forceinline__ void push_end(const View<T>& v, int owner, int sc, int partner,
-                                         int feature, int side, const double* xs,
-                                         const double* xo, const double* n, double kap,
-                                         double mu) {
+__device__ __forceinline__ void put_end(const View<T>& v, int owner, int slot, int sc, int partner,
+                                        int feature, int side, const double* xs,
+                                        const double* xo, const double* n, double kap,
+                                        double mu) {
   const SceneDev& S = v.scenes[sc];
-  const int slot = atomicAdd(v.ccount + owner, 1);
   if (slot >= S.ccap) {
     atomicOr(v.health + sc, 2);
     return;
@@ -356,18 +356,46 @@ __device__ __forceinline__ void push_end(const View<T>& v, int owner, int sc, in
           ((unsigned long long)(unsigned)feature << 1) | (unsigned)side;
 }
 
+// both ends of a contact between i and j (j = -1: a plane), into slots si and sj
+template <typename T>
+__device__ __forceinline__ void put_contact(const View<T>& v, const ContactBuf& cb, int sc,
+                                            int i, int si, int j, int sj, int feature, const double* xi,
+                                            const double* xj, const double* n) {
+  const SceneDev& S = v.scenes[sc];
+  double m = fmax(free_mass(v, cb, i), free_mass(v, cb, j));
+  double kap = S.kscale * m;  // h^2 kappa_c, kappa_c = scale m / h^2
+  put_end(v, i, si, sc, j, feature, 0, xi, xj, n, kap, S.mu);
+  if (j >= 0) {
+    double nn[3] = {-n[0], -n[1], -n[2]};
+    put_end(v, j, sj, sc, i, feature, 1, xj, xi, nn, kap, S.mu);
+  }
+}
+
+// one contact of a lane by itself
 template <typename T>
 __device__ __forceinline__ void emit_contact(const View<T>& v, const ContactBuf& cb, int sc,
                                              int i, int j, int feature, const double* xi,
                                              const double* xj, const double* n) {
-  const SceneDev& S = v.scenes[sc];
-  double m = fmax(free_mass(v, cb, i), free_mass(v, cb, j));
-  double kap = S.kscale * m;  // h^2 kappa_c, kappa_c = scale m / h^2
-  push_end(v, i, sc, j, feature, 0, xi, xj, n, kap, S.mu);
-  if (j >= 0) {
-    double nn[3] = {-n[0], -n[1], -n[2]};
-    push_end(v, j, sc, i, feature, 1, xj, xi, nn, kap, S.mu);
-  }
+  const int si = atomicAdd(v.ccount + i, 1);
+  const int sj = j >= 0 ? atomicAdd(v.ccount + j, 1) : 0;
+  put_contact(v, cb, sc, i, si, j, sj, feature, xi, xj, n);
+}
+
+// The contacts of eight consecutive lanes with the same bodies i and j, those of
+// the lanes with `hit`: their slots come from one atomic per body, whose wait the
+// lanes share.
+template <typename T>
+__device__ __forceinline__ void emit_eight(const View<T>& v, const ContactBuf& cb, bool hit, int sc, int i, int j,
+                                           int feature, const double* xi, const double* xj, const double* n) {
+  const int lane = __lane_id(), first = lane & ~7;
+  const unsigned mask = (unsigned)(__ballot(hit) >> first) & 0xffu;
+  if (!mask) return;
+  int base = 0;
+  if (lane == first) base = atomicAdd(v.ccount + i, __popc(mask));
+  if (lane == first + 1 && j >= 0) base = atomicAdd(v.ccount + j, __popc(mask));
+  const int rank = __popc(mask & ((1u << (lane & 7)) - 1u));
+  const int si = __shfl(base, first) + rank, sj = __shfl(base, first + 1) + rank;
+  if (hit) put_contact(v, cb, sc, i, si, j, sj, feature, xi, xj, n);
 }
 
 template <typename T>
@@ -398,38 +426,59 @@ __device__ __forceinline__ double pick3(const double* a, int k) {
   return k == 0 ? a[0] : (k == 1 ? a[1] : a[2]);
 }
 
+// x of lane J = 0 .. 7 away by xor within eight lanes (1, 2, or mirrored)
+template <int STEP, typename U>
+__device__ __forceinline__ U eight_other(U x) {
+  return lane_of<STEP == 1 ? 0xB1 : (STEP == 2 ? 0x4E : 0x141)>(x);
+}
+
 // box-box, vertex-face: reference face = face axis (3 of i, then 3 of j) of least
 // overlap; incident vertices within the margin of that face and inside its
 // lateral extent become contacts (incident box = i side, reference box = j side).
-// All loops are unrolled and run-time choices are selects, so the geometry stays
-// in registers.
+// Eight lanes share a pair: each forms the overlap along one axis (the last two
+// repeat others), then one vertex.  Run-time choices are selects, so the geometry
+// stays in registers; sums of products are fused in one order.
 template <typename T>
 __device__ __forceinline__ void narrow_box_box(const View<T>& v, const ContactBuf& cb, int sc, int bi,
                                                int bj, const BodyGeo<T>& gi, const BodyGeo<T>& gj,
                                                double pm) {
+  const int l = __lane_id() & 7;
   const double dc[3] = {gj.c[0] - gi.c[0], gj.c[1] - gi.c[1], gj.c[2] - gi.c[2]};
-  int best = -1;
-  double best_ov = 0.0;
-  bool apart = false;
+  int best = l < 6 ? l : l - 3;
+  {
+    const bool of_i = best < 3;
+    const int k = best % 3;
+    double u[3];
 #pragma unroll
-  for (int ax = 0; ax < 6; ++ax) {
-    const double* A = ax < 3 ? gi.A : gj.A;
-    const int k = ax % 3;
-    const double u[3] = {A[k], A[3 + k], A[6 + k]};
-    double ri = 0.0, rj = 0.0;
+    for (int r = 0; r < 3; ++r) u[r] = of_i ? pick3(gi.A + 3 * r, k) : pick3(gj.A + 3 * r, k);
+    double wi[3], wj[3];
 #pragma unroll
     for (int m = 0; m < 3; ++m) {
-      ri += gi.he[m] * fabs(u[0] * gi.A[m] + u[1] * gi.A[3 + m] + u[2] * gi.A[6 + m]);
-      rj += gj.he[m] * fabs(u[0] * gj.A[m] + u[1] * gj.A[3 + m] + u[2] * gj.A[6 + m]);
+      const double ci[3] = {gi.A[m], gi.A[3 + m], gi.A[6 + m]}, cj[3] = {gj.A[m], gj.A[3 + m], gj.A[6 + m]};
+      wi[m] = fabs(dot_fused(u, ci));
+      wj[m] = fabs(dot_fused(u, cj));
     }
-    const double ov = ri + rj - fabs(u[0] * dc[0] + u[1] * dc[1] + u[2] * dc[2]);
-    if (ov < -pm) apart = true;
-    if (best < 0 || ov < best_ov) {
-      best = ax;
-      best_ov = ov;
-    }
+    const double ri = fma(gi.he[2], wi[2], fma(gi.he[1], wi[1], gi.he[0] * wi[0]));
+    const double rj = fma(gj.he[2], wj[2], fma(gj.he[1], wj[1], gj.he[0] * wj[0]));
+    double best_ov = ri + rj - fabs(dot_fused(u, dc));
+    // apart along some axis; the first axis of least overlap.  The lanes must agree
+    // on it: an overlap that is not a number counts as the least on the first axis,
+    // as the largest on the others.
+    int apart = best_ov < -pm ? 1 : 0;
+    if (best_ov != best_ov) best_ov = best == 0 ? -__builtin_huge_val() : __builtin_huge_val();
+    auto less = [&](auto other) {
+      const double o = other(best_ov);
+      const int b = other(best);
+      apart |= other(apart);
+      const bool take = o < best_ov || (o == best_ov && b < best);
+      best_ov = take ? o : best_ov;
+      best = take ? b : best;
+    };
+    less([](auto x) { return eight_other<1>(x); });
+    less([](auto x) { return eight_other<2>(x); });
+    less([](auto x) { return eight_other<4>(x); });
+    if (apart) return;  // the same in all eight
   }
-  if (apart) return;
   const bool ref_is_i = best < 3;
   const int k = best % 3;
   double RA[9], IA[9], Rc[3], Ic[3], Rhe[3], Ihe[3];
@@ -447,31 +496,27 @@ __device__ __forceinline__ void narrow_box_box(const View<T>& v, const ContactBu
   }
   const int ref = ref_is_i ? bi : bj, inc = ref_is_i ? bj : bi;
   const double ax[3] = {pick3(RA, k), pick3(RA + 3, k), pick3(RA + 6, k)};
-  const double tw = ax[0] * (Ic[0] - Rc[0]) + ax[1] * (Ic[1] - Rc[1]) + ax[2] * (Ic[2] - Rc[2]);
-  const double sgn = tw >= 0.0 ? 1.0 : -1.0;
+  const double ic[3] = {Ic[0] - Rc[0], Ic[1] - Rc[1], Ic[2] - Rc[2]};
+  const double sgn = dot_fused(ax, ic) >= 0.0 ? 1.0 : -1.0;
   const double nw[3] = {sgn * ax[0], sgn * ax[1], sgn * ax[2]};
   const double hek = pick3(Rhe, k);
+  double xv[3], rel[3], pl[3], xs[3];
+  vertex_of(l, Ihe, xv);
 #pragma unroll
-  for (int vtx = 0; vtx < 8; ++vtx) {
-    double xv[3], p[3], rel[3], pl[3];
-    vertex_of(vtx, Ihe, xv);
-    mat_vec(IA, xv, p);
+  for (int r = 0; r < 3; ++r) rel[r] = dot_fused(IA + 3 * r, xv) + Ic[r] - Rc[r];
 #pragma unroll
-    for (int r = 0; r < 3; ++r) rel[r] = p[r] + Ic[r] - Rc[r];
-    mat_tvec(RA, rel, pl);
-    const double gap = sgn * pick3(pl, k) - hek;
-    if (!(gap < pm) || gap < -2.0 * hek) continue;
-    bool lateral = true;
-#pragma unroll
-    for (int m = 0; m < 3; ++m)
-      if (m != k && fabs(pl[m]) > Rhe[m] + pm) lateral = false;
-    if (!lateral) continue;
-    double xs[3];
-#pragma unroll
-    for (int m = 0; m < 3; ++m)
-      xs[m] = m == k ? sgn * Rhe[m] : (pl[m] < -Rhe[m] ? -Rhe[m] : (pl[m] > Rhe[m] ? Rhe[m] : pl[m]));
-    emit_contact(v, cb, sc, inc, ref, vtx, xv, xs, nw);
+  for (int m = 0; m < 3; ++m) {
+    const double col[3] = {RA[m], RA[3 + m], RA[6 + m]};
+    pl[m] = dot_fused(col, rel);
   }
+  const double gap = sgn * pick3(pl, k) - hek;
+  bool hit = gap < pm && !(gap < -2.0 * hek);
+#pragma unroll
+  for (int m = 0; m < 3; ++m) {
+    if (m != k && fabs(pl[m]) > Rhe[m] + pm) hit = false;
+    xs[m] = m == k ? sgn * Rhe[m] : (pl[m] < -Rhe[m] ? -Rhe[m] : (pl[m] > Rhe[m] ? Rhe[m] : pl[m]));
+  }
+  emit_eight(v, cb, hit, sc, inc, ref, l, xv, xs, nw);
 }
 
 // sphere s (i side) against box b (j side)
@@ -522,21 +567,12 @@ __device__ __forceinline__ void narrow_sphere_box(const View<T>& v, const Contac
   emit_contact(v, cb, sc, s, b, 8, xi, q, nw);
 }
 
+// a pair with a sphere, whose bounding test has passed: one lane
 template <typename T>
-__device__ __forceinline__ void narrow_pair(const View<T>& v, const ContactBuf& cb, int sc, int i, int j,
-                            const BodyGeo<T>& gi, double pmi) {
-  BodyGeo<T> gj;
-  body_geo(v, j, gj);
-  T vw[VW];
-  load<T, VW>(v.vel + (size_t)VW * j, vw);
-  const double vd[6] = {(double)vw[0], (double)vw[1], (double)vw[2], (double)vw[3], (double)vw[4], (double)vw[5]};
-  const double pm = pmi + body_pm(v.scenes[sc], vd, gj.R, gj.shape);
-  const double dc[3] = {gj.c[0] - gi.c[0], gj.c[1] - gi.c[1], gj.c[2] - gi.c[2]};
-  const double dist = sqrt(dc[0] * dc[0] + dc[1] * dc[1] + dc[2] * dc[2]);
-  if (!(dist < gi.R + gj.R + pm)) return;
-  if (gi.shape == 0 && gj.shape == 0) {
-    narrow_box_box(v, cb, sc, i, j, gi, gj, pm);
-  } else if (gi.shape == 1 && gj.shape == 1) {
+__device__ __forceinline__ void narrow_sphere(const View<T>& v, const ContactBuf& cb, int sc, int i, int j,
+                                              const BodyGeo<T>& gi, const BodyGeo<T>& gj, const double* dc, double dist,
+                                              double pm) {
+  if (gi.shape == 1 && gj.shape == 1) {
     const double gap = dist - gi.he[0] - gj.he[0];
     if (!(gap < pm) || dist == 0.0) return;
     const double n[3] = {-dc[0] / dist, -dc[1] / dist, -dc[2] / dist};
@@ -621,35 +657,34 @@ __device__ __forceinline__ bool pair_allowed(bool pin_i, int group_i, unsigned f
   return true;
 }
 
+// contacts of body i with the scene's planes, by eight lanes: a vertex each of a
+// box, the first lane for a sphere
 template <typename T>
 __device__ void plane_contacts(const View<T>& v, const ContactBuf& cb, int sc, int i,
                                const BodyGeo<T>& gi, double pmi) {
   const SceneDev& S = v.scenes[sc];
+  const int l = __lane_id() & 7;
+  double x[3], y[3];
+  vertex_of(l, gi.he, x);
+#pragma unroll
+  for (int r = 0; r < 3; ++r) y[r] = dot_fused(gi.A + 3 * r, x) + gi.c[r];
   for (int p = 0; p < S.n_planes; ++p) {
     const double* pl = v.planes + 4 * (size_t)(S.plane_off + p);
     const double n[3] = {pl[0], pl[1], pl[2]};
     if (gi.shape == 0) {
-      for (int k = 0; k < 8; ++k) {
-        double x[3], y[3];
-        vertex_of(k, gi.he, x);
-        mat_vec(gi.A, x, y);
-        for (int r = 0; r < 3; ++r) y[r] += gi.c[r];
-        const double gap = n[0] * y[0] + n[1] * y[1] + n[2] * y[2] - pl[3];
-        if (gap < pmi) {
-          const double xw[3] = {y[0] - gap * n[0], y[1] - gap * n[1], y[2] - gap * n[2]};
-          emit_contact(v, cb, sc, i, -1, 16 * p + k, x, xw, n);
-        }
-      }
-    } else {
+      const double gap = dot_fused(n, y) - pl[3];
+      const double xw[3] = {fma(-gap, n[0], y[0]), fma(-gap, n[1], y[1]), fma(-gap, n[2], y[2])};
+      emit_eight(v, cb, gap < pmi, sc, i, -1, 16 * p + l, x, xw, n);
+    } else if (l == 0) {
       const double r = gi.he[0];
       const double gap = n[0] * gi.c[0] + n[1] * gi.c[1] + n[2] * gi.c[2] - r - pl[3];
       if (gap < pmi) {
         const double pw[3] = {-r * n[0], -r * n[1], -r * n[2]};
-        double x[3];
-        mat_tvec(gi.A, pw, x);
+        double xs[3];
+        mat_tvec(gi.A, pw, xs);
         const double xw[3] = {gi.c[0] - (r + gap) * n[0], gi.c[1] - (r + gap) * n[1],
                               gi.c[2] - (r + gap) * n[2]};
-        emit_contact(v, cb, sc, i, -1, 16 * p + 8, x, xw, n);
+        emit_contact(v, cb, sc, i, -1, 16 * p + 8, xs, xw, n);
       }
     }
   }
@@ -663,8 +698,17 @@ __device__ __forceinline__ double own_pm(const View<T>& v, int i, int sc, const 
   return body_pm(v.scenes[sc], vd, g.R, g.shape);
 }
 
-// BLPB lanes per body: the first lane does the plane contacts; then, for a
-// small body, the lanes split the 14 cells made of its own cell (partners of
+// plane contacts of the body of these eight lanes, when it can have any
+template <typename T>
+__device__ __forceinline__ void plane_body(const View<T>& v, const ContactBuf& cb, int i) {
+  const int sc = v.bscene[i];
+  if (!contact_body(v, i, sc) || (v.flags[i] & F_PINNED) || v.scenes[sc].n_planes <= 0) return;
+  BodyGeo<T> gi;
+  body_geo(v, i, gi);
+  plane_contacts(v, cb, sc, i, gi, own_pm(v, i, sc, gi));
+}
+
+// BLPB lanes per body: for a small body, the lanes split the 14 cells made of its own cell (partners of
 // higher index) and the 13 cells of the forward half of its neighbourhood, so
 // each pair of neighbouring cells is searched from one side only.  One cell per
 // lane: each lane's loads form one short dependent chain (bucket range, then
@@ -686,11 +730,6 @@ __global__ void __launch_bounds__(256) k_broad_small(View<T> v, ContactBuf cb) {
   if (i < v.n && contact_body(v, i, sc)) {
     const SceneDev& S = v.scenes[sc];
     const bool pin_i = (v.flags[i] & F_PINNED) != 0;
-    if (sub == 0 && !pin_i && S.n_planes > 0) {
-      BodyGeo<T> gi;
-      body_geo(v, i, gi);
-      plane_contacts(v, cb, sc, i, gi, own_pm(v, i, sc, gi));
-    }
     if (!is_large(v, cb, i, sc)) {
       double c[3];
       int cc[3];
@@ -860,60 +899,144 @@ __global__ void __launch_bounds__(BL_CHUNK) k_broad_large(View<T> v, ContactBuf 
   flush_pairs(pb, v, cb);
 }
 
-// A single scene of few bodies, [first, first + n): every pair tested directly,
-// one thread per pair, and one thread per body for its plane contacts.  The
-// candidate rule is the broad kernels' (bounding spheres of reach R + pm, the
-// same filters), so the pairs proposed are the same; only the spatial hash and
-// its eight launches are gone.  The narrow phase repeats the exact test and the
-// sort fixes the order, so the contact set and its order do not depend on which
-// broad phase found the pairs.
+// A single scene of few bodies, [first, first + n): its whole contact search in one
+// launch.  A workgroup takes a pair of tiles of BRUTE_TILE bodies, whose geometry,
+// margins and reaches it forms once in LDS; it tests the pairs of bounding spheres
+// and runs the narrow phase on those that are near, eight lanes per pair.  The
+// workgroups past the last tile pair do the planes.  The candidate rule is the hash
+// path's, and the sort fixes the order, so the contacts do not depend on which of
+// the two found them.  A chain of latencies bounds it, not work: reaches, pairs
+// (one thread each) and narrow phase (one thread per pair) in three launches with
+// the pair list in memory took 4.4 + 8.4 + 15 us on 200 boxes; this takes 9 to 15.
+// Tiles of 16 are level on 200 boxes and lose 3% of a step on 731, 8% on 2,040.
+constexpr int BRUTE_TILE = 32;
+
 template <typename T>
-__global__ void __launch_bounds__(256) k_broad_brute(View<T> v, ContactBuf cb, int first, int n) {
-  __shared__ int2 lbuf[PAIR_LDS];
-  __shared__ int lcount, lbase;
-  if (threadIdx.x == 0) lcount = 0;
-  __syncthreads();
-  const PairBuf pb{lbuf, &lcount, &lbase};
-  const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  const long long npairs = (long long)n * (n - 1) / 2;
-  if (t < n) {
-    const int i = first + (int)t;
-    const int sc = v.bscene[i];
-    if (contact_body(v, i, sc) && !(v.flags[i] & F_PINNED) && v.scenes[sc].n_planes > 0) {
-      BodyGeo<T> gi;
-      body_geo(v, i, gi);
-      plane_contacts(v, cb, sc, i, gi, own_pm(v, i, sc, gi));
-    }
-  } else if (t < n + npairs) {
-    // pair p = b (b - 1) / 2 + a with 0 <= a < b < n
-    const long long p = t - n;
-    long long b = (long long)((1.0 + sqrt(1.0 + 8.0 * (double)p)) * 0.5);
-    while (b * (b - 1) / 2 > p) --b;
-    while ((b + 1) * b / 2 <= p) ++b;
-    const int i = first + (int)(p - b * (b - 1) / 2), j = first + (int)b;
-    const int sc = v.bscene[i];
-    if (sc == v.bscene[j] && contact_body(v, i, sc) && contact_body(v, j, sc) &&
-        pair_allowed((v.flags[i] & F_PINNED) != 0, v.group[i], v.flags[j], v.group[j])) {
-      double ci[3], cj[3];
-      centre_of(v, i, ci);
-      centre_of(v, j, cj);
-      if (spheres_near(ci, cb.breach[i], cj, cb.breach[j])) append_pair(pb, cb, v.health, sc, i, j);
+__global__ void __launch_bounds__(256) k_contacts_brute(View<T> v, ContactBuf cb, int first, int n, int tile_pairs) {
+  constexpr int BT = BRUTE_TILE;
+  __shared__ BodyGeo<T> geo[2 * BT];
+  __shared__ double pm[2 * BT], reach[2 * BT];
+  __shared__ int group[2 * BT], flags[2 * BT];
+  __shared__ unsigned short near[BT * BT];
+  __shared__ int count;
+  const int t = threadIdx.x;
+  if ((int)blockIdx.x >= tile_pairs) {
+    const int k = (((int)blockIdx.x - tile_pairs) * 256 + t) / 8;
+    if (k < n) plane_body(v, cb, first + k);
+    return;
+  }
+  // tiles (ta, tb), ta <= tb, of tile pair tb (tb + 1) / 2 + ta
+  const int p = blockIdx.x;
+  int tb = (int)((sqrtf(1.0f + 8.0f * (float)p) - 1.0f) * 0.5f);
+  while (tb * (tb + 1) / 2 > p) --tb;
+  while ((tb + 1) * (tb + 2) / 2 <= p) ++tb;
+  const int ta = p - tb * (tb + 1) / 2;
+  const int a0 = first + ta * BT, b0 = first + tb * BT;
+  if (t == 0) count = 0;
+  if (t < 2 * BT) {
+    const int i = (t < BT ? a0 : b0 - BT) + t;
+    flags[t] = F_NOCONTACT;
+    if (i < first + n) {
+      const int sc = v.bscene[i];
+      if (contact_body(v, i, sc)) {
+        BodyGeo<T> g;
+        body_geo(v, i, g);
+        const double m = own_pm(v, i, sc, g);
+        geo[t] = g;
+        pm[t] = m;
+        reach[t] = g.R + m;
+        group[t] = v.group[i];
+        flags[t] = v.flags[i];
+      }
     }
   }
-  flush_pairs(pb, v, cb);
+  __syncthreads();
+  const int a = t % BT;
+  for (int b = BT + t / BT; b < 2 * BT; b += 256 / BT) {
+    if (ta == tb && a >= b - BT) continue;
+    if ((flags[a] & F_NOCONTACT) ||
+        !pair_allowed((flags[a] & F_PINNED) != 0, group[a], (unsigned)flags[b], group[b]))
+      continue;
+    if (spheres_near(geo[a].c, reach[a], geo[b].c, reach[b])) near[atomicAdd(&count, 1)] = (unsigned short)(a | b << 8);
+  }
+  __syncthreads();
+  const int found = count;
+  // the list in memory is not needed, its limit still holds
+  if (t == 0 && found > 0 && atomicAdd(cb.counters + 1, found) > cb.pcap - found)
+    atomicOr(v.health + v.bscene[a0], 2);
+  for (int g = t / 8; g < found; g += 32) {
+    const int la = near[g] & 255, lb = near[g] >> 8;
+    const int i = a0 + la, j = b0 + lb - BT;
+    const BodyGeo<T> gi = geo[la], gj = geo[lb];
+    const double pmp = pm[la] + pm[lb];
+    const double dc[3] = {gj.c[0] - gi.c[0], gj.c[1] - gi.c[1], gj.c[2] - gi.c[2]};
+    const double dist = sqrt(dc[0] * dc[0] + dc[1] * dc[1] + dc[2] * dc[2]);
+    if (!(dist < gi.R + gj.R + pmp)) continue;
+    if (gi.shape == 0 && gj.shape == 0)
+      narrow_box_box(v, cb, v.bscene[i], i, j, gi, gj, pmp);
+    else if (t % 8 == 0)
+      narrow_sphere(v, cb, v.bscene[i], i, j, gi, gj, dc, dist, pmp);
+  }
 }
 
-// one thread per candidate pair (grid-stride)
+// Candidate pairs, 64 per wave and round (grid-stride).  Every lane runs the exact
+// bounding test of its own pair and, where a sphere is in it, its contact; the
+// pairs of boxes that pass are lined up in LDS and taken eight at a time, eight
+// lanes each.  One lane per pair of boxes walked six axes and eight vertices in a
+// row, with two atomics per contact, in 204 registers.  The workgroups past the
+// first `pair_blocks` do the contacts with planes.
 template <typename T>
-__global__ void __launch_bounds__(256) k_narrow_pairs(View<T> v, ContactBuf cb) {
+__global__ void __launch_bounds__(256) k_narrow_pairs(View<T> v, ContactBuf cb, int pair_blocks) {
+  if ((int)blockIdx.x >= pair_blocks) {
+    const long long k = ((long long)((int)blockIdx.x - pair_blocks) * 256 + threadIdx.x) / 8;
+    if (k < v.n) plane_body(v, cb, (int)k);
+    return;
+  }
+  struct Near {
+    double pm;
+    int i, j;
+  };
+  __shared__ Near queue[4][64];
   const int np = min(cb.counters[1], cb.pcap);
-  for (int p = blockIdx.x * blockDim.x + threadIdx.x; p < np; p += gridDim.x * blockDim.x) {
-    const int2 pr = cb.pairs[p];
-    const int i = pr.x, j = pr.y;
-    const int sc = v.bscene[i];
-    BodyGeo<T> gi;
-    body_geo(v, i, gi);
-    narrow_pair(v, cb, sc, i, j, gi, own_pm(v, i, sc, gi));
+  const int lane = threadIdx.x & 63;
+  Near* q = queue[threadIdx.x / 64];
+  const int stride = pair_blocks * 256;
+  for (int p0 = blockIdx.x * blockDim.x + (threadIdx.x & ~63); p0 < np; p0 += stride) {
+    const int p = p0 + lane;
+    bool boxes = false;
+    Near mine{};
+    if (p < np) {
+      const int2 pr = cb.pairs[p];
+      mine.i = pr.x;
+      mine.j = pr.y;
+      const int sc = v.bscene[pr.x];
+      BodyGeo<T> gi, gj;
+      body_geo(v, pr.x, gi);
+      body_geo(v, pr.y, gj);
+      mine.pm = own_pm(v, pr.x, sc, gi) + own_pm(v, pr.y, sc, gj);
+      const double dc[3] = {gj.c[0] - gi.c[0], gj.c[1] - gi.c[1], gj.c[2] - gi.c[2]};
+      const double dist = sqrt(dc[0] * dc[0] + dc[1] * dc[1] + dc[2] * dc[2]);
+      if (dist < gi.R + gj.R + mine.pm) {
+        if (gi.shape == 0 && gj.shape == 0)
+          boxes = true;
+        else
+          narrow_sphere(v, cb, sc, pr.x, pr.y, gi, gj, dc, dist, mine.pm);
+      }
+    }
+    const unsigned long long near = __ballot(boxes);
+    if (boxes) q[__popcll(near & ((1ull << lane) - 1ull))] = mine;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const int nn = __popcll(near);
+    for (int g = lane / 8; g < nn; g += 8) {
+      const Near m = q[g];
+      BodyGeo<T> gi, gj;
+      body_geo(v, m.i, gi);
+      body_geo(v, m.j, gj);
+      narrow_box_box(v, cb, v.bscene[m.i], m.i, m.j, gi, gj, m.pm);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
   }
 }
 

@@ -1,0 +1,57 @@
+"""The two contact searches: all pairs of tiles of 32 bodies in one launch for a
+small plain scene, and the spatial hash for the scenes of a batch.  Both find the
+oracle's contacts, and the states after them agree bit by bit."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2609_02675_amd import scenes as S
+from test_gpu_contact import _compare_contacts
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def P():
+    import paper_2609_02675_amd as P
+    if P.device_count() < 1:
+        pytest.fail("no HIP device visible")
+    return P
+
+
+def _mixed(n, prec):
+    """n touching bodies near the ground: boxes and every third a sphere, some
+    pinned, some of one group, one without contacts."""
+    rng = np.random.Generator(np.random.PCG64(n))
+    side = max(1, round(n ** (1 / 3)))
+    sc = S.box_drop(side, layers=-(-n // side ** 2), seed=n, spacing=1.2, base_height=-0.7, precision=prec)
+    k = np.arange(n)
+    sc = sc.copy(**{f: getattr(sc, f)[k] for f in ("shape", "shape_param", "density", "flags", "group", "c0", "A0",
+                                                   "v0")}, w0=rng.uniform(-1, 1, (n, 3)))
+    sc.shape[k % 3 == 1] = S.SHAPE_SPHERE
+    sc.shape_param[k % 3 == 1] = [0.45, 0.0, 0.0]
+    sc.group[k % 5 == 0] = 7
+    sc.flags[k % 7 == 6] |= S.FLAG_PINNED
+    sc.flags[n // 2] |= S.FLAG_NO_CONTACT
+    return sc
+
+
+@pytest.mark.parametrize("n", [9, 31, 32, 33, 64, 65, 130])
+def test_both_searches_find_the_oracles_contacts(P, n):
+    sc = _mixed(n, S.PREC_FP64)
+    print(f"[case] contact search n={n}", flush=True)
+    g = P.Scene(sc)
+    g.step(1)
+    o = oracle.Oracle(sc)
+    o.step(1)
+    _compare_contacts(g, o)
+    for prec in (S.PREC_FP32, S.PREC_FP64):
+        sc = _mixed(n, prec)
+        g = P.Scene(sc)
+        g.step(2)
+        b = P.Batch(4, 1 << 28, prec)
+        slots = [b.admit(sc, 2), b.admit(_mixed(20, prec), 2)]
+        b.step()
+        b.step()
+        for p, q in zip(g.state(), b.state(slots[0])):
+            assert np.array_equal(p, q)
