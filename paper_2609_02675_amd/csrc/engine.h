@@ -523,10 +523,20 @@ struct Engine {
   // whose rows need more than the 128 registers that 1,024 leave (chain of 200, us
   // per step: FP32 27 with one lane per body, 20 with quads).
   static constexpr int ROWS_MAX = sizeof(T) == 4 ? 256 : 128;
+  // Scenes with variable or driven bonds up to this many quads, ends and driven
+  // bonds take a quad of lanes per body to add the ends and solve (k_resident_ends),
+  // larger ones one lane per body (k_resident_net): up to four waves each have a
+  // SIMD to themselves, beyond them the four inversions of a quad queue (us per step:
+  // 11 x 11 net of order 6 in FP64 88 with quads, 70 without; 16 x 16 in FP32 123
+  // and 69).  Quadratic bonds alone stay in one phase (8 x 8 net 21 us, two phases
+  // 26; 16 x 16 34 and 50).
+  static constexpr int QUADS_MAX = 256;
   // nsteps steps of the plain scene in the resident kernels, after a contact scene's
-  // contact construction (then nsteps is 1); general: it has variable bonds
-  void launch_resident(bool contact, bool general, int n_driven, int ccap, int nsteps, hipStream_t st) {
-    if (!contact && !general && n_driven == 0 && cap.n <= ROWS_MAX) {
+  // contact construction (then nsteps is 1); general: it has variable bonds; n_ends: its
+  // static bond ends
+  void launch_resident(bool contact, bool general, int n_ends, int n_driven, int ccap, int nsteps, hipStream_t st) {
+    const bool any_kind = general || n_driven > 0;
+    if (!contact && !any_kind && cap.n <= ROWS_MAX) {
       const View<T> v = view();
       if (cap.n <= 16)
         hipLaunchKernelGGL((k_resident_rows<T, 64>), dim3(1), dim3(64), 0, st, v, cap.n, nsteps);
@@ -538,34 +548,62 @@ struct Engine {
         hipLaunchKernelGGL((k_resident_rows<T, 1024>), dim3(1), dim3(1024), 0, st, v, cap.n, nsteps);
       return;
     }
-    const int lanes = cap.n * (contact ? 4 : 1);
-    if (lanes <= 64)
-      launch_resident_as<64>(contact, general, n_driven, ccap, nsteps, st);
-    else if (lanes <= 256)
-      launch_resident_as<256>(contact, general, n_driven, ccap, nsteps, st);
-    else if (lanes <= 512)
-      launch_resident_as<512>(contact, general, n_driven, ccap, nsteps, st);
+    if (!contact && any_kind) {
+      const int quads = std::max({4 * cap.n, n_ends, n_driven});
+      if (quads <= 64)
+        launch_ends_as<64>(general, n_ends, n_driven, nsteps, st);
+      else if (quads <= QUADS_MAX)
+        launch_ends_as<QUADS_MAX>(general, n_ends, n_driven, nsteps, st);
+      else if (cap.n <= 512)
+        launch_net_as<512>(general, n_ends, n_driven, nsteps, st);
+      else
+        launch_net_as<Resident<T>::NT>(general, n_ends, n_driven, nsteps, st);
+      return;
+    }
+    if (contact) {
+      if (cap.n <= 16)
+        launch_contact_as<64>(any_kind, n_driven, ccap, st);
+      else
+        launch_contact_as<256>(any_kind, n_driven, ccap, st);
+      return;
+    }
+    if (cap.n <= 256)
+      launch_joints_as<256>(nsteps, st);
+    else if (cap.n <= 512)
+      launch_joints_as<512>(nsteps, st);
     else
-      launch_resident_as<Resident<T>::NT>(contact, general, n_driven, ccap, nsteps, st);
+      launch_joints_as<Resident<T>::NT>(nsteps, st);
   }
   template <int NT>
-  void launch_resident_as(bool contact, bool general, int n_driven, int ccap, int nsteps, hipStream_t st) {
+  void launch_ends_as(bool variable, int n_ends, int n_driven, int nsteps, hipStream_t st) {
     const View<T> v = view();
     const DrivenTable dt{n_driven, drv_scene, drv_end_i, drv_end_j, drv_param, mass64};
-    const bool g = general || n_driven > 0;
-    if constexpr (NT <= 256) {
-      if (contact) {
-        if (g)
-          hipLaunchKernelGGL((k_resident_contact<T, NT, true>), dim3(1), dim3(NT), 0, st, v, cap.n, ccap, dt);
-        else
-          hipLaunchKernelGGL((k_resident_contact<T, NT, false>), dim3(1), dim3(NT), 0, st, v, cap.n, ccap, dt);
-        return;
-      }
-    }
-    if (g)
-      hipLaunchKernelGGL((k_resident_joints<T, NT, true>), dim3(1), dim3(NT), 0, st, v, cap.n, nsteps, dt);
+    if (variable)
+      hipLaunchKernelGGL((k_resident_ends<T, NT, true>), dim3(1), dim3(NT), 0, st, v, cap.n, n_ends, nsteps, dt);
     else
-      hipLaunchKernelGGL((k_resident_joints<T, NT, false>), dim3(1), dim3(NT), 0, st, v, cap.n, nsteps, dt);
+      hipLaunchKernelGGL((k_resident_ends<T, NT, false>), dim3(1), dim3(NT), 0, st, v, cap.n, n_ends, nsteps, dt);
+  }
+  template <int NT>
+  void launch_net_as(bool variable, int n_ends, int n_driven, int nsteps, hipStream_t st) {
+    const View<T> v = view();
+    const DrivenTable dt{n_driven, drv_scene, drv_end_i, drv_end_j, drv_param, mass64};
+    if (variable)
+      hipLaunchKernelGGL((k_resident_net<T, NT, true>), dim3(1), dim3(NT), 0, st, v, cap.n, n_ends, nsteps, dt);
+    else
+      hipLaunchKernelGGL((k_resident_net<T, NT, false>), dim3(1), dim3(NT), 0, st, v, cap.n, n_ends, nsteps, dt);
+  }
+  template <int NT>
+  void launch_contact_as(bool any_kind, int n_driven, int ccap, hipStream_t st) {
+    const View<T> v = view();
+    const DrivenTable dt{n_driven, drv_scene, drv_end_i, drv_end_j, drv_param, mass64};
+    if (any_kind)
+      hipLaunchKernelGGL((k_resident_contact<T, NT, true>), dim3(1), dim3(NT), 0, st, v, cap.n, ccap, dt);
+    else
+      hipLaunchKernelGGL((k_resident_contact<T, NT, false>), dim3(1), dim3(NT), 0, st, v, cap.n, ccap, dt);
+  }
+  template <int NT>
+  void launch_joints_as(int nsteps, hipStream_t st) {
+    hipLaunchKernelGGL((k_resident_joints<T, NT>), dim3(1), dim3(NT), 0, st, view(), cap.n, nsteps);
   }
 
   // FP64 block factorisation of bodies [first, first + count)

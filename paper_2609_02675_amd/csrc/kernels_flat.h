@@ -67,13 +67,16 @@ __device__ __forceinline__ void polynomial_sums(T l, T dn, T* w_out, T* phim_out
       phim -= (T)binom * (k >= 1 ? dk1 * dn : (T)1) * lp[j];
     }
     if (k >= 1) dk1 *= dn;
+    settle<1>(&dk1);
   }
   *w_out = w;
   *phim_out = phim;
 }
 template <typename T>
 __device__ __forceinline__ T polynomial_end(const T* a, const T* d, T h2, T* f) {
-  const T kap = a[0], l = a[2];
+  const T kap = a[0];
+  T l = a[2];
+  settle<1>(&l);  // no power of it taken ahead of a caller's loop
   const T dn = sqrt(dot_fused(d, d));
   T w = (T)0, phim = (T)0;
   switch ((int)(-a[3])) {
@@ -206,15 +209,20 @@ __device__ __forceinline__ void quadratic_ends(const View<T>& v, int e, int e1, 
   }
 }
 
-// one static end of any kind, record E and, for a body with variable ends, its
-// state a (else zeros), partner j (-1: the world) at qj.  Ends whose weight or
-// point moves add to dB, the change of the block, and set refactor; an augmented
-// end's multiplier and stiffness move on in a, a slider's anchor, in the step's
-// last iteration, in E[7].
+// the terms of one static end of any kind, record E and, for a body with variable
+// ends, its state a (else zeros), partner j (-1: the world) at qj: the force g f, the
+// own point x it acts at and, for an end whose weight or point moves (then true is
+// returned), its weight w in the block.  An augmented end's multiplier and
+// stiffness move on in a, a slider's anchor, in the step's last iteration, in E[7].
 template <typename T>
-__device__ __forceinline__ void general_end(T* E, T* a, int j, const T* q, const T* qj, const SceneDev& S, bool last,
-                                            T* rb, Block& dB, bool& refactor) {
+__device__ __forceinline__ bool end_terms(T* E, T* a, int j, const T* q, const T* qj, T h2, T beta, bool last, T* f,
+                                          T* g, T* x, T* w) {
   const T kind = a[3];
+  x[0] = E[0];
+  x[1] = E[1];
+  x[2] = E[2];
+  *w = (T)0;
+  *g = (T)1;
   // a slider end's line anchor sits t0 = E[7] along the axis from the given
   // one (a slider's rest length is 0, so E[7] holds no phi^-): the same line,
   // re-anchored near the point every step so that the bond vector, whose
@@ -228,42 +236,63 @@ __device__ __forceinline__ void general_end(T* E, T* a, int j, const T* q, const
 #pragma unroll
     for (int r = 0; r < 3; ++r) xs[r] = fma(E[7], a[r], xs[r]);
   }
-  T d[3], f[3];
+  T d[3];
+  bool moves = false;
   bond_vec<T>(q, xs, j < 0 ? (const T*)nullptr : qj, xo, d);
   settle<3>(d);
   if (kind == (T)AL_SLIDER_POINT) {
     // fixed weight at the own point (in the static block), drawn to the foot
-    T dp[3];
-    const T t = slider_end(d, j < 0 ? (const T*)nullptr : qj + 3, a, dp);
-    end_force(E[3], (T)0, dp, f);
-    settle<3>(f);
-    add_JT(rb, E, f[0], f[1], f[2]);
+    const T t = slider_end(d, j < 0 ? (const T*)nullptr : qj + 3, a, f);
+    *g = E[3];
     if (last) E[7] = E[7] - t;  // the foot is -t from the anchor
   } else if (kind == (T)AL_SLIDER_LINE) {
     // the own point is the foot xf = x_s + t u, so its weight moves every iteration
-    T dp[3];
-    const T t = slider_end(d, q + 3, a, dp);
-    const T xf[3] = {fma(t, a[0], xs[0]), fma(t, a[1], xs[1]), fma(t, a[2], xs[2])};
-    end_force(E[3], (T)0, dp, f);
-    settle<3>(f);
-    add_JT(rb, xf, f[0], f[1], f[2]);
-    block_add_end(dB, (double)E[3], (double)xf[0], (double)xf[1], (double)xf[2]);
-    refactor = true;
+    const T t = slider_end(d, q + 3, a, f);
+#pragma unroll
+    for (int r = 0; r < 3; ++r) x[r] = fma(t, a[r], xs[r]);
+    *g = *w = E[3];
+    moves = true;
     if (last) E[7] = E[7] + t;
   } else if (kind != (T)0) {
-    const T w = kind > (T)0 ? augmented_end(a, d, (T)(S.h * S.h), (T)S.al_beta, f)
-                            : polynomial_end(a, d, (T)(S.h * S.h), f);
-    settle<3>(f);
-    block_add_end(dB, (double)w, (double)E[0], (double)E[1], (double)E[2]);
-    refactor = true;
-    add_JT(rb, E, f[0], f[1], f[2]);
+    *w = kind > (T)0 ? augmented_end(a, d, h2, beta, f) : polynomial_end(a, d, h2, f);
+    moves = true;
   } else {
     quad_end_force(E, d, f);
-    settle<3>(f);
-    add_JT(rb, E, f[0], f[1], f[2]);
+  }
+  settle<3>(f);
+  settle<1>(g);
+  settle<3>(x);
+  settle<1>(w);
+  return moves;
+}
+
+// an end's terms added: force (times 1 rounds to itself), and block change of an end
+// that moves
+template <typename T>
+__device__ __forceinline__ void add_scaled(T* rb, const T* x, T g, const T* f) {
+#pragma unroll
+  for (int r = 0; r < 3; ++r) {
+    T y = g * f[r];
+    settle<1>(&y);
+    rb[r] = fma(g, f[r], rb[r]);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) rb[3 + 3 * r + c] = fma(y, x[c], rb[3 + 3 * r + c]);
   }
   settle<QW>(rb);
+}
+template <typename T>
+__device__ __forceinline__ void add_moved(bool moves, T w, const T* x, Block& dB) {
+  if (moves) block_add_end(dB, (double)w, (double)x[0], (double)x[1], (double)x[2]);
   settle_block(dB);
+}
+template <typename T>
+__device__ __forceinline__ void general_end(T* E, T* a, int j, const T* q, const T* qj, const SceneDev& S, bool last,
+                                            T* rb, Block& dB, bool& refactor) {
+  T f[3], g, x[3], w;
+  const bool moves = end_terms(E, a, j, q, qj, (T)(S.h * S.h), (T)S.al_beta, last, f, &g, x, &w);
+  add_scaled(rb, x, g, f);
+  add_moved(moves, w, x, dB);
+  refactor = refactor || moves;
 }
 
 // forces of the static ends e, e + LPB, ... below e1 of any kind, from global

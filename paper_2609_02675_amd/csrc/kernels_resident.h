@@ -18,7 +18,7 @@
 // trip of a partner's state, the dependent arithmetic of its ends, block solve and
 // rotation), not any throughput; the contact kernel with more than four
 // waves is bound by their instruction issue on the one compute unit, so larger
-// piles take the flat kernels (EngineT::resident_max).
+// piles take the flat kernels (EngineT::resident).
 //
 // Measured per step, against one kernel that read records, masses, factors and the
 // scene from memory in every iteration behind barriers of 16 waves (and took a
@@ -118,51 +118,33 @@ __device__ __forceinline__ void resident_predict(const SceneDev& S, const T* qn,
   settle<QR>(s);
 }
 
-// nsteps steps of a scene of at most NT bodies without contacts.  GENERAL: the scene
-// has variable or driven bonds.  The first ends of a body (two; of a GENERAL scene
-// as many as fit LDS, with their states) are read once per launch, or per step
-// when driven bonds move them; any further ones from global memory as they are
-// needed.
-template <typename T, int NT, bool GENERAL>
-__global__ void __launch_bounds__(NT) k_resident_joints(View<T> v, int n, int nsteps, DrivenTable dt) {
+// nsteps steps of a scene of at most NT bodies without contacts whose bonds are all
+// quadratic.  The first two ends of a body are read once per launch, any further
+// ones from global memory as they are needed.
+template <typename T, int NT>
+__global__ void __launch_bounds__(NT) k_resident_joints(View<T> v, int n, int nsteps) {
   constexpr int QR = Rec<T>::Q;
   constexpr bool HOLD = Resident<T>::hold(NT);
   using Q = Plane<T, QR, NT>;
-  // ends per body held in LDS: what the buffers of q leave, at most 8
-  constexpr int END_BYTES = 12 * sizeof(T) + 4;
-  constexpr int ROOM = (150 * 1024 - 2 * Q::N * (int)sizeof(T)) / (NT * END_BYTES);
-  constexpr int ME = !HOLD ? 0 : !GENERAL ? 2 : (ROOM < 8 ? ROOM : 8);
-  constexpr int SLOTS = GENERAL && ME > 0 ? ME * NT : 1;
-  using ES = Plane<T, EW, SLOTS>;
-  using AS = Plane<T, 4, SLOTS>;
   __shared__ __align__(16) T lq[2][Q::N];
-  __shared__ __align__(16) T le[GENERAL ? ES::N : 4], la[GENERAL ? AS::N : 4];
-  __shared__ int lp[SLOTS];
   const int t = threadIdx.x;
   const SceneDev& S = v.scenes[0];
   const int K = S.iters, step0 = S.step;
   const bool skip_local = (S.debug & 1) != 0;
   const bool body = t < n;
-  T qn[QR], vw[VW], m[MW], fac[FW], E[GENERAL ? 1 : 2][EW];
-  double bb[GENERAL ? 10 : 1];
-  int id[GENERAL ? 1 : 2];
+  T qn[QR], vw[VW], m[MW], fac[FW], E[2][EW];
+  int id[2];
   int e0 = 0, ne = 0;
-  bool free = false, var = false;
+  bool free = false;
   if (body) {
     load<T, QR>(v.qn + (size_t)QR * t, qn);
     load<T, VW>(v.vel + (size_t)VW * t, vw);
-    if constexpr (HOLD) load<T, MW>(v.mass + (size_t)MW * t, m);
-    const uint8_t fl = v.flags[t];
-    free = (fl & F_PINNED) == 0;
-    var = (fl & F_VARIABLE) != 0;
+    free = (v.flags[t] & F_PINNED) == 0;
     e0 = v.srow[t];
     ne = free ? v.srow_end[t] - e0 : 0;
     if constexpr (HOLD) {
+      load<T, MW>(v.mass + (size_t)MW * t, m);
       if (free) load<T, FW>(v.fac + (size_t)FW * t, fac);
-    }
-    if constexpr (HOLD && GENERAL) {
-      if (free) load<double, 10>(v.blk + 10 * (size_t)t, bb);
-    } else if constexpr (HOLD) {
 #pragma unroll
       for (int u = 0; u < 2; ++u)
         if (u < ne) {
@@ -171,54 +153,12 @@ __global__ void __launch_bounds__(NT) k_resident_joints(View<T> v, int n, int ns
         }
     }
   }
-  auto stage_ends = [&]() {
-    if constexpr (GENERAL && ME > 0) {
-      for (int u = 0; u < ME && u < ne; ++u) {
-        T r[EW];
-        load<T, EW>(v.se + (size_t)EW * (e0 + u), r);
-        ES::put(le, u * NT + t, r);
-        lp[u * NT + t] = v.se_partner[e0 + u];
-      }
-    }
-  };
-  stage_ends();
-  if constexpr (GENERAL && ME > 0) {
-    for (int u = 0; u < ME && u < ne; ++u) {
-      T a[4] = {(T)0, (T)0, (T)0, (T)0};
-      if (var) load<T, 4>(v.al + 4 * (size_t)(e0 + u), a);
-      AS::put(la, u * NT + t, a);
-    }
-  }
   if (body && !free) {  // a pinned body keeps q^n, in both buffers
     Q::put(lq[0], t, qn);
     Q::put(lq[1], t, qn);
   }
   double num = 0.0, den = 0.0;
   for (int st = 0; st < nsteps; ++st) {
-    if constexpr (GENERAL) {
-      if (dt.n > 0) {
-        // driven anchors at this step's time, then every block of the scene
-        // refactored (the same functions as the flat path's kernels)
-        for (int b = t; b < dt.n; b += NT)
-          update_driven_entry(v, b, step0 + st, S, dt.end_i, dt.end_j, dt.param);
-        __syncthreads();
-        if (body && free) {
-          factor_body(v, dt.mass64, t);
-          if constexpr (HOLD) {
-            load<T, FW>(v.fac + (size_t)FW * t, fac);
-            load<double, 10>(v.blk + 10 * (size_t)t, bb);
-          }
-          // the anchors that moved; a slider's E[7] lives in LDS between steps
-          for (int u = 0; u < ME && u < ne; ++u) {
-            T r[EW], x[EW];
-            load<T, EW>(v.se + (size_t)EW * (e0 + u), r);
-            ES::get(le, u * NT + t, x);
-            r[7] = x[7];
-            ES::put(le, u * NT + t, r);
-          }
-        }
-      }
-    }
     T s[QR], q[QR];
     if (free) {
       if constexpr (!HOLD) {
@@ -230,25 +170,6 @@ __global__ void __launch_bounds__(NT) k_resident_joints(View<T> v, int n, int ns
       if constexpr (!HOLD) store<T, QR>(v.s + (size_t)QR * t, s);
 #pragma unroll
       for (int c = 0; c < QR; ++c) q[c] = s[c];
-      if constexpr (GENERAL) {
-        if (var) {  // augmented ends, warm start (Sec. 5.2.2), as in the flat path's prediction
-          const T ga = (T)S.al_gamma, ag = (T)(S.al_alpha * S.al_gamma);
-          for (int u = 0; u < ne; ++u) {
-            T a[4];
-            if (u < ME)
-              AS::get(la, u * NT + t, a);
-            else
-              load<T, 4>(v.al + 4 * (size_t)(e0 + u), a);
-            if (!(a[3] > (T)0)) continue;
-            a[0] = fmax(ga * a[0], a[3]);
-            a[1] = ag * a[1];
-            if (u < ME)
-              AS::put(la, u * NT + t, a);
-            else
-              store<T, 4>(v.al + 4 * (size_t)(e0 + u), a);
-          }
-        }
-      }
     }
     __syncthreads();
     for (int k = 0; k < K; ++k) {
@@ -259,24 +180,7 @@ __global__ void __launch_bounds__(NT) k_resident_joints(View<T> v, int n, int ns
         T rb[QW];
 #pragma unroll
         for (int c = 0; c < QW; ++c) rb[c] = (T)0;
-        bool refactor = false;
-        Block dB{};
-        if constexpr (GENERAL) {
-          for (int u = 0; u < ME && u < ne; ++u) {
-            const int x = u * NT + t, j = lp[x];
-            T R[EW], a[4], qj[QR];
-            ES::get(le, x, R);
-            AS::get(la, x, a);
-            if (j >= 0) state(j, qj);
-            general_end(R, a, j, q, qj, S, k == K - 1, rb, dB, refactor);
-            if (a[3] > (T)0)
-              AS::put(la, x, a);
-            else if (k == K - 1 && a[3] != (T)0)
-              ES::put(le, x, R);
-          }
-          if (ne > ME)
-            general_ends<T, 1>(v, S, e0 + ME, e0 + ne, var, k == K - 1, q, state, rb, dB, refactor);
-        } else if constexpr (!HOLD) {
+        if constexpr (!HOLD) {
           quadratic_ends<T, 1>(v, e0, e0 + ne, q, state, rb);
         } else {
           T qj[2][QR];
@@ -296,12 +200,6 @@ __global__ void __launch_bounds__(NT) k_resident_joints(View<T> v, int n, int ns
           load<T, FW>(v.fac + (size_t)FW * t, fk);
           load<T, QR>(v.s + (size_t)QR * t, s);
           load<T, MW>(v.mass + (size_t)MW * t, m);
-        }
-        if constexpr (GENERAL) {
-          if (refactor) {
-            if constexpr (!HOLD) load<double, 10>(v.blk + 10 * (size_t)t, bb);
-            refactored(bb, dB, fk);
-          }
         }
         T qo[QR];
         solve_body(fk, s, m, rb, q, skip_local, v.polar, t, qo);
@@ -325,23 +223,240 @@ __global__ void __launch_bounds__(NT) k_resident_joints(View<T> v, int n, int ns
       }
     }
   }
-  if (free) {
-    if constexpr (HOLD) {
+  if constexpr (HOLD) {
+    if (free) {
       store<T, QR>(v.qn + (size_t)QR * t, qn);
       store<T, VW>(v.vel + (size_t)VW * t, vw);
     }
-    if constexpr (GENERAL && ME > 0) {
-      if (var)
-        for (int u = 0; u < ME && u < ne; ++u) {
-          T a[4], R[EW];
-          AS::get(la, u * NT + t, a);
-          ES::get(le, u * NT + t, R);
-          store<T, 4>(v.al + 4 * (size_t)(e0 + u), a);
-          v.se[(size_t)EW * (e0 + u) + 7] = R[7];
-        }
-    }
   }
   double* red = reinterpret_cast<double*>(&lq[0][0]);  // the buffers are done with
+  red[t] = num;
+  red[NT + t] = den;
+  __syncthreads();
+  resident_finish<NT>(red, red + NT, v.rho, &v.scenes[0].step, step0 + nsteps);
+}
+
+// Per end of a two-phase iteration, in LDS: (force, weight), (point, 1 if weight or
+// point moves within the step) and the force's factor (end_terms)
+template <typename T, int NE>
+struct EndLds {
+  using P = Plane<T, 4, NE>;
+  T f[P::N], x[P::N], g[NE];
+  __device__ void put(int e, const T* fw, const T* xm, T scale) {
+    P::put(f, e, fw);
+    P::put(x, e, xm);
+    g[e] = scale;
+  }
+  // add(f, x, g) of ends e0 .. e0 + ne in order, four ends' reads in flight
+  template <typename Add>
+  __device__ __forceinline__ void each(int e0, int ne, Add add) const {
+    for (int u0 = 0; u0 < ne; u0 += 4) {
+      T a[4][4], b[4][4], c[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int e = e0 + min(u0 + u, ne - 1);
+        P::get(f, e, a[u]);
+        P::get(x, e, b[u]);
+        c[u] = g[e];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (u0 + u < ne) add(a[u], b[u], c[u]);
+    }
+  }
+};
+
+// The most ends of a scene in k_resident_net: what 160 KB of LDS hold beside q^k.
+template <typename T>
+constexpr int NET_ENDS = sizeof(T) == 4 ? 2560 : 1536;
+
+// nsteps steps of a scene of at most NT bodies and NET_ENDS ends of any kind, without
+// contacts.  An iteration has two phases: the threads form the terms of the ends,
+// one end each, and put them in LDS; then one thread per body adds its ends in
+// order and solves.  The first U ends of a thread stay in its registers, with their
+// states; the rest come from global memory.  VARIABLE: some weight or point moves
+// within a step, so its body's block is inverted in every iteration.  One thread
+// per body for both phases walked its ends one after another; a quad of threads per
+// body (k_resident_ends) inverts the block four times, which more than 64 bodies
+// pay for in instructions.
+template <typename T, int NT, bool VARIABLE>
+__global__ void __launch_bounds__(NT) k_resident_net(View<T> v, int n, int n_ends, int nsteps, DrivenTable dt) {
+  constexpr int QR = Rec<T>::Q, NE = NET_ENDS<T>, U = NT < 1024 ? 2 : 1;
+  constexpr bool HOLD = NT < 1024;
+  using Q = Plane<T, QR, NT>;
+  __shared__ __align__(16) T lq[Q::N];
+  __shared__ __align__(16) EndLds<T, NE> le;
+  __shared__ short owner[NE];  // 2 b + 1 of a body with variable ends, 2 b of another; -1: pinned
+  const int t = threadIdx.x;
+  const SceneDev& S = v.scenes[0];
+  const int K = S.iters, step0 = S.step;
+  const bool skip_local = (S.debug & 1) != 0;
+  const T h2 = (T)(S.h * S.h), beta = (T)S.al_beta, ga = (T)S.al_gamma, ag = (T)(S.al_alpha * S.al_gamma);
+  T qn[QR], vw[VW], m[MW], fac[FW];
+  double bb[VARIABLE ? 10 : 1];
+  int e0 = 0, ne = 0;
+  bool free = false;
+  if (t < n) {
+    load<T, QR>(v.qn + (size_t)QR * t, qn);
+    load<T, VW>(v.vel + (size_t)VW * t, vw);
+    const unsigned fl = v.flags[t];
+    free = (fl & F_PINNED) == 0;
+    e0 = v.srow[t];
+    ne = v.srow_end[t] - e0;
+    const short o = free ? (short)(2 * t + (fl & F_VARIABLE ? 1 : 0)) : (short)-1;
+    for (int u = 0; u < ne; ++u) owner[e0 + u] = o;
+    if (!free) Q::put(lq, t, qn);  // a pinned body keeps q^n
+  }
+  __syncthreads();
+  // this thread's register ends
+  int eo[U], ej[U];
+  T E[U][EW], al[U][4];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int e = t + u * NT;
+    eo[u] = e < n_ends ? owner[e] : -1;
+    ej[u] = -1;
+    al[u][0] = al[u][1] = al[u][2] = al[u][3] = (T)0;
+    if (eo[u] >= 0) {
+      load<T, EW>(v.se + (size_t)EW * e, E[u]);
+      ej[u] = v.se_partner[e];
+      if (eo[u] & 1) load<T, 4>(v.al + 4 * (size_t)e, al[u]);
+    }
+  }
+  auto warm = [&](T* a) {  // augmented ends, warm start (Sec. 5.2.2)
+    a[0] = fmax(ga * a[0], a[3]);
+    a[1] = ag * a[1];
+  };
+  double num = 0.0, den = 0.0;
+  for (int st = 0; st < nsteps; ++st) {
+    if (dt.n > 0) {
+      // driven anchors at this step's time, then every block of the scene
+      // refactored (the same functions as the flat path's kernels)
+      for (int b = t; b < dt.n; b += NT)
+        update_driven_entry(v, b, step0 + st, S, dt.end_i, dt.end_j, dt.param);
+      __syncthreads();
+      if (free) factor_body(v, dt.mass64, t);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (eo[u] >= 0) {  // a slider's E[7] lives in the register
+          T r[EW];
+          load<T, EW>(v.se + (size_t)EW * (t + u * NT), r);
+#pragma unroll
+          for (int c = 0; c < 7; ++c) E[u][c] = r[c];
+        }
+    }
+    if (free && (st == 0 || dt.n > 0) && HOLD) {
+      load<T, MW>(v.mass + (size_t)MW * t, m);
+      load<T, FW>(v.fac + (size_t)FW * t, fac);
+      if constexpr (VARIABLE) load<double, 10>(v.blk + 10 * (size_t)t, bb);
+    }
+    if constexpr (VARIABLE) {
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (al[u][3] > (T)0) warm(al[u]);
+      for (int e = t + U * NT; e < n_ends; e += NT)
+        if (owner[e] >= 0 && (owner[e] & 1)) {
+          T a[4];
+          load<T, 4>(v.al + 4 * (size_t)e, a);
+          if (a[3] > (T)0) {
+            warm(a);
+            store<T, 4>(v.al + 4 * (size_t)e, a);
+          }
+        }
+    }
+    T s[QR], q[QR];
+    if (free) {
+      resident_predict(S, qn, vw, s);
+      Q::put(lq, t, s);
+      if constexpr (!HOLD) store<T, QR>(v.s + (size_t)QR * t, s);
+#pragma unroll
+      for (int c = 0; c < QR; ++c) q[c] = s[c];
+    }
+    __syncthreads();
+    for (int k = 0; k < K; ++k) {
+      auto terms = [&](int e, int o, int j, T* R, T* a) {
+        T qi[QR], qj[QR], f[4], g, x[4];
+        Q::get(lq, o >> 1, qi);
+        if (j >= 0) Q::get(lq, j, qj);
+        const bool moves = end_terms(R, a, j, qi, qj, h2, beta, k == K - 1, f, &g, x, f + 3);
+        x[3] = (T)(moves ? 1 : 0);
+        le.put(e, f, x, g);
+      };
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (eo[u] >= 0) terms(t + u * NT, eo[u], ej[u], E[u], al[u]);
+      for (int e = t + U * NT; e < n_ends; e += NT) {
+        const int o = owner[e];
+        if (o < 0) continue;
+        T R[EW], a[4] = {(T)0, (T)0, (T)0, (T)0};
+        load<T, EW>(v.se + (size_t)EW * e, R);
+        if (VARIABLE && (o & 1)) load<T, 4>(v.al + 4 * (size_t)e, a);
+        terms(e, o, v.se_partner[e], R, a);
+        if constexpr (VARIABLE) {
+          if (a[3] > (T)0)
+            store<T, 4>(v.al + 4 * (size_t)e, a);
+          else if (k == K - 1 && a[3] != (T)0)
+            v.se[(size_t)EW * e + 7] = R[7];
+        }
+      }
+      __syncthreads();
+      if (free) {
+        T rb[QW], fk[FW];
+#pragma unroll
+        for (int c = 0; c < QW; ++c) rb[c] = (T)0;
+        Block dB{};
+        bool refactor = false;
+        le.each(e0, ne, [&](const T* f, const T* x, T g) {
+          add_scaled(rb, x, g, f);
+          if constexpr (VARIABLE) {
+            add_moved(x[3] != (T)0, f[3], x, dB);
+            refactor = refactor || x[3] != (T)0;
+          }
+        });
+        if constexpr (HOLD) {
+#pragma unroll
+          for (int c = 0; c < 10; ++c) fk[c] = fac[c];
+        } else {
+          load<T, FW>(v.fac + (size_t)FW * t, fk);
+          load<T, QR>(v.s + (size_t)QR * t, s);
+          load<T, MW>(v.mass + (size_t)MW * t, m);
+        }
+        if constexpr (VARIABLE) {
+          if (refactor) {
+            if constexpr (!HOLD) load<double, 10>(v.blk + 10 * (size_t)t, bb);
+            refactored(bb, dB, fk);
+          }
+        }
+        T qo[QR];
+        solve_body(fk, s, m, rb, q, skip_local, v.polar, t, qo);
+        if (k == K - 1) residual_terms(m, qo, q, &num, &den);
+        settle<QR>(qo);
+        Q::put(lq, t, qo);
+#pragma unroll
+        for (int c = 0; c < QR; ++c) q[c] = qo[c];
+      }
+      __syncthreads();
+    }
+    if (free) {
+      resident_recover(q, qn, (T)(1.0 / S.h), vw, v.health);
+#pragma unroll
+      for (int c = 0; c < QR; ++c) qn[c] = q[c];
+    }
+  }
+  if (free) {
+    store<T, QR>(v.qn + (size_t)QR * t, qn);
+    store<T, VW>(v.vel + (size_t)VW * t, vw);
+  }
+  if constexpr (VARIABLE) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (eo[u] >= 0 && (eo[u] & 1)) {
+        const size_t e = t + u * NT;
+        store<T, 4>(v.al + 4 * e, al[u]);
+        v.se[EW * e + 7] = E[u][7];
+      }
+  }
+  double* red = reinterpret_cast<double*>(lq);  // the buffer is done with
   red[t] = num;
   red[NT + t] = den;
   __syncthreads();

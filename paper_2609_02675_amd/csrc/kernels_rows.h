@@ -198,6 +198,29 @@ struct RowLds {
   }
 };
 
+// the global step of row k (solve_body) from the row's summed force terms (rc, ra)
+template <typename T>
+__device__ __forceinline__ void solve_row(const T* fac, const T* m, T shi, T slo, const T* sa, T hi, T lo, const T* a,
+                                          T rc, T* ra, T* hn, T* ln, T* x) {
+  constexpr bool F32 = sizeof(T) == 4;
+  settle<1>(&rc);
+  settle<3>(ra);
+  // + M (s - q^k)
+  const T dc = F32 ? slo - lo : shi - hi;  // within a step the high words agree
+  const T d0 = sa[0] - a[0], d1 = sa[1] - a[1], d2 = sa[2] - a[2];
+  rc = fma(m[0], dc, rc);
+  ra[0] += fma(m[3], d2, fma(m[1], d0, m[2] * d1));
+  ra[1] += fma(m[5], d2, fma(m[2], d0, m[4] * d1));
+  ra[2] += fma(m[6], d2, fma(m[3], d0, m[5] * d1));
+  // H^{-1} r
+  const T qc = fma(fac[0], rc, -fma(fac[3], ra[2], fma(fac[1], ra[0], fac[2] * ra[1])));
+  x[0] = a[0] + fma(fac[6], ra[2], fma(fac[5], ra[1], fma(fac[4], ra[0], -(fac[1] * rc))));
+  x[1] = a[1] + fma(fac[8], ra[2], fma(fac[7], ra[1], fma(fac[5], ra[0], -(fac[2] * rc))));
+  x[2] = a[2] + fma(fac[9], ra[2], fma(fac[8], ra[1], fma(fac[6], ra[0], -(fac[3] * rc))));
+  *hn = F32 ? hi : hi + qc;
+  *ln = F32 ? lo + qc : lo;
+}
+
 // nsteps steps of a plain scene of at most NT / 4 bodies whose bonds are all quadratic
 template <typename T, int NT>
 __global__ void __launch_bounds__(NT) k_resident_rows(View<T> v, int n, int nsteps) {
@@ -286,26 +309,8 @@ __global__ void __launch_bounds__(NT) k_resident_rows(View<T> v, int n, int nste
             end(X, p, pl, true);
           }
         }
-        settle<1>(&rc);
-        settle<3>(ra);
-        // + M (s - q^k)
-        const T dc = F32 ? slo - lo : shi - hi;  // within a step the high words agree
-        const T d0 = sa[0] - a[0], d1 = sa[1] - a[1], d2 = sa[2] - a[2];
-        rc = fma(m[0], dc, rc);
-        ra[0] += fma(m[3], d2, fma(m[1], d0, m[2] * d1));
-        ra[1] += fma(m[5], d2, fma(m[2], d0, m[4] * d1));
-        ra[2] += fma(m[6], d2, fma(m[3], d0, m[5] * d1));
-        // H^{-1} r
-        const T qc = fma(fac[0], rc, -fma(fac[3], ra[2], fma(fac[1], ra[0], fac[2] * ra[1])));
-        T x[3];
-        x[0] = a[0] + fma(fac[6], ra[2], fma(fac[5], ra[1], fma(fac[4], ra[0], -(fac[1] * rc))));
-        x[1] = a[1] + fma(fac[8], ra[2], fma(fac[7], ra[1], fma(fac[5], ra[0], -(fac[2] * rc))));
-        x[2] = a[2] + fma(fac[9], ra[2], fma(fac[8], ra[1], fma(fac[6], ra[0], -(fac[3] * rc))));
-        T hn = hi, ln = lo;
-        if constexpr (F32)
-          ln += qc;
-        else
-          hn += qc;
+        T hn, ln, x[3];
+        solve_row(fac, m, shi, slo, sa, hi, lo, a, rc, ra, &hn, &ln, x);
         if (!skip_local) polar_rows(x, k, v.polar, b);
         lds[(it + 1) & 1].put(t, hn, ln, x);
         if (it == K - 1) {
@@ -333,6 +338,197 @@ __global__ void __launch_bounds__(NT) k_resident_rows(View<T> v, int n, int nste
   if (free && k == 0) {
     store<T, QR>(v.qn + (size_t)QR * b, qn);
     store<T, VW>(v.vel + (size_t)VW * b, vw);
+  }
+  if (k == 0) {
+    red[b] = num;
+    red[NB + b] = den;
+  }
+  __syncthreads();
+  resident_finish<NB>(red, red + NB, v.rho, &v.scenes[0].step, step0 + nsteps);
+}
+
+// nsteps steps of a plain scene of at most NT / 4 bodies and NT bond ends, of any
+// kind.  An iteration has two phases: thread e forms the terms of end e, whose
+// record and state it holds in registers, and puts them in LDS; then the quads add
+// their bodies' ends in order and solve.  A body with five ends walks one end's
+// chain instead of five.  VARIABLE: some weight or point moves within a step, so
+// its body's block is inverted in every iteration.  Driven anchors pass from the
+// thread of their entry to their ends through LDS; only a body whose own point is
+// driven is factored again.
+template <typename T, int NT, bool VARIABLE>
+__global__ void __launch_bounds__(NT) k_resident_ends(View<T> v, int n, int n_ends, int nsteps, DrivenTable dt) {
+  constexpr int QR = Rec<T>::Q, NB = NT / 4;
+  constexpr bool F32 = sizeof(T) == 4;
+  __shared__ __align__(16) RowLds<T, NT> lds[2];
+  __shared__ __align__(16) EndLds<T, NT> le;
+  __shared__ T anchor[3 * NT];                    // per driven entry
+  __shared__ int owner[NT], driver[NT];           // per end: its body, its driven entry (2 b: the partner's point, 2 b + 1: its own)
+  __shared__ double red[2 * NB];
+  const int t = threadIdx.x, b = t / 4, k = t % 4;
+  const SceneDev& S = v.scenes[0];
+  const int K = S.iters, step0 = S.step;
+  const bool skip_local = (S.debug & 1) != 0;
+  const T h2 = (T)(S.h * S.h), beta = (T)S.al_beta, ga = (T)S.al_gamma, ag = (T)(S.al_alpha * S.al_gamma);
+  T qn[QR], vw[VW], m[MW], fac[FW];
+  double bb[VARIABLE ? 10 : 1];
+  int e0 = 0, ne = 0;
+  bool free = false, var = false, own_driven = false;
+  owner[t] = -1;
+  driver[t] = -1;
+  __syncthreads();
+  for (int d = t; d < dt.n; d += NT) {
+    if (dt.end_i[d] >= 0) driver[dt.end_i[d]] = 2 * d;
+    if (dt.end_j[d] >= 0) driver[dt.end_j[d]] = 2 * d + 1;
+  }
+  if (b < n) {
+    load<T, QR>(v.qn + (size_t)QR * b, qn);
+    load<T, VW>(v.vel + (size_t)VW * b, vw);
+    load<T, MW>(v.mass + (size_t)MW * b, m);
+    const unsigned fl = v.flags[b];
+    free = (fl & F_PINNED) == 0;
+    var = (fl & F_VARIABLE) != 0;
+    e0 = v.srow[b];
+    ne = free ? v.srow_end[b] - e0 : 0;
+    if (free) {
+      load<T, FW>(v.fac + (size_t)FW * b, fac);
+      if constexpr (VARIABLE) load<double, 10>(v.blk + 10 * (size_t)b, bb);
+    }
+    for (int u = k; u < ne; u += 4) owner[e0 + u] = 2 * b + (var ? 1 : 0);
+    if (!free) {  // a pinned body keeps q^n, in both buffers
+      T a[3];
+      take_row(qn + 3, k, a);
+      const T hi = pick(qn[0], qn[1], qn[2], k), lo = F32 ? pick(qn[QR - 4], qn[QR - 3], qn[QR - 2], k) : (T)0;
+      lds[0].put(t, hi, lo, a);
+      lds[1].put(t, hi, lo, a);
+    }
+  }
+  __syncthreads();
+  // this thread's end
+  const bool end = t < n_ends && owner[t] >= 0;
+  const bool end_var = end && (owner[t] & 1);
+  const int eb = end ? owner[t] >> 1 : 0, drv = end ? driver[t] : -1;
+  int ej = -1;
+  T E[EW], al[4] = {(T)0, (T)0, (T)0, (T)0};
+  if (end) {
+    load<T, EW>(v.se + (size_t)EW * t, E);
+    ej = v.se_partner[t];
+    if (end_var) load<T, 4>(v.al + 4 * (size_t)t, al);
+  }
+  for (int u = 0; u < ne; ++u) own_driven = own_driven || (driver[e0 + u] >= 0 && (driver[e0 + u] & 1));
+  double num = 0.0, den = 0.0;
+  for (int st = 0; st < nsteps; ++st) {
+    if (dt.n > 0) {
+      for (int d = t; d < dt.n; d += NT)
+        update_driven_entry(v, d, step0 + st, S, dt.end_i, dt.end_j, dt.param, anchor + 3 * d);
+      __syncthreads();
+      if (drv >= 0) {
+        const T* x = anchor + 3 * (drv >> 1);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+          E[c] = drv & 1 ? x[c] : E[c];
+          E[4 + c] = drv & 1 ? E[4 + c] : x[c];
+        }
+      }
+      if (own_driven) {
+        if (k == 0) factor_body(v, dt.mass64, b);
+        __threadfence_block();
+        load<T, FW>(v.fac + (size_t)FW * b, fac);
+        if constexpr (VARIABLE) load<double, 10>(v.blk + 10 * (size_t)b, bb);
+      }
+    }
+    if (al[3] > (T)0) {  // augmented ends, warm start (Sec. 5.2.2)
+      al[0] = fmax(ga * al[0], al[3]);
+      al[1] = ag * al[1];
+    }
+    T hi = (T)0, lo = (T)0, a[3], shi = (T)0, slo = (T)0, sa[3];
+    if (free) {
+      T s[QR];
+      resident_predict(S, qn, vw, s);
+      shi = hi = pick(s[0], s[1], s[2], k);
+      slo = lo = F32 ? pick(s[QR - 4], s[QR - 3], s[QR - 2], k) : (T)0;
+      take_row(s + 3, k, sa);
+#pragma unroll
+      for (int c = 0; c < 3; ++c) a[c] = sa[c];
+      lds[0].put(t, hi, lo, a);
+    }
+    __syncthreads();
+    for (int it = 0; it < K; ++it) {
+      const RowLds<T, NT>& src = lds[it & 1];
+      if (end) {
+        auto state = [&](int body, T* q) {
+          T r[3][4], l[3];
+#pragma unroll
+          for (int c = 0; c < 3; ++c) src.get(4 * body + c, r[c], l + c);
+#pragma unroll
+          for (int c = 0; c < 3; ++c) {
+            q[c] = r[c][0];
+#pragma unroll
+            for (int i = 0; i < 3; ++i) q[3 + 3 * c + i] = r[c][1 + i];
+            if constexpr (F32) q[12 + c] = l[c];
+          }
+        };
+        T q[QR], qj[QR], f[4], g, x[4];
+        state(eb, q);
+        if (ej >= 0) state(ej, qj);
+        const bool moves = end_terms(E, al, ej, q, qj, h2, beta, it == K - 1, f, &g, x, f + 3);
+        x[3] = (T)(moves ? 1 : 0);
+        le.put(t, f, x, g);
+      }
+      __syncthreads();
+      if (free) {
+        T rc = (T)0, ra[3] = {(T)0, (T)0, (T)0}, fk[FW];
+        Block dB{};
+        bool refactor = false;
+        le.each(e0, ne, [&](const T* f, const T* x, T g) {
+          const T fk = pick(f[0], f[1], f[2], k);
+          T fr = g * fk;
+          settle<1>(&fr);
+          rc = fma(g, fk, rc);
+#pragma unroll
+          for (int c = 0; c < 3; ++c) ra[c] = fma(fr, x[c], ra[c]);
+          if constexpr (VARIABLE) {
+            add_moved(x[3] != (T)0, f[3], x, dB);
+            refactor = refactor || x[3] != (T)0;
+          }
+        });
+#pragma unroll
+        for (int c = 0; c < 10; ++c) fk[c] = fac[c];
+        if constexpr (VARIABLE) {
+          if (refactor) refactored(bb, dB, fk);
+        }
+        T hn, ln, x[3];
+        solve_row(fk, m, shi, slo, sa, hi, lo, a, rc, ra, &hn, &ln, x);
+        if (!skip_local) polar_rows(x, k, v.polar, b);
+        lds[(it + 1) & 1].put(t, hn, ln, x);
+        if (it == K - 1) {
+          T q0[QR], q1[QR];
+          gather_body(hi, lo, a, q0);
+          gather_body(hn, ln, x, q1);
+          residual_terms(m, q1, q0, &num, &den);
+        }
+        hi = hn;
+        lo = ln;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) a[c] = x[c];
+      }
+      __syncthreads();
+    }
+    if (free) {
+      T q[QR];
+      gather_body(hi, lo, a, q);
+      if constexpr (F32) q[QR - 1] = qn[QR - 1];
+      resident_recover(q, qn, (T)(1.0 / S.h), vw, v.health);
+#pragma unroll
+      for (int c = 0; c < QR; ++c) qn[c] = q[c];
+    }
+  }
+  if (free && k == 0) {
+    store<T, QR>(v.qn + (size_t)QR * b, qn);
+    store<T, VW>(v.vel + (size_t)VW * b, vw);
+  }
+  if (end_var) {
+    store<T, 4>(v.al + 4 * (size_t)t, al);
+    v.se[(size_t)EW * t + 7] = E[7];
   }
   if (k == 0) {
     red[b] = num;

@@ -227,7 +227,8 @@ __global__ void __launch_bounds__(256) k_reduce_history(int n, int K, const doub
 // end's own anchor (T and FP64 copies).
 template <typename T>
 __device__ __forceinline__ void update_driven_entry(const View<T>& v, int b, int step, const SceneDev& S,
-                                                    const int* d_end_i, const int* d_end_j, const double* d_param) {
+                                                    const int* d_end_i, const int* d_end_j, const double* d_param,
+                                                    T* anchor = nullptr) {
   const double t = S.t0 + (double)(step + 1) * S.h;
   const double* p = d_param + 13 * (size_t)b;
   const double th = p[9] + p[10] * sin(2.0 * 3.14159265358979323846 * p[11] * t + p[12]);
@@ -253,6 +254,11 @@ __device__ __forceinline__ void update_driven_entry(const View<T>& v, int b, int
     e64[0] = x0;
     e64[1] = x1;
     e64[2] = x2;
+  }
+  if (anchor) {
+    anchor[0] = (T)x0;
+    anchor[1] = (T)x1;
+    anchor[2] = (T)x2;
   }
 }
 template <typename T>

@@ -56,7 +56,7 @@ struct EngineBase {
   virtual void resident_steps(const HostScene& hs, int nsteps, hipStream_t st) = 0;
   // the most bodies of a scene that one workgroup takes (a contact scene's bodies
   // take four lanes each)
-  virtual int resident_max(bool contact) const = 0;
+  virtual bool resident(const HostScene& hs) const = 0;
   virtual void tile_step(int tile_bodies, const TileTable& tt, int grid, int nsteps,
                          hipStream_t st) = 0;
   virtual void finish_scenes(int n_scenes, hipStream_t st) = 0;
@@ -119,12 +119,12 @@ struct EngineT final : EngineBase {
   void resident_steps(const HostScene& hs, int nsteps, hipStream_t st) override {
     const int nd = (int)hs.drv_end_i.size();
     if (!hs.contact) {
-      e.launch_resident(false, hs.variable, nd, 0, nsteps, st);
+      e.launch_resident(false, hs.variable, hs.ne, nd, 0, nsteps, st);
       return;
     }
     for (int k = 0; k < nsteps; ++k) {
       e.launch_contacts(1, st);
-      e.launch_resident(true, hs.variable, nd, hs.ccap, 1, st);
+      e.launch_resident(true, hs.variable, hs.ne, nd, hs.ccap, 1, st);
     }
   }
   // A contact scene's limit is four waves, one per SIMD of the workgroup's compute
@@ -133,7 +133,12 @@ struct EngineT final : EngineBase {
   // against 0.167 ms, 200 boxes 0.222 against 0.180).  Joint scenes gain from one
   // workgroup at every size it holds (chain of 500 0.043 against 0.093 ms, of
   // 1,000 0.088 against 0.097).
-  int resident_max(bool contact) const override { return contact ? 64 : Resident<T>::NT; }
+  // The ends of variable and driven joints have to fit LDS.
+  bool resident(const HostScene& hs) const override {
+    if (hs.n == 0) return false;
+    if (hs.contact) return hs.n <= 64;
+    return hs.n <= Resident<T>::NT && (!(hs.variable || hs.driven) || hs.ne <= NET_ENDS<T>);
+  }
   // At most this many tiles (three workgroups per compute unit in FP32, two in FP64,
   // by registers) take the kernel with a quad of lanes per body; beyond it the
   // quads' idle lanes cost more issue slots than the shorter chains save.  Us per
@@ -451,7 +456,7 @@ pabd_status pabd_scene_create(const pabd_scene_desc* desc, pabd_scene** out) {
   pabd_status st = s->eng->allocate(c);
   if (st != PABD_OK) return fail(st, s->eng->error());
   s->hs.params.steps_total = INT_MAX;
-  s->resident = s->hs.n > 0 && s->hs.n <= s->eng->resident_max(s->hs.contact);
+  s->resident = s->eng->resident(s->hs);
   st = s->eng->upload(s->hs, 0, 0, 0, 0, 0, s->stream);
   if (st != PABD_OK) return fail(st, s->eng->error());
   s->eng->factor(s->stream);
@@ -2074,7 +2079,7 @@ pabd_status pabd_scene_run_noalloc(const pabd_scene_desc* desc, int32_t nsteps, 
   if (st != PABD_OK) return fail(st, eng->error());
   hs.params.steps_total = INT_MAX;
   // the same path as the plain scene's (pabd_scene_step)
-  const bool resident = hs.n > 0 && hs.n <= eng->resident_max(hs.contact);
+  const bool resident = eng->resident(hs);
   st = eng->upload(hs, 0, 0, 0, 0, 0, stream);
   if (st != PABD_OK) return fail(st, eng->error());
   eng->factor(stream);

@@ -138,3 +138,24 @@ def test_number_of_tiles_does_not_change_a_scenes_bits(P, prec, tile):
         for p, q in zip(x[:4], y[:4]):
             assert np.array_equal(p, q), sc.name
         assert x[4:] == y[4:], sc.name
+
+
+@pytest.mark.parametrize("prec", [S.PREC_FP32, S.PREC_FP64], ids=["fp32", "fp64"])
+def test_two_phase_kernels_match_the_flat_ones(P, prec):
+    """The resident kernels that form the ends first and add them afterwards, against
+    the flat kernels as above: ends beyond what registers hold and beyond what LDS
+    holds, many driven and sliding joints around the change from four lanes per
+    body to one, and a driven point on a free body, whose block is factored again."""
+    driven = S.linkage("slider", drive_amp_deg=60.0, precision=prec)
+    free = driven.copy(bond_j=np.where(driven.bond_type == S.BOND_DRIVEN, 2, driven.bond_j).astype(np.int32))
+    many = [S.merge([driven, free] * k) for k in (1, 8, 9, 33)]
+    nets = [S.spring_net(n, order=4, precision=prec) for n in (9, 19, 22)]
+    for sc in many + nets:
+        g, f = P.Scene(sc), P.Scene(sc)
+        g.step(3)
+        g.step(4)
+        f.set_debug(2)
+        f.step(7)
+        for p, q in zip(g.state(), f.state()):
+            assert np.isfinite(p).all() and np.array_equal(p, q), (sc.name, sc.n_bodies)
+        assert g.residual() == pytest.approx(f.residual(), rel=1e-12), sc.name
