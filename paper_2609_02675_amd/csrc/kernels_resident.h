@@ -4,8 +4,10 @@
 // The bodies exchange q^k through LDS and everything a step does not change
 // stays in registers and LDS, so an iteration waits on no global load.
 //
-//   k_resident_joints   a scene without contacts, one lane per body: any number of
+//   k_resident_joints   a scene of quadratic bonds, one lane per body: any number of
 //                       steps in one launch (nothing is built between them)
+//   k_resident_net      the same for bonds of any kind, in two phases: a lane per
+//                       end, then a lane per body (smaller scenes: kernels_rows.h)
 //   k_resident_contact  one step of a contact scene after its contact construction:
 //                       four lanes per body form its ends' terms, then one lane
 //                       per body solves
@@ -24,8 +26,8 @@
 // scene from memory in every iteration behind barriers of 16 waves (and took a
 // launch per step): eight-body chain 0.044 -> 0.025 ms (FP64 0.066 -> 0.051),
 // chain of 200 0.057 -> 0.027, of 500 0.075 -> 0.040, of 1,000 0.101 -> 0.085,
-// slider crank 0.106 -> 0.079, 11 x 11 net of order 4 in FP64 0.164 -> 0.090, pile
-// of 16 boxes 0.118 -> 0.095, of 60 0.134 -> 0.111 with its contact construction.
+// 11 x 11 net of order 4 in FP64 0.164 -> 0.074 (0.090 with one lane walking a body's
+// ends), 16 x 16 net of order 6 0.180 -> 0.070, pile of 16 boxes 0.118 -> 0.095, of 60 0.134 -> 0.111 with its contact construction.
 #pragma once
 
 #include "common.h"
@@ -278,7 +280,8 @@ constexpr int NET_ENDS = sizeof(T) == 4 ? 2560 : 1536;
 // within a step, so its body's block is inverted in every iteration.  One thread
 // per body for both phases walked its ends one after another; a quad of threads per
 // body (k_resident_ends) inverts the block four times, which more than 64 bodies
-// pay for in instructions.
+// pay for in instructions.  Issue bounds it: about 1,100 FP64 instructions per body
+// and iteration on two to eight waves.
 template <typename T, int NT, bool VARIABLE>
 __global__ void __launch_bounds__(NT) k_resident_net(View<T> v, int n, int n_ends, int nsteps, DrivenTable dt) {
   constexpr int QR = Rec<T>::Q, NE = NET_ENDS<T>, U = NT < 1024 ? 2 : 1;

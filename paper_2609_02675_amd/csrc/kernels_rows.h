@@ -13,6 +13,7 @@
 // saves, so large batches keep kernels_tile.h.
 //
 //   k_resident_rows  steps of a small plain scene (k_resident_joints' arithmetic)
+//   k_resident_ends  the same for bonds of any kind, in two phases
 //   k_tile_rows      steps of a batch's tiles (k_tile_step's arithmetic)
 //
 // Each entry is formed by the operations of those kernels in their order, so the
@@ -354,7 +355,9 @@ __global__ void __launch_bounds__(NT) k_resident_rows(View<T> v, int n, int nste
 // chain instead of five.  VARIABLE: some weight or point moves within a step, so
 // its body's block is inverted in every iteration.  Driven anchors pass from the
 // thread of their entry to their ends through LDS; only a body whose own point is
-// driven is factored again.
+// driven is factored again.  Us per step, one lane per body against this: slider
+// crank 79 and 34, four-bar linkage 72 and 28 (FP64 79 and 34), 8 x 8 net of order 4
+// 81 and 41.
 template <typename T, int NT, bool VARIABLE>
 __global__ void __launch_bounds__(NT) k_resident_ends(View<T> v, int n, int n_ends, int nsteps, DrivenTable dt) {
   constexpr int QR = Rec<T>::Q, NB = NT / 4;
