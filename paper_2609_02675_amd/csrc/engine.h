@@ -479,6 +479,9 @@ struct Engine {
   // a single contact scene of at most this many bodies takes the all-pairs search
   // (at most 2,080 pairs of tiles)
   static constexpr int BRUTE_MAX = 2048;
+  // beyond this many bodies the sort's workgroups hold four waves (fewer to dispatch);
+  // below it one, over as many compute units as there are bodies
+  static constexpr int SORT_WIDE = 4096;
   // predict: the prep kernel also runs the step's prediction for the bodies
   // [0, min(cap.n, contact bodies))
   void launch_contacts(int n_scenes, hipStream_t st, bool predict = false, FlatWave* waves = nullptr,
@@ -515,7 +518,8 @@ struct Engine {
       const int ng = std::min(8192, std::max(1, (pcap + 255) / 256));
       hipLaunchKernelGGL(k_narrow_pairs<T>, dim3((unsigned)(ng + (n + 31) / 32)), dim3(256), 0, st, v, cb, ng);
     }
-    hipLaunchKernelGGL(k_sort_contacts<T>, dim3((unsigned)std::max(1, n)), dim3(64), 0, st, v);
+    const int sw = n > SORT_WIDE ? 4 : 1;  // waves (bodies) per workgroup
+    hipLaunchKernelGGL(k_sort_contacts<T>, dim3((unsigned)std::max(1, (n + sw - 1) / sw)), dim3(64 * sw), 0, st, v);
   }
 
   // Plain scenes of quadratic bonds up to this size take a quad of lanes per body
