@@ -146,7 +146,7 @@ pabd_status pabd_set_allocator(void *(*alloc)(size_t bytes, void *ctx),
 /* number of HIP devices visible (0 without a GPU); never fails */
 int32_t pabd_device_count(void);
 
-/* ---- plain path: one scene, one kernel launch per iteration --------------- */
+/* ---- plain path: one scene ------------------------------------------------ */
 
 /* Validate the descriptor, take m and Pi0 per body (given, or from density and
  * shape: Sec. 4.1.1), build the bond incidence lists in (body, bond id) order,

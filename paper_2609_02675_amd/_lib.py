@@ -297,7 +297,8 @@ def run_noalloc(scene: SceneDesc, nsteps: int, stream: Optional[int] = None):
 
 
 class Scene:
-    """One scene on the plain path (one kernel launch per iteration)."""
+    """One scene on the plain path (small scenes in one kernel launch, larger ones
+    in one per iteration)."""
 
     def __init__(self, scene: SceneDesc):
         self.n = scene.n_bodies
