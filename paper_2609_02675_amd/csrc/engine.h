@@ -136,7 +136,7 @@ struct Engine {
   unsigned long long *ce_key = nullptr, *reach = nullptr;
   T* ce = nullptr;
   StageRec<T>* ce_stage = nullptr;
-  int *bucket_count = nullptr, *bucket_start = nullptr, *bucket_fill = nullptr, *scan_tmp = nullptr;
+  int *bucket_count = nullptr, *bucket_start = nullptr, *bucket_fill = nullptr;
   int *hist = nullptr, *large = nullptr, *counters = nullptr, *ltask = nullptr;
   double* breach = nullptr;
   BroadRec* brec = nullptr;
@@ -295,18 +295,17 @@ struct Engine {
       PABD_TRY(alloc(ce_partner, nc));
       PABD_TRY(alloc(ce_key, nc));
       PABD_TRY(alloc(ce_stage, nc));
-      // power of two, at most 2^20 so the three-pass scan (1024 x 1024) covers it
+      // power of two, at least a workgroup's 1,024 and at most 2^20
       tb = 1024;
       while (tb < 2 * ncb && tb < (1 << 20)) tb <<= 1;
       PABD_TRY(alloc(bucket_count, (size_t)tb));
-      PABD_TRY(alloc(bucket_start, (size_t)tb + 1));
+      PABD_TRY(alloc(bucket_start, (size_t)tb));
       PABD_TRY(alloc(bucket_fill, (size_t)tb));
-      PABD_TRY(alloc(scan_tmp, (size_t)(tb / 1024 + 2)));
       PABD_TRY(alloc(brec, nb));
       PABD_TRY(alloc(breach, nb));
       PABD_TRY(alloc(large, nb));
       PABD_TRY(alloc(ltask, nb + 1));
-      PABD_TRY(alloc(counters, 3));
+      PABD_TRY(alloc(counters, 4));
       PABD_TRY(alloc(hist, (size_t)REACH_BINS * c.s));
       // candidate pairs: half a pair per slot, at least 16 per body
       const size_t pc = std::max(nb * 16, nc / 2);
@@ -489,7 +488,7 @@ struct Engine {
     View<T> v = view();
     v.n = std::min(cap.n, ncb);
     ContactBuf cb{tb,    bucket_count, bucket_start, bucket_fill, brec,  reach,   hist,
-                  breach, large,       counters,     pairs,       pcap,  mass64,  scan_tmp, ltask};
+                  breach, large,       counters,     pairs,       pcap,  mass64,  ltask};
     const int n = v.n;
     const bool brute = n_scenes == 1 && n <= BRUTE_MAX;
     const int nbk = brute ? 0 : tb;  // bucket counts cleared by the prep kernel
@@ -504,17 +503,10 @@ struct Engine {
       hipLaunchKernelGGL(k_contact_cells, grid_for(n_scenes, 64), dim3(64), 0, st, scenes, n_scenes,
                          (const unsigned long long*)reach, (const int*)hist);
       hipLaunchKernelGGL(k_hash_count<T>, grid_for(n, 256), dim3(256), 0, st, v, cb);
-      const int nb = (tb + 1023) / 1024;
-      hipLaunchKernelGGL(k_scan_block, dim3(nb), dim3(1024), 0, st, (const int*)bucket_count,
-                         bucket_start, tb, scan_tmp);
-      hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(1024), 0, st, scan_tmp, nb, bucket_start + tb);
-      hipLaunchKernelGGL(k_scan_add, grid_for(tb, 256), dim3(256), 0, st, bucket_start, tb,
-                         (const int*)scan_tmp);
+      hipLaunchKernelGGL(k_buckets<T>, dim3((unsigned)(tb / 1024 + 1)), dim3(1024), 0, st, v, cb);
       hipLaunchKernelGGL(k_hash_fill<T>, grid_for(n, 256), dim3(256), 0, st, v, cb);
-      hipLaunchKernelGGL(k_broad_small<T>, grid_for((int)std::min<long long>((long long)n * BLPB, INT_MAX), 256),
-                         dim3(256), 0, st, v, cb);
-      hipLaunchKernelGGL(k_large_tasks<T>, dim3(1), dim3(1024), 0, st, v, cb);
-      hipLaunchKernelGGL(k_broad_large<T>, dim3(1024), dim3(BL_CHUNK), 0, st, v, cb);
+      const int lb = 1024, sb = (int)(((long long)n * BLPB + 255) / 256);
+      hipLaunchKernelGGL(k_broad<T>, dim3((unsigned)(lb + sb)), dim3(BL_CHUNK), 0, st, v, cb, lb);
       const int ng = std::min(8192, std::max(1, (pcap + 255) / 256));
       hipLaunchKernelGGL(k_narrow_pairs<T>, dim3((unsigned)(ng + (n + 31) / 32)), dim3(256), 0, st, v, cb, ng);
     }

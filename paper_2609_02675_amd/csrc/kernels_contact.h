@@ -19,14 +19,14 @@
 //   k_contact_cells  per scene: cell = 2 cut, cut = the smaller of the maximum
 //                    reach and the upper edge of the bin holding the 98th
 //                    percentile; bodies with reach > cut are "large"
-//   k_hash_count / scan / k_hash_fill   uniform-grid spatial hash of the small
+//   k_hash_count / k_buckets / k_hash_fill   uniform-grid spatial hash of the small
 //                    bodies (scene id in the hash), each bucket a run of 64-byte
 //                    records holding the body's centre, reach, cell and filters;
 //                    large bodies go to a list instead
-//   k_broad_small    14 lanes per small body: its own cell and the 13 cells of
+//   k_broad          14 lanes per small body: its own cell and the 13 cells of
 //                    the forward half-neighbourhood, one per lane, pairs with
 //                    small bodies
-//   k_large_tasks / k_broad_large   the large bodies' work in tasks of 256
+//                    and beside them the large bodies' work in tasks of 256
 //                    threads spread over the grid: small partners over the
 //                    cells a body's reach spans (or over the scene's bodies when
 //                    that is fewer), large partners of higher index
@@ -73,18 +73,17 @@ constexpr int REACH_BIN_BASE = 468;  // float bits >> 21 of 2^-10: bins span 2^-
 struct ContactBuf {
   int tb;                // hash buckets (power of two)
   int* bucket_count;     // [tb]
-  int* bucket_start;     // [tb + 1]
+  int* bucket_start;     // [tb] first record of a bucket
   int* bucket_fill;      // [tb]
   BroadRec* rec;         // [nc] small bodies in bucket order
   unsigned long long* reach;  // per scene: max(R + pm) as double bits
   int* hist;             // per scene: REACH_BINS counts
   double* breach;        // per body: R + pm
   int* large;            // [nc] large bodies
-  int* counters;         // [0] large bodies, [1] candidate pairs, [2] large-body tasks
+  int* counters;         // [0] large bodies, [1] candidate pairs, [2] large-body tasks, [3] records
   int2* pairs;           // [pcap]
   int pcap;
   const double* mass64;  // 8 per body
-  int* scan_tmp;         // block sums
   int* ltask;            // [nc + 1] first task of each large body (exclusive prefix)
 };
 
@@ -112,7 +111,7 @@ __global__ void k_contact_prep(View<T> v, ContactBuf cb, int n_scenes, int n_buc
   }
   if (i < n_scenes) cb.reach[i] = 0ull;
   if (i < n_scenes * REACH_BINS) cb.hist[i] = 0;
-  if (i < 3) cb.counters[i] = 0;
+  if (i < 4) cb.counters[i] = 0;
   if (i >= v.n) return;
   v.ccount[i] = 0;
   v.r_num[i] = 0.0;
@@ -283,45 +282,6 @@ __global__ void k_hash_fill(View<T> v, ContactBuf cb) {
   const unsigned b = bucket_of(sc, cc[0], cc[1], cc[2], cb.tb);
   const int pos = atomicAdd(cb.bucket_fill + b, 1);
   cb.rec[cb.bucket_start[b] + pos] = r;
-}
-
-// ---- exclusive scan of int counts (three passes, 1024 per block) ---------------
-
-__global__ void __launch_bounds__(1024) k_scan_block(const int* in, int* out, int n, int* block_sums) {
-  __shared__ int sh[1024];
-  const int t = threadIdx.x, i = blockIdx.x * 1024 + t;
-  int x = i < n ? in[i] : 0;
-  sh[t] = x;
-  __syncthreads();
-  for (int off = 1; off < 1024; off <<= 1) {
-    int y = t >= off ? sh[t - off] : 0;
-    __syncthreads();
-    sh[t] += y;
-    __syncthreads();
-  }
-  if (i < n) out[i] = sh[t] - x;
-  if (t == 1023) block_sums[blockIdx.x] = sh[1023];
-}
-
-__global__ void __launch_bounds__(1024) k_scan_sums(int* block_sums, int nb, int* total_out) {
-  __shared__ int sh[1024];
-  const int t = threadIdx.x;
-  int x = t < nb ? block_sums[t] : 0;
-  sh[t] = x;
-  __syncthreads();
-  for (int off = 1; off < 1024; off <<= 1) {
-    int y = t >= off ? sh[t - off] : 0;
-    __syncthreads();
-    sh[t] += y;
-    __syncthreads();
-  }
-  if (t < nb) block_sums[t] = sh[t] - x;
-  if (t == 1023) *total_out = sh[1023];
-}
-
-__global__ void k_scan_add(int* out, int n, const int* block_sums) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) out[i] += block_sums[i / 1024];
 }
 
 // ---- narrow phase ----------------------------------------------------------------
@@ -784,8 +744,8 @@ __device__ __forceinline__ void plane_body(const View<T>& v, const ContactBuf& c
   plane_contacts(v, cb, sc, i, gi, own_pm(v, i, sc, gi));
 }
 
-// BLPB lanes per body: for a small body, the lanes split the 14 cells made of its own cell (partners of
-// higher index) and the 13 cells of the forward half of its neighbourhood, so
+// BLPB lanes per body: for a small body, the lanes split the 14 cells made of its
+// own cell (partners of higher index) and the 13 cells of the forward half of its neighbourhood, so
 // each pair of neighbouring cells is searched from one side only.  One cell per
 // lane: each lane's loads form one short dependent chain (bucket range, then
 // records), which keeps small scenes from waiting on fourteen such chains in a
@@ -794,13 +754,8 @@ __device__ __forceinline__ void plane_body(const View<T>& v, const ContactBuf& c
 constexpr int BLPB = 14;
 
 template <typename T>
-__global__ void __launch_bounds__(256) k_broad_small(View<T> v, ContactBuf cb) {
-  __shared__ int2 lbuf[PAIR_LDS];
-  __shared__ int lcount, lbase;
-  if (threadIdx.x == 0) lcount = 0;
-  __syncthreads();
-  const PairBuf pb{lbuf, &lcount, &lbase};
-  const long long gt = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+__device__ __forceinline__ void broad_small(const View<T>& v, const ContactBuf& cb, const PairBuf& pb, int block) {
+  const long long gt = (long long)block * 256 + threadIdx.x;
   const int i = (int)(gt / BLPB), sub = (int)(gt % BLPB);
   const int sc = i < v.n ? v.bscene[i] : -1;
   if (i < v.n && contact_body(v, i, sc)) {
@@ -823,7 +778,7 @@ __global__ void __launch_bounds__(256) k_broad_small(View<T> v, ContactBuf cb) {
         if (t < 27) {
           const unsigned b = bucket_of(sc, cc[0] + t % 3 - 1, cc[1] + (t / 3) % 3 - 1, cc[2] + t / 9 - 1, cb.tb);
           e0s[u] = cb.bucket_start[b];
-          e1s[u] = cb.bucket_start[b + 1];
+          e1s[u] = e0s[u] + cb.bucket_count[b];
         }
       }
 #pragma unroll
@@ -842,7 +797,6 @@ __global__ void __launch_bounds__(256) k_broad_small(View<T> v, ContactBuf cb) {
       }
     }
   }
-  flush_pairs(pb, v, cb);
 }
 
 // A large body's share of the broad phase, split into tasks of BL_CHUNK
@@ -853,7 +807,7 @@ __global__ void __launch_bounds__(256) k_broad_small(View<T> v, ContactBuf cb) {
 // the grid, so one body with a long reach (a robot's torso over a bed of small
 // spheres: tens of thousands of cells) no longer keeps one workgroup busy while
 // the others idle.
-constexpr int BL_CHUNK = 256;  // threads of k_broad_large
+constexpr int BL_CHUNK = 256;  // threads of k_broad
 
 struct LargeWork {
   double c[3], rL, cell;
@@ -883,8 +837,7 @@ __device__ __forceinline__ LargeWork large_work(const View<T>& v, const ContactB
 // the first task of every large body (exclusive prefix) and their total; one
 // workgroup of 1024 threads
 template <typename T>
-__global__ void __launch_bounds__(1024) k_large_tasks(View<T> v, ContactBuf cb) {
-  __shared__ int part[1024];
+__device__ __forceinline__ void large_tasks(const View<T>& v, const ContactBuf& cb, int* part) {
   const int nl = cb.counters[0];
   int carry = 0;
   for (int base = 0; base < nl; base += 1024) {
@@ -908,16 +861,46 @@ __global__ void __launch_bounds__(1024) k_large_tasks(View<T> v, ContactBuf cb) 
   }
 }
 
-// grid-stride over the large bodies' tasks
+// Every bucket's run of records, in no particular order of the buckets: one
+// workgroup scans 1,024 counts and takes its share of the records with one atomic.
+// (The order of the candidate pairs is free, the sort fixes the contacts'.)  The
+// last workgroup forms the large bodies' tasks.  A scan in bucket order and the
+// tasks were three more launches: 21 us together on 50,000 spheres, this takes 14.
 template <typename T>
-__global__ void __launch_bounds__(BL_CHUNK) k_broad_large(View<T> v, ContactBuf cb) {
-  __shared__ int2 lbuf[PAIR_LDS];
-  __shared__ int lcount, lbase;
-  if (threadIdx.x == 0) lcount = 0;
+__global__ void __launch_bounds__(1024) k_buckets(View<T> v, ContactBuf cb) {
+  __shared__ int part[1024];
+  if ((int)blockIdx.x == cb.tb / 1024) {
+    large_tasks(v, cb, part);
+    return;
+  }
+  const int t = threadIdx.x, lane = t % 64, w = t / 64, i = blockIdx.x * 1024 + t;
+  const int x = cb.bucket_count[i];
+  int sum = x;
+  for (int o = 1; o < 64; o <<= 1) {
+    const int y = __shfl_up(sum, o);
+    if (lane >= o) sum += y;
+  }
+  if (lane == 63) part[w] = sum;
   __syncthreads();
-  const PairBuf pb{lbuf, &lcount, &lbase};
+  if (t == 0) {
+    int total = 0;
+    for (int k = 0; k < 16; ++k) {
+      const int y = part[k];
+      part[k] = total;
+      total += y;
+    }
+    part[16] = total > 0 ? atomicAdd(cb.counters + 3, total) : 0;
+  }
+  __syncthreads();
+  cb.bucket_start[i] = part[16] + part[w] + sum - x;
+}
+
+// workgroup `block` of `blocks`, in turn over the large bodies' tasks
+template <typename T>
+__device__ __forceinline__ void broad_large(const View<T>& v, const ContactBuf& cb, const PairBuf& pb, int block,
+                                            int blocks) {
   const int nl = cb.counters[0], total = cb.counters[2];
-  for (int task = blockIdx.x; task < total; task += gridDim.x) {
+  for (int task = block; task < total; task += blocks) {
     // the large body holding this task: the last l with ltask[l] <= task
     int lo = 0, hi = nl - 1;
     while (lo < hi) {
@@ -941,8 +924,8 @@ __global__ void __launch_bounds__(BL_CHUNK) k_broad_large(View<T> v, ContactBuf 
         const int tx = cc[0] + t % w - m, ty = cc[1] + (t / w) % w - m, tz = cc[2] + t / (w * w) - m;
         const unsigned long long key = pack_cell(tx, ty, tz);
         const unsigned b = bucket_of(sc, tx, ty, tz, cb.tb);
-        const int e1 = cb.bucket_start[b + 1];
-        for (int e = cb.bucket_start[b]; e < e1; ++e) {
+        const int e0 = cb.bucket_start[b], e1 = e0 + cb.bucket_count[b];
+        for (int e = e0; e < e1; ++e) {
           const BroadRec r = cb.rec[e];
           if (r.cell != key || r.scene != sc) continue;
           if (!near_rec(lw.c, lw.rL, r)) continue;
@@ -972,6 +955,22 @@ __global__ void __launch_bounds__(BL_CHUNK) k_broad_large(View<T> v, ContactBuf 
       }
     }
   }
+}
+
+// the broad phase by the hash: the first `large_blocks` workgroups take the large
+// bodies' tasks, the rest the small bodies, whose time hides the few long tasks (50,000
+// spheres under a robot: 80 + 14 us in two launches, 80 in one)
+template <typename T>
+__global__ void __launch_bounds__(BL_CHUNK) k_broad(View<T> v, ContactBuf cb, int large_blocks) {
+  __shared__ int2 lbuf[PAIR_LDS];
+  __shared__ int lcount, lbase;
+  if (threadIdx.x == 0) lcount = 0;
+  __syncthreads();
+  const PairBuf pb{lbuf, &lcount, &lbase};
+  if ((int)blockIdx.x < large_blocks)
+    broad_large(v, cb, pb, blockIdx.x, large_blocks);
+  else
+    broad_small(v, cb, pb, (int)blockIdx.x - large_blocks);
   flush_pairs(pb, v, cb);
 }
 
