@@ -815,8 +815,18 @@ size_t contact_cost(int ts) {
 // per flat-path body: broad-phase record, reach, large-list entry, at least 16 candidate pairs
 size_t contact_body_cost() { return sizeof(BroadRec) + 8 + 4 + 8 * 16; }
 
+// Steps that a caller's stream may still run read the tables, records and scene
+// entries that the batch's own stream is about to rewrite: a wave table rewritten
+// under a step would end that step's iterations (arm_wave sets their count anew for
+// each step).
+pabd_status wait_foreign(const pabd_batch* b) {
+  if (b->foreign) API_HIP(hipDeviceSynchronize());
+  return PABD_OK;
+}
+
+// rebuild the device tables; nothing may be stepping (wait_foreign)
 pabd_status batch_tables(pabd_batch* b) {
-  // rebuild the device tile table from the host tiles
+  // the device tile table from the host tiles
   std::vector<int> first, count, kmax;
   for (const Tile& t : b->tiles) {
     if (t.slots.empty()) continue;
@@ -918,6 +928,19 @@ pabd_status batch_tables(pabd_batch* b) {
     b->launch = L;
     b->graph.reset();
   }
+  return PABD_OK;
+}
+
+// the tables brought up to date for a step on st, if scenes came or went
+pabd_status batch_refresh(pabd_batch* b, hipStream_t st) {
+  if (!b->dirty) return PABD_OK;
+  hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+  API_HIP(hipStreamIsCapturing(st, &capturing));
+  if (capturing == hipStreamCaptureStatusNone) {  // a capture forbids the wait
+    if (pabd_status s = wait_foreign(b); s != PABD_OK) return s;
+  }
+  if (pabd_status s = batch_tables(b); s != PABD_OK) return s;
+  b->dirty = false;
   return PABD_OK;
 }
 
@@ -1167,8 +1190,9 @@ pabd_status pabd_batch_admit(pabd_batch* b, const pabd_scene_desc* desc, int32_t
       break;
     }
   if (slot < 0) return fail(PABD_E_BUSY, "no free slot");
-  // the flat path is not yet recorded in a graph: finish in-flight work first
+  // finish in-flight work first
   API_HIP(hipStreamSynchronize(b->stream));
+  if (pabd_status st = wait_foreign(b); st != PABD_OK) return st;
   Slot& s = b->slots[slot];
   s = Slot{};
   s.hs = hs;
@@ -1195,6 +1219,7 @@ pabd_status pabd_batch_release(pabd_batch* b, int32_t slot) {
   if (!b) return fail(PABD_E_INVALID, "null batch");
   if (slot < 0 || slot >= b->max_slots || !b->slots[slot].used) return fail(PABD_E_NOTFOUND, "slot not in use");
   API_HIP(hipStreamSynchronize(b->stream));
+  if (pabd_status st = wait_foreign(b); st != PABD_OK) return st;
   Slot& s = b->slots[slot];
   pabd_status st = b->eng->clear_bodies(s.boff, std::max(1, s.n), b->stream, s.doff, s.nd);
   if (st != PABD_OK) return fail(st, b->eng->error());
@@ -1219,12 +1244,9 @@ pabd_status pabd_batch_steps(pabd_batch* b, int32_t nsteps, void* hip_stream) {
   if (!b) return fail(PABD_E_INVALID, "null batch");
   if (nsteps < 1 || nsteps > PABD_MAX_STEPS_PER_LAUNCH) return fail(PABD_E_INVALID, "nsteps out of range");
   hipStream_t st = hip_stream ? (hipStream_t)hip_stream : b->stream;
+  // the graph is rebuilt only if the launch extents changed
+  if (pabd_status s2 = batch_refresh(b, st); s2 != PABD_OK) return s2;
   b->foreign = b->foreign || st != b->stream;
-  if (b->dirty) {  // new tables; the graph is rebuilt only if the launch extents changed
-    pabd_status s2 = batch_tables(b);
-    if (s2 != PABD_OK) return s2;
-    b->dirty = false;
-  }
   if (use_graphs()) {
     if (b->graph.x && b->graph_steps != nsteps) b->graph.reset();
     if (!b->graph.x) {
@@ -1427,11 +1449,7 @@ pabd_status pabd_batch_time_tile_kernel(pabd_batch* b, int32_t reps, int32_t nst
   if (!b || reps < 1 || !avg_ms) return fail(PABD_E_INVALID, "bad arguments");
   if (nsteps < 1 || nsteps > PABD_MAX_STEPS_PER_LAUNCH) return fail(PABD_E_INVALID, "nsteps out of range");
   *avg_ms = 0.0;
-  if (b->dirty) {
-    pabd_status s2 = batch_tables(b);
-    if (s2 != PABD_OK) return s2;
-    b->dirty = false;
-  }
+  if (pabd_status s2 = batch_refresh(b, b->stream); s2 != PABD_OK) return s2;
   if (b->grid_tiles == 0) return PABD_OK;
   struct Events {  // released on every path, failures included
     hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -1818,10 +1836,7 @@ pabd_status pabd_batch_tune(pabd_batch* b, int32_t flags, pabd_schedule* out) {
     b->tile_auto = false;
   }
   // 2. the flat path (its scenes depend on the tile size just chosen)
-  if (b->dirty) {
-    if ((st = batch_tables(b)) != PABD_OK) return st;
-    b->dirty = false;
-  }
+  if ((st = batch_refresh(b, b->stream)) != PABD_OK) return st;
   long long flat_contact = 0, flat_other = 0;
   for (const Slot& s : b->slots)
     if (s.used && !s.tiled) (s.contact ? flat_contact : flat_other) += s.n;
