@@ -404,7 +404,9 @@ struct pabd_scene {
   // the whole step in the resident kernel (bodies fit its LDS; not while the
   // residual of every iteration is recorded, which the flat kernels do)
   bool resident = false;
-  bool foreign = false;  // steps were enqueued on a caller's stream since the last read
+  // steps were enqueued on a caller's stream.  Never taken back: that stream may have
+  // been under capture, and the caller's graph replays them at any later time.
+  bool foreign = false;
   Graph graph;
   // releases what the handle holds, also after a create that failed part-way
   // (its own stream is drained first; work on callers' streams is the caller's)
@@ -529,7 +531,6 @@ pabd_status pabd_scene_read_state(pabd_scene* s, double* c, double* A, double* v
   if (!s) return fail(PABD_E_INVALID, "null scene");
   // steps on the handle's own stream precede the read there; others are waited for
   if (s->foreign) API_HIP(hipDeviceSynchronize());
-  s->foreign = false;
   int health = 0;
   pabd_status st = s->eng->read_bodies(0, s->hs.n, 0, c, A, v, w, &health, s->stream);
   if (st != PABD_OK) return st;
@@ -766,7 +767,7 @@ struct pabd_batch {
   Graph graph;
   int graph_steps = 0;  // steps one replay of the captured graph advances
   bool dirty = true;
-  bool foreign = false;  // steps were enqueued on a caller's stream since the last read
+  bool foreign = false;  // steps were enqueued on a caller's stream (pabd_scene::foreign)
   int grid_tiles = 0;
   bool any_stream = false, any_contact = false;
   int stream_kmax = 0, n_driven_hi = 0;
@@ -1296,8 +1297,7 @@ pabd_status pabd_batch_read_state(pabd_batch* b, int32_t slot, double* c, double
                                   double* w) {
   if (!b) return fail(PABD_E_INVALID, "null batch");
   if (slot < 0 || slot >= b->max_slots || !b->slots[slot].used) return fail(PABD_E_NOTFOUND, "slot not in use");
-  if (b->foreign) API_HIP(hipDeviceSynchronize());
-  b->foreign = false;
+  if (pabd_status st = wait_foreign(b); st != PABD_OK) return st;
   const Slot& s = b->slots[slot];
   int health = 0;
   pabd_status st = b->eng->read_bodies(s.boff, s.n, slot, c, A, v, w, &health, b->stream);

@@ -45,3 +45,23 @@ def test_scenes_come_and_go_under_steps_on_a_callers_stream(P, prec):
     for x, y in zip(run(None), run(st.cuda_stream)):
         for p, q in zip(x, y):
             assert np.array_equal(p, q)
+
+
+def test_a_read_waits_for_replays_of_a_callers_graph(P):
+    """Steps captured in a caller's graph: every read after a replay, the second and
+    later ones too, finds that replay's steps done."""
+    import torch
+    sc = S.chain(200, tilt_deg=30.0, precision=S.PREC_FP64)
+    want, g = P.Scene(sc), P.Scene(sc)
+    st = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(st), torch.cuda.graph(graph, stream=st):
+        g.step(100, stream=st.cuda_stream)
+    for _ in range(5):
+        with torch.cuda.stream(st):
+            graph.replay()
+        got = g.state()
+        want.step(100)
+        for p, q in zip(got, want.state()):
+            assert np.array_equal(p, q)
+        torch.zeros(1000, device="cuda").add_(1).sum().item()
