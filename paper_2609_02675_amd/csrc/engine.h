@@ -9,6 +9,7 @@
 #include <algorithm>
 #include <climits>
 #include <cstring>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -161,7 +162,10 @@ struct Engine {
   std::vector<void*> allocs;
   std::string err;
   DeviceAllocator dev = current_allocator();
-  // staged uploads: one pinned host buffer, one device buffer, grown on demand
+  // staged uploads: one pinned host buffer, one device buffer, grown on demand.
+  // State reads go through the pinned one too, and threads may read the scenes of one
+  // batch at the same time, so stage_mu is held from filling it to emptying it.
+  std::mutex stage_mu;
   char* h_stage = nullptr;
   char* d_stage = nullptr;
   size_t stage_cap = 0;
@@ -202,6 +206,7 @@ struct Engine {
     }
     if (segs.empty()) return PABD_OK;
     const size_t need = total + segs.size() * sizeof(Seg);
+    const std::lock_guard<std::mutex> lock(stage_mu);
     if (need > stage_cap) {
       size_t cap2 = std::max<size_t>(need, std::max<size_t>(2 * stage_cap, 1 << 20));
       if (h_stage) (void)hipHostFree(h_stage);

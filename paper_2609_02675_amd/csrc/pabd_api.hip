@@ -180,6 +180,7 @@ struct EngineT final : EngineBase {
   pabd_status read_bodies(int boff, int n, int slot, double* c, double* A, double* v, double* w, int* health,
                           hipStream_t st) override {
     const size_t N = (size_t)n, need = (18 * N + 1) * sizeof(double);
+    std::unique_lock<std::mutex> lock(e.stage_mu);
     if (n > 0 && e.h_stage && need <= e.stage_cap) {
       double* o = reinterpret_cast<double*>(e.h_stage);
       hipLaunchKernelGGL(k_read_state<T>, dim3((unsigned)((18 * N + 255) / 256)), dim3(256), 0, st, (const T*)e.qn,
@@ -193,6 +194,7 @@ struct EngineT final : EngineBase {
       *health = *reinterpret_cast<int*>(o + 18 * N);
       return PABD_OK;
     }
+    lock.unlock();
     // no staging buffer, or a smaller one: plain copies
     constexpr int QR = Rec<T>::Q;
     std::vector<T> q((size_t)QR * n), vl((size_t)VW * n);

@@ -71,3 +71,21 @@ def test_a_read_waits_for_steps_on_a_callers_stream(P):
         b.step(nsteps=50)
     for got in (g.state(), b.state(slot)):
         assert all(np.array_equal(p, q) for p, q in zip(got, ref))
+
+
+def test_threads_read_the_scenes_of_one_batch(P):
+    """Reads of different scenes at the same time: each returns its own scene."""
+    from concurrent.futures import ThreadPoolExecutor
+    scs = [_spread(n, S.PREC_FP64) for n in (400, 900, 1300, 700)]
+    b = P.Batch(len(scs), 1 << 27, S.PREC_FP64)
+    slots = [b.admit(s, 1) for s in scs]
+
+    def read(k):
+        for _ in range(100):
+            for x, y in zip(b.state(slots[k]), (scs[k].c0, scs[k].A0, scs[k].v0, scs[k].w0)):
+                if not np.array_equal(x, y):
+                    return False
+        return True
+
+    with ThreadPoolExecutor(len(scs)) as pool:
+        assert all(pool.map(read, range(len(scs))))
