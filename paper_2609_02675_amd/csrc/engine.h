@@ -11,6 +11,7 @@
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <tuple>
 #include <vector>
 
 #include "host_scene.h"
@@ -58,6 +59,19 @@ struct DeviceAllocator {
 inline DeviceAllocator& current_allocator() {
   static DeviceAllocator a;
   return a;
+}
+
+// A kernel launch by its own status: hipGetLastError would also report an error that
+// the caller left behind earlier.
+template <typename... P, typename... A>
+hipError_t launch(void (*kernel)(P...), dim3 grid, dim3 block, hipStream_t st, A... a) {
+  std::tuple<P...> args(static_cast<P>(a)...);
+  return std::apply(
+      [&](P&... p) {
+        void* ptr[] = {&p...};
+        return hipLaunchKernel(reinterpret_cast<const void*>(kernel), grid, block, ptr, 0, st);
+      },
+      args);
 }
 
 // one segment of a staged upload: bytes at src_off of the staging buffer go to dst
@@ -535,76 +549,53 @@ struct Engine {
   // nsteps steps of the plain scene in the resident kernels, after a contact scene's
   // contact construction (then nsteps is 1); general: it has variable bonds; n_ends: its
   // static bond ends
-  void launch_resident(bool contact, bool general, int n_ends, int n_driven, int ccap, int nsteps, hipStream_t st) {
+  hipError_t launch_resident(bool contact, bool general, int n_ends, int n_driven, int ccap, int nsteps,
+                             hipStream_t st) {
     const bool any_kind = general || n_driven > 0;
     if (!contact && !any_kind && cap.n <= ROWS_MAX) {
       const View<T> v = view();
-      if (cap.n <= 16)
-        hipLaunchKernelGGL((k_resident_rows<T, 64>), dim3(1), dim3(64), 0, st, v, cap.n, nsteps);
-      else if (cap.n <= 64)
-        hipLaunchKernelGGL((k_resident_rows<T, 256>), dim3(1), dim3(256), 0, st, v, cap.n, nsteps);
-      else if (cap.n <= 128)
-        hipLaunchKernelGGL((k_resident_rows<T, 512>), dim3(1), dim3(512), 0, st, v, cap.n, nsteps);
-      else if constexpr (sizeof(T) == 4)
-        hipLaunchKernelGGL((k_resident_rows<T, 1024>), dim3(1), dim3(1024), 0, st, v, cap.n, nsteps);
-      return;
+      if (cap.n <= 16) return launch(k_resident_rows<T, 64>, dim3(1), dim3(64), st, v, cap.n, nsteps);
+      if (cap.n <= 64) return launch(k_resident_rows<T, 256>, dim3(1), dim3(256), st, v, cap.n, nsteps);
+      if (cap.n <= 128) return launch(k_resident_rows<T, 512>, dim3(1), dim3(512), st, v, cap.n, nsteps);
+      if constexpr (sizeof(T) == 4)
+        return launch(k_resident_rows<T, 1024>, dim3(1), dim3(1024), st, v, cap.n, nsteps);
     }
     if (!contact && any_kind) {
       const int quads = std::max({4 * cap.n, n_ends, n_driven});
-      if (quads <= 64)
-        launch_ends_as<64>(general, n_ends, n_driven, nsteps, st);
-      else if (quads <= QUADS_MAX)
-        launch_ends_as<QUADS_MAX>(general, n_ends, n_driven, nsteps, st);
-      else if (cap.n <= 512)
-        launch_net_as<512>(general, n_ends, n_driven, nsteps, st);
-      else
-        launch_net_as<Resident<T>::NT>(general, n_ends, n_driven, nsteps, st);
-      return;
+      if (quads <= 64) return launch_ends_as<64>(general, n_ends, n_driven, nsteps, st);
+      if (quads <= QUADS_MAX) return launch_ends_as<QUADS_MAX>(general, n_ends, n_driven, nsteps, st);
+      if (cap.n <= 512) return launch_net_as<512>(general, n_ends, n_driven, nsteps, st);
+      return launch_net_as<Resident<T>::NT>(general, n_ends, n_driven, nsteps, st);
     }
     if (contact) {
-      if (cap.n <= 16)
-        launch_contact_as<64>(any_kind, n_driven, ccap, st);
-      else
-        launch_contact_as<256>(any_kind, n_driven, ccap, st);
-      return;
+      if (cap.n <= 16) return launch_contact_as<64>(any_kind, n_driven, ccap, st);
+      return launch_contact_as<256>(any_kind, n_driven, ccap, st);
     }
-    if (cap.n <= 256)
-      launch_joints_as<256>(nsteps, st);
-    else if (cap.n <= 512)
-      launch_joints_as<512>(nsteps, st);
-    else
-      launch_joints_as<Resident<T>::NT>(nsteps, st);
+    if (cap.n <= 256) return launch_joints_as<256>(nsteps, st);
+    if (cap.n <= 512) return launch_joints_as<512>(nsteps, st);
+    return launch_joints_as<Resident<T>::NT>(nsteps, st);
   }
   template <int NT>
-  void launch_ends_as(bool variable, int n_ends, int n_driven, int nsteps, hipStream_t st) {
-    const View<T> v = view();
+  hipError_t launch_ends_as(bool variable, int n_ends, int n_driven, int nsteps, hipStream_t st) {
     const DrivenTable dt{n_driven, drv_scene, drv_end_i, drv_end_j, drv_param, mass64};
-    if (variable)
-      hipLaunchKernelGGL((k_resident_ends<T, NT, true>), dim3(1), dim3(NT), 0, st, v, cap.n, n_ends, nsteps, dt);
-    else
-      hipLaunchKernelGGL((k_resident_ends<T, NT, false>), dim3(1), dim3(NT), 0, st, v, cap.n, n_ends, nsteps, dt);
+    return launch(variable ? k_resident_ends<T, NT, true> : k_resident_ends<T, NT, false>, dim3(1), dim3(NT), st,
+                  view(), cap.n, n_ends, nsteps, dt);
   }
   template <int NT>
-  void launch_net_as(bool variable, int n_ends, int n_driven, int nsteps, hipStream_t st) {
-    const View<T> v = view();
+  hipError_t launch_net_as(bool variable, int n_ends, int n_driven, int nsteps, hipStream_t st) {
     const DrivenTable dt{n_driven, drv_scene, drv_end_i, drv_end_j, drv_param, mass64};
-    if (variable)
-      hipLaunchKernelGGL((k_resident_net<T, NT, true>), dim3(1), dim3(NT), 0, st, v, cap.n, n_ends, nsteps, dt);
-    else
-      hipLaunchKernelGGL((k_resident_net<T, NT, false>), dim3(1), dim3(NT), 0, st, v, cap.n, n_ends, nsteps, dt);
+    return launch(variable ? k_resident_net<T, NT, true> : k_resident_net<T, NT, false>, dim3(1), dim3(NT), st, view(),
+                  cap.n, n_ends, nsteps, dt);
   }
   template <int NT>
-  void launch_contact_as(bool any_kind, int n_driven, int ccap, hipStream_t st) {
-    const View<T> v = view();
+  hipError_t launch_contact_as(bool any_kind, int n_driven, int ccap, hipStream_t st) {
     const DrivenTable dt{n_driven, drv_scene, drv_end_i, drv_end_j, drv_param, mass64};
-    if (any_kind)
-      hipLaunchKernelGGL((k_resident_contact<T, NT, true>), dim3(1), dim3(NT), 0, st, v, cap.n, ccap, dt);
-    else
-      hipLaunchKernelGGL((k_resident_contact<T, NT, false>), dim3(1), dim3(NT), 0, st, v, cap.n, ccap, dt);
+    return launch(any_kind ? k_resident_contact<T, NT, true> : k_resident_contact<T, NT, false>, dim3(1), dim3(NT), st,
+                  view(), cap.n, ccap, dt);
   }
   template <int NT>
-  void launch_joints_as(int nsteps, hipStream_t st) {
-    hipLaunchKernelGGL((k_resident_joints<T, NT>), dim3(1), dim3(NT), 0, st, view(), cap.n, nsteps);
+  hipError_t launch_joints_as(int nsteps, hipStream_t st) {
+    return launch(k_resident_joints<T, NT>, dim3(1), dim3(NT), st, view(), cap.n, nsteps);
   }
 
   // FP64 block factorisation of bodies [first, first + count)

@@ -52,8 +52,8 @@ struct EngineBase {
                          FlatWave* waves = nullptr, const int* n_waves = nullptr,
                          int wave_grid = 0) = 0;
   // nsteps steps of a plain scene that the resident kernels take (contact
-  // construction included)
-  virtual void resident_steps(const HostScene& hs, int nsteps, hipStream_t st) = 0;
+  // construction included); the status of the joint kernels' launch
+  virtual hipError_t resident_steps(const HostScene& hs, int nsteps, hipStream_t st) = 0;
   // the most bodies of a scene that one workgroup takes (a contact scene's bodies
   // take four lanes each)
   virtual bool resident(const HostScene& hs) const = 0;
@@ -116,16 +116,14 @@ struct EngineT final : EngineBase {
     e.launch_flat_step(n_scenes, kmax, contacts, ccap, n_driven, history, fin, st, waves, n_waves, wave_grid);
     e.cap.n = saved;
   }
-  void resident_steps(const HostScene& hs, int nsteps, hipStream_t st) override {
+  hipError_t resident_steps(const HostScene& hs, int nsteps, hipStream_t st) override {
     const int nd = (int)hs.drv_end_i.size();
-    if (!hs.contact) {
-      e.launch_resident(false, hs.variable, hs.ne, nd, 0, nsteps, st);
-      return;
-    }
-    for (int k = 0; k < nsteps; ++k) {
+    if (!hs.contact) return e.launch_resident(false, hs.variable, hs.ne, nd, 0, nsteps, st);
+    for (int k = 0; k < nsteps; ++k) {  // (callers look at hipGetLastError)
       e.launch_contacts(1, st);
-      e.launch_resident(true, hs.variable, hs.ne, nd, hs.ccap, 1, st);
+      (void)e.launch_resident(true, hs.variable, hs.ne, nd, hs.ccap, 1, st);
     }
+    return hipSuccess;
   }
   // A contact scene's limit is four waves, one per SIMD of the workgroup's compute
   // unit: with more, their instructions queue there, while the flat kernels spread
@@ -183,9 +181,9 @@ struct EngineT final : EngineBase {
     std::unique_lock<std::mutex> lock(e.stage_mu);
     if (n > 0 && e.h_stage && need <= e.stage_cap) {
       double* o = reinterpret_cast<double*>(e.h_stage);
-      hipLaunchKernelGGL(k_read_state<T>, dim3((unsigned)((18 * N + 255) / 256)), dim3(256), 0, st, (const T*)e.qn,
-                         (const T*)e.vel, (const int*)(e.health + slot), boff, n, o);
-      if (hipGetLastError() != hipSuccess || hipDeviceSynchronize() != hipSuccess)
+      if (launch(k_read_state<T>, dim3((unsigned)((18 * N + 255) / 256)), dim3(256), st, e.qn, e.vel,
+                 e.health + slot, boff, n, o) != hipSuccess ||
+          hipDeviceSynchronize() != hipSuccess)
         return fail(PABD_E_DEVICE, "state read failed");
       if (c) std::memcpy(c, o, 3 * N * sizeof(double));
       if (A) std::memcpy(A, o + 3 * N, 9 * N * sizeof(double));
@@ -492,7 +490,7 @@ pabd_status pabd_set_allocator(void* (*alloc)(size_t bytes, void* ctx), void (*r
 static void scene_enqueue_step(pabd_scene* s, hipStream_t st) {
   const HostScene& hs = s->hs;
   if (s->resident && !s->history) {
-    s->eng->resident_steps(hs, 1, st);
+    (void)s->eng->resident_steps(hs, 1, st);
     return;
   }
   s->eng->flat_step(0, std::max(1, hs.n), 1, hs.params.iters, hs.contact, hs.ccap,
@@ -507,9 +505,8 @@ pabd_status pabd_scene_step(pabd_scene* s, int32_t nsteps, void* hip_stream) {
   s->foreign = s->foreign || st != s->stream;
   if (s->resident && !s->hs.contact && !s->history) {
     // a launch takes several steps, so there is nothing to record
-    for (int k = 0; k < nsteps; k += PABD_MAX_STEPS_PER_LAUNCH)
-      s->eng->resident_steps(s->hs, std::min(nsteps - k, PABD_MAX_STEPS_PER_LAUNCH), st);
-    API_HIP(hipGetLastError());
+    for (int left = nsteps; left > 0; left -= PABD_MAX_STEPS_PER_LAUNCH)
+      API_HIP(s->eng->resident_steps(s->hs, std::min(left, PABD_MAX_STEPS_PER_LAUNCH), st));
     return PABD_OK;
   }
   if (!use_graphs() || s->history) {
@@ -2101,8 +2098,8 @@ pabd_status pabd_scene_run_noalloc(const pabd_scene_desc* desc, int32_t nsteps, 
   if (st != PABD_OK) return fail(st, eng->error());
   eng->factor(stream);
   if (resident) {
-    for (int k = 0; k < nsteps; k += PABD_MAX_STEPS_PER_LAUNCH)
-      eng->resident_steps(hs, std::min(nsteps - k, PABD_MAX_STEPS_PER_LAUNCH), stream);
+    for (int left = nsteps; left > 0; left -= PABD_MAX_STEPS_PER_LAUNCH)
+      (void)eng->resident_steps(hs, std::min(left, PABD_MAX_STEPS_PER_LAUNCH), stream);
   } else {
     for (int k = 0; k < nsteps && hs.n > 0; ++k)
       eng->flat_step(0, std::max(1, hs.n), 1, hs.params.iters, hs.contact, hs.ccap, (int)hs.drv_end_i.size(),

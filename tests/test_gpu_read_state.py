@@ -89,3 +89,20 @@ def test_threads_read_the_scenes_of_one_batch(P):
 
     with ThreadPoolExecutor(len(scs)) as pool:
         assert all(pool.map(read, range(len(scs))))
+
+
+@pytest.mark.parametrize("n", [8, 200, 1000])
+def test_an_error_the_caller_left_behind_is_not_this_calls(P, n):
+    """A caller's own failed HIP call does not fail the step or the read after it."""
+    sc = S.chain(n, tilt_deg=20.0, precision=S.PREC_FP32)
+    want, g = P.Scene(sc), P.Scene(sc)
+    want.step(4)
+    ref = want.state()
+    hip = _lib.lib()  # its symbols include those of the HIP runtime it is linked to
+    assert hip.hipSetDevice(9999) != 0
+    g.step(4)
+    assert hip.hipSetDevice(9999) != 0
+    got = g.state()
+    hip.hipGetLastError()
+    for p, q in zip(got, ref):
+        assert np.array_equal(p, q)
