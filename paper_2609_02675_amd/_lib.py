@@ -7,6 +7,7 @@ immediately when the built library is missing -- there is no fallback.
 from __future__ import annotations
 
 import ctypes as C
+import functools
 import os
 from typing import List, Optional
 
@@ -61,6 +62,15 @@ _d = _P(C.c_double)
 _i = _P(C.c_int32)
 
 
+class _Doubles:
+    """Argument type of a state array: what a pointer to double takes, or a void
+    pointer.  Other pointers and bare numbers are refused."""
+
+    @staticmethod
+    def from_param(x):
+        return x if isinstance(x, C.c_void_p) else _d.from_param(x)
+
+
 class _Schedule(C.Structure):
     _fields_ = [("tile_bodies", C.c_int32), ("contact_lanes", C.c_int32),
                 ("group_waves", C.c_int32), ("from_cache", C.c_int32)]
@@ -112,7 +122,7 @@ def lib():
     L.pabd_scene_create.argtypes = [_P(_Desc), _P(vp)]
     L.pabd_scene_destroy.argtypes = [vp]
     L.pabd_scene_step.argtypes = [vp, C.c_int32, vp]
-    L.pabd_scene_read_state.argtypes = [vp, vp, vp, vp, vp]
+    L.pabd_scene_read_state.argtypes = [vp, _Doubles, _Doubles, _Doubles, _Doubles]
     L.pabd_scene_residuals.argtypes = [vp, _d, C.c_int32, _i]
     L.pabd_scene_contacts.argtypes = [vp, C.c_int32, _i, _i, _i, _d, _d, _d, _d, _i]
     L.pabd_scene_bond_state.argtypes = [vp, _d, _d]
@@ -129,7 +139,7 @@ def lib():
     L.pabd_batch_step.argtypes = [vp, vp]
     L.pabd_batch_steps.argtypes = [vp, C.c_int32, vp]
     L.pabd_batch_poll.argtypes = [vp, _i, C.c_int32, _i]
-    L.pabd_batch_read_state.argtypes = [vp, C.c_int32, vp, vp, vp, vp]
+    L.pabd_batch_read_state.argtypes = [vp, C.c_int32, _Doubles, _Doubles, _Doubles, _Doubles]
     L.pabd_batch_residual.argtypes = [vp, C.c_int32, _d]
     L.pabd_batch_release.argtypes = [vp, C.c_int32]
     L.pabd_batch_steps_done.argtypes = [vp, C.c_int32, _i]
@@ -280,9 +290,26 @@ def _state_arrays(n):
 
 
 def _addresses(arrays):
-    """Addresses of the arrays' data (a tenth of the time of typed ctypes pointers,
-    which counts in a loop that reads thousands of scenes)."""
+    """Addresses of the arrays' data, for the state reads below."""
     return [a.__array_interface__["data"][0] for a in arrays]
+
+
+def _reader(name, *head):
+    """A state read that takes bare addresses: a tenth of the time of typed pointers,
+    which counts in a loop that reads thousands of scenes."""
+    fn = lib()[name]  # a function object of its own
+    fn.argtypes = [*head, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p]
+    return fn
+
+
+@functools.lru_cache(None)
+def _scene_reader():
+    return _reader("pabd_scene_read_state", C.c_void_p)
+
+
+@functools.lru_cache(None)
+def _batch_reader():
+    return _reader("pabd_batch_read_state", C.c_void_p, C.c_int32)
 
 
 def run_noalloc(scene: SceneDesc, nsteps: int, stream: Optional[int] = None):
@@ -325,7 +352,7 @@ class Scene:
 
     def state(self, check: bool = True):
         out = _state_arrays(self.n)
-        st = lib().pabd_scene_read_state(self._h, *_addresses(out))
+        st = _scene_reader()(self._h, *_addresses(out))
         if check:
             _check(st)
         return out
@@ -445,7 +472,7 @@ class Batch:
 
     def state(self, slot: int, check: bool = True):
         out = _state_arrays(self._n[slot])
-        st = lib().pabd_batch_read_state(self._h, int(slot), *_addresses(out))
+        st = _batch_reader()(self._h, int(slot), *_addresses(out))
         if check:
             _check(st)
         return out
