@@ -76,11 +76,13 @@ struct SceneDev {
 };
 
 // What a wavefront of the flat iteration works on: the bodies [first, first +
-// count) of one scene, lpb lanes each.
+// count) of one scene, CL lanes each when it has contacts, else one; or, one lane
+// each, of several neighbouring scenes without contacts (scene -1).
 struct FlatWave {
-  int first, count, lpb, contact;  // lpb: CL for a contact wave, else 1
-  int scene, ce0, ccap;            // contact slots: ccap per body from ce0, the first body's
-  int iters;                       // K, or 0 when the scene has no steps left: set every step
+  int first, count, contact;
+  int scene, ce0, ccap;  // contact slots: ccap per body from ce0, the first body's
+  int iters;             // K, or 0 when the scene has no steps left: set every step (INT_MAX for several scenes)
+  int pad;
 };
 
 // first contact slot of body i of scene S

@@ -420,22 +420,36 @@ __device__ __forceinline__ void solve_body(const T* fac, const T* s, const T* m,
 // across the lanes and records only for ends that exist, in fewer registers, so
 // that more waves hide one another's waits.
 //
+// MIXED: the lanes' bodies belong to several scenes (scene, K and sc are not given).
+// The scenes' entries are two more links, beside the first of the chain: nothing
+// waits for them before the ends (a wait ahead of everything took 2% more of a step).
+//
 // Measured (FP32, per step): a 1,000-box pile 0.251 -> 0.209 ms against the chain
 // of six links it had (scene id, scene, ranges, partner ids, records and states,
 // solve operands), a chain of 2,000 bodies 0.119 -> 0.103; the 125,000-block
 // pile, bound by the bytes of its records (4.5 TB/s), unchanged at 64 us an
 // iteration.
-template <typename T, bool CONTACT, int LPB, int U, bool EARLY>
-__device__ __forceinline__ void iterate_flat(const View<T>& v, const SceneDev& S, int k, int K, double* rh_num,
+template <typename T, bool CONTACT, int LPB, int U, bool EARLY, bool MIXED = false>
+__device__ __forceinline__ void iterate_flat(const View<T>& v, const SceneDev* scene, int k, int K, double* rh_num,
                                              double* rh_den, int i, int sub, size_t base, int ccap, int sc) {
   constexpr int QR = Rec<T>::Q, W = ContactRec<T>::W;
   const T* qs = v.q[k & 1];
   T* qd = v.q[(k + 1) & 1];
   T q[QR], s[QR], m[MW], fac[FW];
   double bb[10];
+  if constexpr (MIXED) {
+    sc = v.bscene[i];
+    scene = v.scenes + sc;
+  }
   const uint8_t flags = v.flags[i];
   const int e0 = v.srow[i], e1 = v.srow_end[i];
   load<T, QR>(qs + (size_t)QR * i, q);
+  const SceneDev& S = *scene;
+  bool live = true;  // this scene takes iteration k
+  if constexpr (MIXED) {
+    K = S.step < S.steps_total ? S.iters : 0;
+    live = k < K;
+  }
   int cnt = 0;
   int id[U];
   T C[U][W];
@@ -470,12 +484,12 @@ __device__ __forceinline__ void iterate_flat(const View<T>& v, const SceneDev& S
   bool refactor = false;
   Block dB{};  // contact and augmented part of H^k - H (this lane's ends)
   const bool var = (flags & F_VARIABLE) != 0;
-  const int eb = e0 + sub, ee = pinned ? eb : e1;
+  const int eb = e0 + sub, ee = pinned || !live ? eb : e1;
   // a wave with a body that has variable ends takes the general loop, any
   // other wave the quadratic loop (a divergent wave would run both loops one
   // after the other)
   auto state = [&](int j, T* qj) { load<T, QR>(qs + (size_t)QR * j, qj); };
-  if (wave_any(var && !pinned))
+  if (wave_any(var && !pinned && live))
     general_ends<T, LPB>(v, S, eb, ee, var, k == K - 1, q, state, rb, dB, refactor);
   else
     quadratic_ends<T, LPB>(v, eb, ee, q, state, rb);
@@ -524,6 +538,7 @@ __device__ __forceinline__ void iterate_flat(const View<T>& v, const SceneDev& S
     }
     refactored(bb, dB, fac);
   }
+  if (!live) return;
   if (pinned) {
     // a pinned body's residual shares stay zero (it never moves); written in
     // the first iteration, before the step's residual reduction reads them
@@ -594,15 +609,16 @@ __global__ void __launch_bounds__(256, (FlatBounds<T, EARLY>::WAVES)) k_iterate(
   const int t = (int)(blockIdx.x * blockDim.x + threadIdx.x);
   const int i = t / LPB, sub = t % LPB;
   if (i >= v.n) return;
-  iterate_flat<T, CONTACT, LPB, FlatRound<LPB, EARLY>::U, EARLY>(v, v.scenes[0], k, K, rh_num, rh_den, i, sub,
+  iterate_flat<T, CONTACT, LPB, FlatRound<LPB, EARLY>::U, EARLY>(v, v.scenes, k, K, rh_num, rh_den, i, sub,
                                                                (size_t)i * ccap, ccap, 0);
 }
 
 // The same iteration over a batch's table of wavefronts: a wave covers 64 / CL
 // bodies of a contact scene with CL lanes each (16 with the default four), or
-// 64 bodies of a contact-free scene with one lane each, and never spans two
-// scenes.  Waves past the table's count leave at once, so the grid can stay
-// fixed while scenes come and go.
+// 64 bodies without contacts with one lane each: of one scene, or, where the batch
+// holds many small ones (MIX_WAVES), of several, whose lanes look their scenes up.
+// Waves past the table's count leave at once, so the grid can stay fixed while
+// scenes come and go.
 template <typename T, int CL, bool EARLY>
 __global__ void __launch_bounds__(256, (FlatBounds<T, EARLY>::WAVES)) k_iterate_waves(View<T> v, int k,
                                                                                   const FlatWave* waves,
@@ -612,15 +628,19 @@ __global__ void __launch_bounds__(256, (FlatBounds<T, EARLY>::WAVES)) k_iterate_
   if (w >= *n_waves) return;
   const FlatWave fw = waves[w];
   if (k >= fw.iters) return;
-  const SceneDev& S = v.scenes[fw.scene];
   if (fw.contact) {
     const int b = l / CL;
     if (b >= fw.count) return;
-    iterate_flat<T, true, CL, FlatRound<CL, EARLY>::U, EARLY>(v, S, k, fw.iters, nullptr, nullptr, fw.first + b, l % CL,
+    iterate_flat<T, true, CL, FlatRound<CL, EARLY>::U, EARLY>(v, v.scenes + fw.scene, k, fw.iters, nullptr, nullptr,
+                                                            fw.first + b, l % CL,
                                                             (size_t)fw.ce0 + (size_t)b * fw.ccap, fw.ccap, fw.scene);
   } else {
     if (l >= fw.count) return;
-    iterate_flat<T, false, 1, 1, EARLY>(v, S, k, fw.iters, nullptr, nullptr, fw.first + l, 0, 0, 0, fw.scene);
+    if (fw.scene >= 0)
+      iterate_flat<T, false, 1, 1, EARLY>(v, v.scenes + fw.scene, k, fw.iters, nullptr, nullptr, fw.first + l, 0, 0, 0,
+                                          fw.scene);
+    else
+      iterate_flat<T, false, 1, 1, EARLY, true>(v, nullptr, k, 0, nullptr, nullptr, fw.first + l, 0, 0, 0, 0);
   }
 }
 

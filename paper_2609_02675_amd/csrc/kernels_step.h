@@ -57,7 +57,7 @@ __device__ __forceinline__ void predict_body(const View<T>& v, int i) {
 // the iterations of wave w of a batch's table in this step: a scene that has
 // taken its steps iterates no more
 __device__ __forceinline__ void arm_wave(const SceneDev* scenes, FlatWave* waves, const int* n_waves, int w) {
-  if (!waves || w >= *n_waves) return;
+  if (!waves || w >= *n_waves || waves[w].scene < 0) return;
   const SceneDev& S = scenes[waves[w].scene];
   waves[w].iters = S.step < S.steps_total ? S.iters : 0;
 }

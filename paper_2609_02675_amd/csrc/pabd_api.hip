@@ -824,6 +824,52 @@ pabd_status wait_foreign(const pabd_batch* b) {
   return PABD_OK;
 }
 
+// Beyond this many waves, a batch's scenes without contacts on the flat path share
+// waves, 64 bodies each whatever their scenes; up to it each scene has waves of its
+// own.  A shared wave waits for its lanes' scene entries as well, own waves leave most
+// lanes of a small scene or of a scene's last wave idle.  Us per step, own against
+// shared: linkages of four bodies 139 and 136 at 256 waves, 161 and 137 at 384, 209 and
+// 140 at 1,024 (FP64 152 and 150, 178 and 150, 232 and 154; 501 and 190 at 4,096);
+// chains of 65, of two waves each, 85 and 87 at 256, 95 and 92 at 512, 211 and 148 at
+// 2,048; augmented chains of 19 63 and 64 at 256, 70 and 73 at 1,024, 141 and 130 at
+// 4,096.
+constexpr int MIX_WAVES = 256;
+
+// Flat-path waves: a contact scene's bodies take contact_lanes lanes each (64 /
+// contact_lanes per wave), any other scene's one lane each (64 per wave).
+std::vector<FlatWave> flat_waves(const pabd_batch* b) {
+  std::vector<FlatWave> waves;
+  std::vector<const Slot*> flat;
+  int own = 0;  // waves of the scenes without contacts if none share
+  for (const Slot& s : b->slots)
+    if (s.used && !s.tiled && s.n > 0) {
+      flat.push_back(&s);
+      if (!s.contact) own += (s.n + 63) / 64;
+    }
+  std::sort(flat.begin(), flat.end(), [](const Slot* x, const Slot* y) { return x->boff < y->boff; });
+  const bool mix = own > MIX_WAVES;
+  bool open = false;  // the last wave may take the next scene's first bodies
+  for (const Slot* s : flat) {
+    const int per = 64 / (s->contact ? b->contact_lanes : 1), cc = s->contact ? s->hs->ccap : 0;
+    const int scene = (int)(s - b->slots.data());
+    int f = 0;
+    if (mix && open && !s->contact) {
+      FlatWave& w = waves.back();
+      if (w.count < 64 && w.first + w.count == s->boff) {
+        f = std::min(64 - w.count, s->n);
+        w.count += f;
+        w.scene = -1;
+        w.iters = INT_MAX;
+      }
+    }
+    for (; f < s->n; f += per)
+      waves.push_back(FlatWave{s->boff + f, std::min(per, s->n - f), s->contact ? 1 : 0, scene, s->coff + f * cc, cc,
+                               0, 0});
+    open = !s->contact;
+  }
+  return waves;
+}
+
 // rebuild the device tables; nothing may be stepping (wait_foreign)
 pabd_status batch_tables(pabd_batch* b) {
   // the device tile table from the host tiles
@@ -874,24 +920,8 @@ pabd_status batch_tables(pabd_batch* b) {
     b->stream_kmax = std::max(b->stream_kmax, s.iters);
   }
   auto round_up = [](int x, int q, int cap) { return std::min(cap, (x + q - 1) / q * q); };
-  // flat-path waves: a contact scene's bodies take contact_lanes lanes each (64 /
-  // contact_lanes per wave), any other scene's one lane each (64 per wave); a wave
-  // stays within one scene
   b->eng->set_schedule(b->contact_lanes, b->group_waves);
-  std::vector<FlatWave> waves;
-  if (b->any_stream) {
-    std::vector<const Slot*> flat;
-    for (const Slot& s : b->slots)
-      if (s.used && !s.tiled && s.n > 0) flat.push_back(&s);
-    std::sort(flat.begin(), flat.end(), [](const Slot* x, const Slot* y) { return x->boff < y->boff; });
-    for (const Slot* s : flat) {
-      const int lpb = s->contact ? b->contact_lanes : 1, per = 64 / lpb, cc = s->contact ? s->hs->ccap : 0;
-      const int scene = (int)(s - b->slots.data());
-      for (int f = 0; f < s->n; f += per)
-        waves.push_back(FlatWave{s->boff + f, std::min(per, s->n - f), lpb, s->contact ? 1 : 0, scene,
-                                 s->coff + f * cc, cc, 0});
-    }
-  }
+  const std::vector<FlatWave> waves = flat_waves(b);
   const int nw = (int)waves.size();
   if (b->any_stream) {
     if (nw > b->wave_table_cap || !b->d_waves) {
