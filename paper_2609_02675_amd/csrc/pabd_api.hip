@@ -137,17 +137,21 @@ struct EngineT final : EngineBase {
     if (hs.contact) return hs.n <= 64;
     return hs.n <= Resident<T>::NT && (!(hs.variable || hs.driven) || hs.ne <= NET_ENDS<T>);
   }
-  // At most this many tiles (three workgroups per compute unit in FP32, two in FP64,
-  // by registers) take the kernel with a quad of lanes per body; beyond it the
-  // quads' idle lanes cost more issue slots than the shorter chains save.  Us per
-  // step of 64-body tiles (K = 20), one lane per body against quads: FP32 20.1
-  // against 14.4 at 9 tiles, 23.1 against 16.7 at 290, 23.7 against 19.6 at 735,
-  // 23.6 against 30.2 at 1,000; FP64 26.4 against 21.5 at 9, 29.4 against 24.3 at
-  // 151, 31.1 against 31.2 at 506, 32.3 against 47.1 at 735.
-  static constexpr int ROWS_TILES = sizeof(T) == 4 ? 768 : 512;
+  // At most this many tiles take the kernel with a quad of lanes per body: what fits
+  // the chip at once by registers, three waves per SIMD in FP32 and two in FP64, so
+  // for each compute unit three (two) tiles of 64 bodies but one of 128, whose eight
+  // waves take two of a SIMD's places.  Beyond it the launch runs in rounds of whole
+  // step sequences, while one lane per body still holds every tile.  Us per step (K =
+  // 20), one lane per body against quads:
+  //   64 bodies   FP32 20.9 and 15.7 at 256 tiles, 23.1 and 20.0 at 768, 23.5 and 31.4 at
+  //               1,024; FP64 26.6 and 22.9 at 256, 28.9 and 29.6 at 512, 29.6 and 45.5 at 768
+  //   128 bodies  FP32 24.1 and 18.2 at 256, 25.3 and 34.9 at 512, 25.7 and 51.6 at 768;
+  //               FP64 29.7 and 29.5 at 256, 33.0 and 56.2 at 512
+  //   32 bodies   FP32 22.6 and 16.3 at 768; FP64 28.0 and 27.1 at 512
+  static constexpr int rows_tiles(int tb) { return tb == 128 ? 256 : (sizeof(T) == 4 ? 768 : 512); }
   void tile_step(int tb, const TileTable& tt, int grid, int nsteps, hipStream_t st) override {
     View<T> v = e.view();
-    if (tb <= 128 && grid <= ROWS_TILES) {
+    if (tb <= 128 && grid <= rows_tiles(tb)) {
       if (tb == 32)
         hipLaunchKernelGGL((k_tile_rows<T, 32>), dim3(grid), dim3(128), 0, st, v, tt, nsteps);
       else if (tb == 64)
