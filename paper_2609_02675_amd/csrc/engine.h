@@ -538,6 +538,22 @@ struct Engine {
   // whose rows need more than the 128 registers that 1,024 leave (chain of 200, us
   // per step: FP32 27 with one lane per body, 20 with quads).
   static constexpr int ROWS_MAX = sizeof(T) == 4 ? 256 : 128;
+  // Bodies of a contact scene, four lanes each, that one workgroup takes: with joints
+  // of any kind or quadratic ones alone.  The contact construction apart, a step of the
+  // flat kernels costs its 20 to 30 launches however few contacts there are; one of a
+  // workgroup grows with the contacts, whose waves queue for the one compute unit.  Us
+  // per step (K = 20 for chains and robots, 30 for boxes), flat against one workgroup:
+  //   FP32, quadratic  128 boxes in the air 96 and 51, in heaps 180..232 and 143..203;
+  //                    chain of 100 on the ground 103 and 73; 128 small spheres that sink
+  //                    into each other 297..485 and 291..469.  With twelve waves (one
+  //                    contact a lane in registers) 192 boxes in the air 97 and 55, but
+  //                    192 spheres 292..548 and 317..579
+  //   FP32, any kind   13-body robots with driven joints, 70 bodies in the air 110 and 92,
+  //                    126 on the ground 254..271 and 244..282
+  //   FP64, quadratic  100 boxes in the air 113 and 59, 128 in heaps 226..301 and 176..265
+  //   FP64, any kind   98 and 126 bodies of robots 253..303 and 245..332
+  static constexpr int CONTACT_ANY_MAX = sizeof(T) == 4 ? 128 : 64;
+  static constexpr int CONTACT_QUADRATIC_MAX = 128;
   // Scenes with variable or driven bonds up to this many quads, ends and driven
   // bonds take a quad of lanes per body to add the ends and solve (k_resident_ends),
   // larger ones one lane per body (k_resident_net): up to four waves each have a
@@ -569,27 +585,34 @@ struct Engine {
     }
     if (contact) {
       if (cap.n <= 16) return launch_contact_as<64>(any_kind, n_driven, ccap, st);
-      return launch_contact_as<256>(any_kind, n_driven, ccap, st);
+      if (cap.n <= 64) return launch_contact_as<256>(any_kind, n_driven, ccap, st);
+      if constexpr (sizeof(T) == 4)
+        return launch_contact_as<512>(any_kind, n_driven, ccap, st);
+      else
+        return launch(k_resident_contact<T, 512, false>, dim3(1), dim3(512), st, view(), cap.n, ccap, driven_table(0));
     }
     if (cap.n <= 256) return launch_joints_as<256>(nsteps, st);
     if (cap.n <= 512) return launch_joints_as<512>(nsteps, st);
     return launch_joints_as<Resident<T>::NT>(nsteps, st);
   }
+  DrivenTable driven_table(int n_driven) const {
+    return DrivenTable{n_driven, drv_scene, drv_end_i, drv_end_j, drv_param, mass64};
+  }
   template <int NT>
   hipError_t launch_ends_as(bool variable, int n_ends, int n_driven, int nsteps, hipStream_t st) {
-    const DrivenTable dt{n_driven, drv_scene, drv_end_i, drv_end_j, drv_param, mass64};
+    const DrivenTable dt = driven_table(n_driven);
     return launch(variable ? k_resident_ends<T, NT, true> : k_resident_ends<T, NT, false>, dim3(1), dim3(NT), st,
                   view(), cap.n, n_ends, nsteps, dt);
   }
   template <int NT>
   hipError_t launch_net_as(bool variable, int n_ends, int n_driven, int nsteps, hipStream_t st) {
-    const DrivenTable dt{n_driven, drv_scene, drv_end_i, drv_end_j, drv_param, mass64};
+    const DrivenTable dt = driven_table(n_driven);
     return launch(variable ? k_resident_net<T, NT, true> : k_resident_net<T, NT, false>, dim3(1), dim3(NT), st, view(),
                   cap.n, n_ends, nsteps, dt);
   }
   template <int NT>
   hipError_t launch_contact_as(bool any_kind, int n_driven, int ccap, hipStream_t st) {
-    const DrivenTable dt{n_driven, drv_scene, drv_end_i, drv_end_j, drv_param, mass64};
+    const DrivenTable dt = driven_table(n_driven);
     return launch(any_kind ? k_resident_contact<T, NT, true> : k_resident_contact<T, NT, false>, dim3(1), dim3(NT), st,
                   view(), cap.n, ccap, dt);
   }

@@ -18,9 +18,9 @@
 //
 // What bounds them: the latency of one iteration (a barrier or two, the LDS round
 // trip of a partner's state, the dependent arithmetic of its ends, block solve and
-// rotation), not any throughput; the contact kernel with more than four
-// waves is bound by their instruction issue on the one compute unit, so larger
-// piles take the flat kernels (EngineT::resident).
+// rotation), not any throughput; the contact kernel with many waves and contacts is
+// bound by their instruction issue on the one compute unit, so larger piles take the
+// flat kernels (EngineT::resident).
 //
 // Measured per step, against one kernel that read records, masses, factors and the
 // scene from memory in every iteration behind barriers of 16 waves (and took a
@@ -467,12 +467,15 @@ __global__ void __launch_bounds__(NT) k_resident_net(View<T> v, int n, int n_end
 }
 
 // One step of a contact scene of at most NT / 4 bodies.  Thread t forms the terms
-// of ends t % 4, t % 4 + 4, ... of body t / 4 (the first two of them held in
+// of ends t % 4, t % 4 + 4, ... of body t / 4 (the first U contacts of them held in
 // registers through the step) and the four lanes' sum goes to LDS; then thread
-// b solves body b, with full waves instead of every fourth lane.
+// b solves body b, with full waves instead of every fourth lane.  U is two, or one
+// where two waves share a SIMD's registers in FP64 (a heap of 100 boxes, us per step: 260
+// with two, which spill 184 bytes a lane, 193 with one and no spills).
 template <typename T, int NT, bool GENERAL>
 __global__ void __launch_bounds__(NT) k_resident_contact(View<T> v, int n, int ccap, DrivenTable dt) {
-  constexpr int QR = Rec<T>::Q, W = ContactRec<T>::W, NB = NT / 4, U = 2;
+  constexpr int QR = Rec<T>::Q, W = ContactRec<T>::W, NB = NT / 4;
+  constexpr int U = sizeof(T) == 8 && NT > 256 ? 1 : 2;
   using Q = Plane<T, QR, NB>;
   using M = Plane<T, MW, NB>;
   using F = Plane<T, FW, NB>;

@@ -54,8 +54,7 @@ struct EngineBase {
   // nsteps steps of a plain scene that the resident kernels take (contact
   // construction included); the status of the joint kernels' launch
   virtual hipError_t resident_steps(const HostScene& hs, int nsteps, hipStream_t st) = 0;
-  // the most bodies of a scene that one workgroup takes (a contact scene's bodies
-  // take four lanes each)
+  // whether one workgroup takes the plain scene's whole steps
   virtual bool resident(const HostScene& hs) const = 0;
   virtual void tile_step(int tile_bodies, const TileTable& tt, int grid, int nsteps,
                          hipStream_t st) = 0;
@@ -125,17 +124,14 @@ struct EngineT final : EngineBase {
     }
     return hipSuccess;
   }
-  // A contact scene's limit is four waves, one per SIMD of the workgroup's compute
-  // unit: with more, their instructions queue there, while the flat kernels spread
-  // them over the chip (steps of piles, resident against flat: 120 boxes 0.181
-  // against 0.167 ms, 200 boxes 0.222 against 0.180).  Joint scenes gain from one
-  // workgroup at every size it holds (chain of 500 0.043 against 0.093 ms, of
-  // 1,000 0.088 against 0.097).
-  // The ends of variable and driven joints have to fit LDS.
+  // Joint scenes gain from one workgroup at every size it holds (chain of 500 0.043
+  // against 0.093 ms, of 1,000 0.088 against 0.097); the ends of variable and driven
+  // joints have to fit LDS.
   bool resident(const HostScene& hs) const override {
     if (hs.n == 0) return false;
-    if (hs.contact) return hs.n <= 64;
-    return hs.n <= Resident<T>::NT && (!(hs.variable || hs.driven) || hs.ne <= NET_ENDS<T>);
+    const bool any_kind = hs.variable || hs.driven;
+    if (hs.contact) return hs.n <= (any_kind ? Engine<T>::CONTACT_ANY_MAX : Engine<T>::CONTACT_QUADRATIC_MAX);
+    return hs.n <= Resident<T>::NT && (!any_kind || hs.ne <= NET_ENDS<T>);
   }
   // At most this many tiles take the kernel with a quad of lanes per body: what fits
   // the chip at once by registers, three waves per SIMD in FP32 and two in FP64, so
