@@ -19,7 +19,7 @@ struct Eps;
 // polar iteration ends (the error left is below polar_tol2 / 2); polar_e_one /
 // polar_e_two: det X_1 - 1 after the first step up to which one / two further
 // steps leave that same error (sqrt(tol) and (4 tol)^(1/4), rounded down for the
-// rounding of the determinant); polar_e_three, in FP64 alone: up to which three do
+// rounding of the determinant); polar_e_three: up to which three do, in FP64 alone
 // ((64 tol)^(1/8))
 template <>
 struct Eps<float> {
@@ -27,6 +27,7 @@ struct Eps<float> {
   static constexpr float det_floor = 1e-6f;
   static constexpr float polar_e_one = 3.1e-4f;
   static constexpr float polar_e_two = 2.5e-2f;
+  static constexpr float polar_e_three = polar_e_two;
 };
 template <>
 struct Eps<double> {
@@ -307,16 +308,17 @@ __device__ __forceinline__ bool polar_fast(T* X, bool* ok_out) {
   const T det1 = cofactor(X, C1);
   const T e = fma(sigma * sigma * sigma, det1, (T)-1);
   const bool one = ok && unscaled && e <= Eps<T>::polar_e_one;
-  bool three = false;
-  if constexpr (sizeof(T) == 8) three = ok && unscaled && e > Eps<T>::polar_e_two && e <= Eps<T>::polar_e_three;
-  const bool two = three || (ok && unscaled && !one && e <= Eps<T>::polar_e_two);
+  const bool two = ok && unscaled && !one && e <= Eps<T>::polar_e_three;
   const T g1 = one || two ? rcp(sigma * sigma * det1) : (T)0;
   sigma = one || two ? (T)0.5 * sigma : sigma;
 #pragma unroll
   for (int k = 0; k < 9; ++k) X[k] = fma(g1, C1[k], X[k]);
-  if (wave_any(two)) polar_newton_plain<T>(X, &sigma, two);
-  if constexpr (sizeof(T) == 8) {
-    if (wave_any(three)) polar_newton_plain<T>(X, &sigma, three);
+  if (wave_any(two)) {
+    polar_newton_plain<T>(X, &sigma, two);
+    if constexpr (sizeof(T) == 8) {
+      const bool three = two && e > Eps<T>::polar_e_two;
+      if (wave_any(three)) polar_newton_plain<T>(X, &sigma, three);
+    }
   }
 #pragma unroll
   for (int k = 0; k < 9; ++k) X[k] *= sigma;

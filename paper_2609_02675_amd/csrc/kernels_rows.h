@@ -117,16 +117,17 @@ __device__ __forceinline__ void polar_rows(T* x, int k, unsigned* counts, int bo
   const T det1 = cofactor_row(x, C1);
   const T e = fma(sigma * sigma * sigma, det1, (T)-1);
   const bool one = ok && unscaled && e <= Eps<T>::polar_e_one;
-  bool three = false;
-  if constexpr (sizeof(T) == 8) three = ok && unscaled && e > Eps<T>::polar_e_two && e <= Eps<T>::polar_e_three;
-  const bool two = three || (ok && unscaled && !one && e <= Eps<T>::polar_e_two);
+  const bool two = ok && unscaled && !one && e <= Eps<T>::polar_e_three;
   const T g1 = one || two ? rcp(sigma * sigma * det1) : (T)0;
   sigma = one || two ? (T)0.5 * sigma : sigma;
 #pragma unroll
   for (int c = 0; c < 3; ++c) x[c] = fma(g1, C1[c], x[c]);
-  if (wave_any(two)) polar_plain_row(x, &sigma, two);
-  if constexpr (sizeof(T) == 8) {
-    if (wave_any(three)) polar_plain_row(x, &sigma, three);
+  if (wave_any(two)) {
+    polar_plain_row(x, &sigma, two);
+    if constexpr (sizeof(T) == 8) {
+      const bool three = two && e > Eps<T>::polar_e_two;
+      if (wave_any(three)) polar_plain_row(x, &sigma, three);
+    }
   }
 #pragma unroll
   for (int c = 0; c < 3; ++c) x[c] *= sigma;
