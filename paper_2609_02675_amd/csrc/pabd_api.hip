@@ -133,18 +133,30 @@ struct EngineT final : EngineBase {
     if (hs.contact) return hs.n <= (any_kind ? Engine<T>::CONTACT_ANY_MAX : Engine<T>::CONTACT_QUADRATIC_MAX);
     return hs.n <= Resident<T>::NT && (!any_kind || hs.ne <= NET_ENDS<T>);
   }
-  // At most this many tiles take the kernel with a quad of lanes per body: what fits
-  // the chip at once by registers, three waves per SIMD in FP32 and two in FP64, so
-  // for each compute unit three (two) tiles of 64 bodies but one of 128, whose eight
-  // waves take two of a SIMD's places.  Beyond it the launch runs in rounds of whole
-  // step sequences, while one lane per body still holds every tile.  Us per step (K =
-  // 20), one lane per body against quads:
-  //   64 bodies   FP32 20.9 and 15.7 at 256 tiles, 23.1 and 20.0 at 768, 23.5 and 31.4 at
-  //               1,024; FP64 26.6 and 22.9 at 256, 28.9 and 29.6 at 512, 29.6 and 45.5 at 768
-  //   128 bodies  FP32 24.1 and 18.2 at 256, 25.3 and 34.9 at 512, 25.7 and 51.6 at 768;
-  //               FP64 29.7 and 29.5 at 256, 33.0 and 56.2 at 512
-  //   32 bodies   FP32 22.6 and 16.3 at 768; FP64 28.0 and 27.1 at 512
-  static constexpr int rows_tiles(int tb) { return tb == 128 ? 256 : (sizeof(T) == 4 ? 768 : 512); }
+  // At most this many tiles take the kernel with a quad of lanes per body.  In FP32 they
+  // are what fits the chip at once by registers, three waves per SIMD: for each compute
+  // unit three tiles of 64 bodies but one of 128, whose eight waves take two of a SIMD's
+  // places; beyond it the launch runs in rounds of whole step sequences, while one lane
+  // per body still holds every tile.  In FP64 a second tile on a compute unit queues for
+  // its FP64 rate, so it is one tile of 64 there, and none of 128, whose waves share
+  // the SIMDs already.  Us per step (K = 20), one lane per body against quads, chains
+  // of a tile's size and, for little arithmetic, pairs joined by a spring, 64 steps a
+  // launch unless said:
+  //   FP32, 64 bodies   chains 20.1 and 14.6 at 256 tiles, 21.8 and 17.7 at 750, 23.5 and
+  //                     31.4 at 1,024; pairs 18.2 and 16.8 at 750
+  //   FP32, 128 bodies  chains 22.8 and 15.8 at 256, 25.3 and 34.9 at 512; pairs 18.8 and
+  //                     14.9 at 256
+  //   FP32, 32 bodies   chains 21.8 and 15.1 at 750; pairs 18.2 and 14.7
+  //   FP64, 64 bodies   chains 25.1 and 20.4 at 256, 26.6 and 26.3 at 512 (39.2 and 41.9 a
+  //                     step a launch); pairs 20.2 and 17.6 at 256, 32.0 and 37.6 at 512
+  //                     a step a launch
+  //   FP64, 128 bodies  chains 27.6 and 25.5 at 64 (38.5 and 38.8 a step a launch); pairs
+  //                     22.4 and 23.6 (32.3 and 36.6)
+  //   FP64, 32 bodies   chains 30.5 and 19.9 at 256, 37.4 and 38.0 at 512 a step a launch
+  static constexpr int rows_tiles(int tb) {
+    if (sizeof(T) == 8) return tb == 128 ? 0 : 256;
+    return tb == 128 ? 256 : 768;
+  }
   void tile_step(int tb, const TileTable& tt, int grid, int nsteps, hipStream_t st) override {
     View<T> v = e.view();
     if (tb <= 128 && grid <= rows_tiles(tb)) {
@@ -152,7 +164,7 @@ struct EngineT final : EngineBase {
         hipLaunchKernelGGL((k_tile_rows<T, 32>), dim3(grid), dim3(128), 0, st, v, tt, nsteps);
       else if (tb == 64)
         hipLaunchKernelGGL((k_tile_rows<T, 64>), dim3(grid), dim3(256), 0, st, v, tt, nsteps);
-      else
+      else if constexpr (rows_tiles(128) > 0)
         hipLaunchKernelGGL((k_tile_rows<T, 128>), dim3(grid), dim3(512), 0, st, v, tt, nsteps);
       return;
     }
