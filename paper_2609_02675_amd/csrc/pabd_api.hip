@@ -138,8 +138,7 @@ struct EngineT final : EngineBase {
   // unit three tiles of 64 bodies but one of 128, whose eight waves take two of a SIMD's
   // places; beyond it the launch runs in rounds of whole step sequences, while one lane
   // per body still holds every tile.  In FP64 a second tile on a compute unit queues for
-  // its FP64 rate, so it is one tile of 64 there, and none of 128, whose waves share
-  // the SIMDs already.  Us per step (K = 20), one lane per body against quads, chains
+  // its FP64 rate, so they are one tile for each.  Us per step (K = 20), one lane per body against quads, chains
   // of a tile's size and, for little arithmetic, pairs joined by a spring, 64 steps a
   // launch unless said:
   //   FP32, 64 bodies   chains 20.1 and 14.6 at 256 tiles, 21.8 and 17.7 at 750, 23.5 and
@@ -150,13 +149,11 @@ struct EngineT final : EngineBase {
   //   FP64, 64 bodies   chains 25.1 and 20.4 at 256, 26.6 and 26.3 at 512 (39.2 and 41.9 a
   //                     step a launch); pairs 20.2 and 17.6 at 256, 32.0 and 37.6 at 512
   //                     a step a launch
-  //   FP64, 128 bodies  chains 27.6 and 25.5 at 64 (38.5 and 38.8 a step a launch); pairs
-  //                     22.4 and 23.6 (32.3 and 36.6)
+  //   FP64, 128 bodies  chains 27.6 and 25.8 at 256 (40.4 and 42.7 a step a launch), 33.0
+  //                     and 56.2 at 512; 5 x 5 x 5 lattices 68.6 and 62.7 at 256; only
+  //                     scenes of little arithmetic lose, pairs 22.5 and 23.6
   //   FP64, 32 bodies   chains 30.5 and 19.9 at 256, 37.4 and 38.0 at 512 a step a launch
-  static constexpr int rows_tiles(int tb) {
-    if (sizeof(T) == 8) return tb == 128 ? 0 : 256;
-    return tb == 128 ? 256 : 768;
-  }
+  static constexpr int rows_tiles(int tb) { return sizeof(T) == 8 || tb == 128 ? 256 : 768; }
   void tile_step(int tb, const TileTable& tt, int grid, int nsteps, hipStream_t st) override {
     View<T> v = e.view();
     if (tb <= 128 && grid <= rows_tiles(tb)) {
@@ -164,7 +161,7 @@ struct EngineT final : EngineBase {
         hipLaunchKernelGGL((k_tile_rows<T, 32>), dim3(grid), dim3(128), 0, st, v, tt, nsteps);
       else if (tb == 64)
         hipLaunchKernelGGL((k_tile_rows<T, 64>), dim3(grid), dim3(256), 0, st, v, tt, nsteps);
-      else if constexpr (rows_tiles(128) > 0)
+      else
         hipLaunchKernelGGL((k_tile_rows<T, 128>), dim3(grid), dim3(512), 0, st, v, tt, nsteps);
       return;
     }
