@@ -492,16 +492,15 @@ struct Engine {
 
   static dim3 grid_for(int n, int bs) { return dim3((unsigned)std::max(1, (n + bs - 1) / bs)); }
 
-  // contact-bond construction for every contact scene among the bodies
-  // [0, min(cap.n, contact bodies))
   // a single contact scene of at most this many bodies takes the all-pairs search
   // (at most 2,080 pairs of tiles)
   static constexpr int BRUTE_MAX = 2048;
   // beyond this many bodies the sort's workgroups hold four waves (fewer to dispatch);
   // below it one, over as many compute units as there are bodies
   static constexpr int SORT_WIDE = 4096;
-  // predict: the prep kernel also runs the step's prediction for the bodies
-  // [0, min(cap.n, contact bodies))
+  // contact-bond construction for every contact scene among the bodies
+  // [0, min(cap.n, contact bodies)); predict: the prep kernel also runs the step's
+  // prediction for them
   void launch_contacts(int n_scenes, hipStream_t st, bool predict = false, FlatWave* waves = nullptr,
                        const int* n_waves = nullptr) {
     View<T> v = view();
@@ -516,7 +515,7 @@ struct Engine {
     if (brute) {
       const int tiles = (n + BRUTE_TILE - 1) / BRUTE_TILE, tile_pairs = tiles * (tiles + 1) / 2;
       hipLaunchKernelGGL(k_contacts_brute<T>, dim3((unsigned)std::max(1, tile_pairs + (n + 31) / 32)), dim3(256), 0, st, v, cb,
-                         0, n, tile_pairs);
+                         n, tile_pairs);
     } else {
       hipLaunchKernelGGL(k_contact_reach<T>, grid_for(n, 256), dim3(256), 0, st, v, cb);
       hipLaunchKernelGGL(k_contact_cells, grid_for(n_scenes, 64), dim3(64), 0, st, scenes, n_scenes,
@@ -591,12 +590,14 @@ struct Engine {
       else
         return launch(k_resident_contact<T, 512, false>, dim3(1), dim3(512), st, view(), cap.n, ccap, driven_table(0));
     }
-    if (cap.n <= 256) return launch_joints_as<256>(nsteps, st);
+    if constexpr (ROWS_MAX < 256) {
+      if (cap.n <= 256) return launch_joints_as<256>(nsteps, st);
+    }
     if (cap.n <= 512) return launch_joints_as<512>(nsteps, st);
     return launch_joints_as<Resident<T>::NT>(nsteps, st);
   }
   DrivenTable driven_table(int n_driven) const {
-    return DrivenTable{n_driven, drv_scene, drv_end_i, drv_end_j, drv_param, mass64};
+    return DrivenTable{n_driven, drv_end_i, drv_end_j, drv_param, mass64};
   }
   template <int NT>
   hipError_t launch_ends_as(bool variable, int n_ends, int n_driven, int nsteps, hipStream_t st) {

@@ -20,9 +20,9 @@
 //                    reach and the upper edge of the bin holding the 98th
 //                    percentile; bodies with reach > cut are "large"
 //   k_hash_count / k_buckets / k_hash_fill   uniform-grid spatial hash of the small
-//                    bodies (scene id in the hash), each bucket a run of 64-byte
-//                    records holding the body's centre, reach, cell and filters;
-//                    large bodies go to a list instead
+//                    bodies (scene id in the hash), each bucket a run of 32-byte
+//                    records holding the body's centre and reach as floats, its
+//                    index, scene and cell; large bodies go to a list instead
 //   k_broad          14 lanes per small body: its own cell and the 13 cells of
 //                    the forward half-neighbourhood, one per lane, pairs with
 //                    small bodies
@@ -37,9 +37,10 @@
 //   k_sort_contacts  one wave per body, ends copied in canonical key order to
 //                    their final slots, so the iteration sums in a fixed order
 //                    whatever order the atomics produced
-// Candidate tests are conservative (a relative slack of 1e-12 on the sum of
-// reaches); the narrow phase repeats the exact bounding test, so the contact
-// set does not depend on the broad phase.
+// Candidate tests are conservative: a relative slack of 1e-12 on the sum of reaches
+// between bodies, 1e-6 of it and of the largest coordinate against a record's floats.
+// The narrow phase repeats the exact bounding test, so the contact set does not
+// depend on the broad phase.
 #pragma once
 
 #include "common.h"
@@ -285,12 +286,6 @@ __global__ void k_hash_fill(View<T> v, ContactBuf cb) {
 }
 
 // ---- narrow phase ----------------------------------------------------------------
-
-template <typename T>
-struct Narrow {
-  View<T> v;
-  ContactBuf cb;
-};
 
 template <typename T>
 __device__ __forceinline__ double free_mass(const View<T>& v, const ContactBuf& cb, int b) {
@@ -974,20 +969,20 @@ __global__ void __launch_bounds__(BL_CHUNK) k_broad(View<T> v, ContactBuf cb, in
   flush_pairs(pb, v, cb);
 }
 
-// A single scene of few bodies, [first, first + n): its whole contact search in one
-// launch.  A workgroup takes a pair of tiles of BRUTE_TILE bodies, whose geometry,
-// margins and reaches it forms once in LDS; it tests the pairs of bounding spheres
-// and runs the narrow phase on those that are near, eight lanes per pair.  The
-// workgroups past the last tile pair do the planes.  The candidate rule is the hash
-// path's, and the sort fixes the order, so the contacts do not depend on which of
-// the two found them.  A chain of latencies bounds it, not work: reaches, pairs
+// A single scene of few bodies, [0, n): its whole contact search in one launch.  A
+// workgroup takes a pair of tiles of BRUTE_TILE bodies, whose geometry, margins and
+// reaches it forms once in LDS; it tests the pairs of bounding spheres and runs the
+// narrow phase on those that are near, eight lanes per pair.  The workgroups past the
+// last tile pair do the planes.  The narrow phase repeats the exact bounding test, as
+// the hash path's does, and the sort fixes the order, so the contacts do not depend on
+// which of the two found them.  A chain of latencies bounds it, not work: reaches, pairs
 // (one thread each) and narrow phase (one thread per pair) in three launches with
 // the pair list in memory took 4.4 + 8.4 + 15 us on 200 boxes; this takes 9 to 15.
 // Tiles of 16 are level on 200 boxes and lose 3% of a step on 731, 8% on 2,040.
 constexpr int BRUTE_TILE = 32;
 
 template <typename T>
-__global__ void __launch_bounds__(256) k_contacts_brute(View<T> v, ContactBuf cb, int first, int n, int tile_pairs) {
+__global__ void __launch_bounds__(256) k_contacts_brute(View<T> v, ContactBuf cb, int n, int tile_pairs) {
   constexpr int BT = BRUTE_TILE;
   __shared__ BodyGeo<T> geo[2 * BT];
   __shared__ double pm[2 * BT], reach[2 * BT];
@@ -997,7 +992,7 @@ __global__ void __launch_bounds__(256) k_contacts_brute(View<T> v, ContactBuf cb
   const int t = threadIdx.x;
   if ((int)blockIdx.x >= tile_pairs) {
     const int k = (((int)blockIdx.x - tile_pairs) * 256 + t) / 8;
-    if (k < n) plane_body(v, cb, first + k);
+    if (k < n) plane_body(v, cb, k);
     return;
   }
   // tiles (ta, tb), ta <= tb, of tile pair tb (tb + 1) / 2 + ta
@@ -1006,12 +1001,12 @@ __global__ void __launch_bounds__(256) k_contacts_brute(View<T> v, ContactBuf cb
   while (tb * (tb + 1) / 2 > p) --tb;
   while ((tb + 1) * (tb + 2) / 2 <= p) ++tb;
   const int ta = p - tb * (tb + 1) / 2;
-  const int a0 = first + ta * BT, b0 = first + tb * BT;
+  const int a0 = ta * BT, b0 = tb * BT;
   if (t == 0) count = 0;
   if (t < 2 * BT) {
     const int i = (t < BT ? a0 : b0 - BT) + t;
     flags[t] = F_NOCONTACT;
-    if (i < first + n) {
+    if (i < n) {
       const int sc = v.bscene[i];
       if (contact_body(v, i, sc)) {
         BodyGeo<T> g;

@@ -56,7 +56,7 @@ struct Resident {
 // k_update_driven and k_factor do
 struct DrivenTable {
   int n;
-  const int *scene, *end_i, *end_j;
+  const int *end_i, *end_j;
   const double *param, *mass64;
 };
 
