@@ -55,3 +55,20 @@ def test_both_searches_find_the_oracles_contacts(P, n):
         b.step()
         for p, q in zip(g.state(), b.state(slots[0])):
             assert np.array_equal(p, q)
+
+
+@pytest.mark.parametrize("n", [731, 2016, 2017, 2047, 2048, 2049])
+@pytest.mark.parametrize("prec", [S.PREC_FP32, S.PREC_FP64], ids=["fp32", "fp64"])
+def test_both_searches_agree_up_to_the_largest_scene_of_the_first(P, prec, n):
+    """Full and partly filled last tiles at large tile-pair indices, and one body past
+    the change to the hash, which the batch's scenes take at every size."""
+    print(f"[case] contact search n={n} prec={prec}", flush=True)
+    sc = _mixed(n, prec)
+    g = P.Scene(sc)
+    g.step(2)
+    assert g.contacts()["i"].size > n
+    b = P.Batch(4, 1 << 30, prec)
+    slots = [b.admit(sc, 2), b.admit(_mixed(20, prec), 2)]
+    b.step(nsteps=2)
+    for p, q in zip(g.state(), b.state(slots[0])):
+        assert np.isfinite(p).all() and np.array_equal(p, q)
