@@ -138,9 +138,9 @@ struct EngineT final : EngineBase {
   // unit three tiles of 64 bodies but one of 128, whose eight waves take two of a SIMD's
   // places; beyond it the launch runs in rounds of whole step sequences, while one lane
   // per body still holds every tile.  In FP64 a second tile on a compute unit queues for
-  // its FP64 rate, so they are one tile for each.  Us per step (K = 20), one lane per body against quads, chains
-  // of a tile's size and, for little arithmetic, pairs joined by a spring, 64 steps a
-  // launch unless said:
+  // its FP64 rate, so they are one tile for each.  Us per step (K = 20), one lane per
+  // body against quads, chains of a tile's size and, for little arithmetic, pairs
+  // joined by a spring, 64 steps a launch unless said:
   //   FP32, 64 bodies   chains 20.1 and 14.6 at 256 tiles, 21.8 and 17.7 at 750, 23.5 and
   //                     31.4 at 1,024; pairs 18.2 and 16.8 at 750
   //   FP32, 128 bodies  chains 22.8 and 15.8 at 256, 25.3 and 34.9 at 512; pairs 18.8 and
@@ -974,8 +974,9 @@ pabd_status batch_tables(pabd_batch* b) {
 pabd_status batch_refresh(pabd_batch* b, hipStream_t st) {
   if (!b->dirty) return PABD_OK;
   hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
-  API_HIP(hipStreamIsCapturing(st, &capturing));
-  if (capturing == hipStreamCaptureStatusNone) {  // a capture forbids the wait
+  const bool known = hipStreamIsCapturing(st, &capturing) == hipSuccess;
+  if (!known) (void)hipGetLastError();
+  if (known && capturing == hipStreamCaptureStatusNone) {  // a capture forbids the wait
     if (pabd_status s = wait_foreign(b); s != PABD_OK) return s;
   }
   if (pabd_status s = batch_tables(b); s != PABD_OK) return s;
