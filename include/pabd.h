@@ -248,10 +248,11 @@ pabd_status pabd_batch_step(pabd_batch *b, void *hip_stream);
 /* nsteps steps (1..PABD_MAX_STEPS_PER_LAUNCH) of every resident scene, each
  * scene stopping at its own step count: the same result as nsteps calls of
  * pabd_batch_step.  Tiled scenes run all nsteps in one launch of the tile
- * kernel (a tile's bodies are loaded once and stored after every step);
- * flat-path scenes take one launch sequence per step.  Nothing can be admitted,
- * released or read between the steps of one call.  PABD_E_INVALID for nsteps
- * out of range. */
+ * kernel (a tile's bodies are loaded once; large batches store them after every
+ * step, batches of few tiles after a launch's or a scene's last); flat-path
+ * scenes take one launch sequence per step.  Nothing can be admitted, released
+ * or read between the steps of one call.  PABD_E_INVALID for nsteps out of
+ * range. */
 #define PABD_MAX_STEPS_PER_LAUNCH 256
 pabd_status pabd_batch_steps(pabd_batch *b, int32_t nsteps, void *hip_stream);
 /* Slots whose scenes finished all their steps (host bookkeeping, no sync). */

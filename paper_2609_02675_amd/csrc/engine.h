@@ -558,7 +558,12 @@ struct Engine {
   // larger ones one lane per body (k_resident_net): up to four waves each have a
   // SIMD to themselves, beyond them the four inversions of a quad queue (us per step:
   // 11 x 11 net of order 6 in FP64 88 with quads, 70 without; 16 x 16 in FP32 123
-  // and 69).  Quadratic bonds alone stay in one phase (8 x 8 net 21 us, two phases
+  // and 69).  k_resident_net runs up to what LDS holds (NET_ENDS).  Against the flat
+  // kernels it gains up to about 500 bodies (nets of order 4, us per step: 121 bodies 54
+  // and 140, 484 bodies 122 and 145, 625 bodies 156 and 146; in FP64 121 bodies 76 and
+  // 145, 400 bodies 157 and 152; driven slider cranks, 512 bodies 116 and 133, 560 bodies
+  // 138 and 133; augmented chains of 500 40 and 62, of 700 68 and 62, of 1,000 85 and
+  // 62), and loses to them beyond.  Quadratic bonds alone stay in one phase (8 x 8 net 21 us, two phases
   // 26; 16 x 16 34 and 50).
   static constexpr int QUADS_MAX = 256;
   // nsteps steps of the plain scene in the resident kernels, after a contact scene's

@@ -1052,9 +1052,9 @@ __global__ void __launch_bounds__(256) k_contacts_brute(View<T> v, ContactBuf cb
 // one thread per candidate pair (grid-stride); the workgroups past the first
 // `pair_blocks` do the contacts with planes, eight lanes per body.  Two atomics per
 // contact, each waited for, were the chain that bound it in served batches (21 ->
-// 11 us with one per body and pair); 125,000 blocks take 321 us with the planes, as
-// before (277, and 50 for planes inside the broad kernel), with eight lanes per
-// pair 339.
+// 11 us with one per body and pair); 125,000 blocks in motion take 321 us with the
+// planes, as before (277, and 50 for planes inside the broad kernel), with eight lanes
+// per pair 339 (from rest 299).
 template <typename T>
 __global__ void __launch_bounds__(256) k_narrow_pairs(View<T> v, ContactBuf cb, int pair_blocks) {
   if ((int)blockIdx.x >= pair_blocks) {
@@ -1087,8 +1087,8 @@ __global__ void __launch_bounds__(256) k_narrow_pairs(View<T> v, ContactBuf cb, 
 // its own, which is the slot's rank.  Bodies with more ends than the registers
 // hold count against the keys in memory instead.  Up to 64 ends, the usual case,
 // one key per lane and the record read beside it: the counting, about 30
-// instructions a key with four keys per lane, bound the kernel (125,000 blocks 209 ->
-// 166 us, 384 MB moved; 50,000 spheres 57 -> 43).
+// instructions a key with four keys per lane, bound the kernel (125,000 blocks in motion
+// 209 -> 166 us, 384 MB moved, from rest 203 -> 137; 50,000 spheres 57 -> 43).
 constexpr int SORT_REG = 4;
 
 __device__ __forceinline__ unsigned long long lane_key(unsigned long long k, int src) {

@@ -27,7 +27,8 @@
 // launch per step): eight-body chain 0.044 -> 0.025 ms (FP64 0.066 -> 0.051),
 // chain of 200 0.057 -> 0.027, of 500 0.075 -> 0.040, of 1,000 0.101 -> 0.085,
 // 11 x 11 net of order 4 in FP64 0.164 -> 0.074 (0.090 with one lane walking a body's
-// ends), 16 x 16 net of order 6 0.180 -> 0.070, pile of 16 boxes 0.118 -> 0.095, of 60 0.134 -> 0.111 with its contact construction.
+// ends), 16 x 16 net of order 6 0.180 -> 0.070, pile of 16 boxes 0.118 -> 0.095, of 60
+// 0.134 -> 0.111 with its contact construction, of 128 falling boxes 0.087 -> 0.051.
 #pragma once
 
 #include "common.h"
